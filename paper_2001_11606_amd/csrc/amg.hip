@@ -275,6 +275,37 @@ __global__ void k_i64_to_i32(int64_t n, const int64_t* __restrict__ a, int32_t* 
 // ascending order, each the sum of the members' entries mapping to it; the
 // entries mapping to I itself and the members' diagonals form the coarse
 // diagonal.  Entries of rows left out of the coarse space (pmap -1) drop out.
+//
+// The distinct columns are collected in a hash table in LDS, one per wave,
+// which the entries are read into once (kGalRows members' rows in flight);
+// the keys are then ranked.  A search for the next larger column over all
+// entries per distinct column, which this replaces, read the entries about 60
+// times: 5.5 ms a set-up at 64^3 particles against 0.2 ms.  That search
+// remains for coarse rows of more than kGalMost distinct columns.  FILL sums
+// in the table with LDS adds of the one wave that owns it, executed in program
+// order, so the order of the additions is fixed.
+constexpr int kGalSlots = 512;
+constexpr int kGalMost = 384;
+constexpr int kGalRows = 4;
+
+// slot of key (>= 0), inserting it; *distinct counts the keys, -1: more than kGalMost
+__device__ __forceinline__ int gal_slot(int32_t key, int* keys, int* distinct) {
+  int s = (int)(((uint32_t)key * 2654435761u) >> 23) & (kGalSlots - 1);
+  while (true) {
+    int cur = ((volatile int*)keys)[s];
+    if (cur == -1) {
+      if (((volatile int*)distinct)[0] >= kGalMost) return -1;
+      cur = atomicCAS(&keys[s], -1, key);
+      if (cur == -1) {
+        atomicAdd(distinct, 1);
+        return s;
+      }
+    }
+    if (cur == key) return s;
+    s = (s + 1) & (kGalSlots - 1);
+  }
+}
+
 template <bool FILL>
 __global__ void __launch_bounds__(kBlock)
 k_galerkin(int64_t nc, const int64_t* __restrict__ crange, const int32_t* __restrict__ amem,
@@ -283,15 +314,96 @@ k_galerkin(int64_t nc, const int64_t* __restrict__ crange, const int32_t* __rest
            const int32_t* __restrict__ pmap, int64_t* __restrict__ cnt,
            const int64_t* __restrict__ crp, int32_t* __restrict__ ccol,
            double* __restrict__ cval, double* __restrict__ cdiag) {
-  const int lane = threadIdx.x & (kWave - 1);
+  constexpr int NW = kBlock / kWave;
+  __shared__ int skey[NW][kGalSlots];
+  __shared__ double sval[FILL ? NW : 1][FILL ? kGalSlots : 1];
+  __shared__ uint16_t slist[FILL ? NW : 1][FILL ? kGalSlots : 1];
+  __shared__ int sdist[NW];
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
   const int64_t I = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / kWave;
-  if (I >= nc) return;   // whole wavefront exits together
-  const int64_t m0 = crange[I], m1 = crange[I + 1];
+  const bool live = I < nc;
+  int* keys = skey[w];
+  for (int s = lane; s < kGalSlots; s += kWave) {
+    keys[s] = -1;
+    if (FILL) sval[w][s] = 0.0;
+  }
+  if (lane == 0) sdist[w] = 0;
+  __syncthreads();
+  const int64_t m0 = live ? crange[I] : 0, m1 = live ? crange[I + 1] : 0;
   double dsum = 0.0;
   if (FILL) {
     for (int64_t q = m0 + lane; q < m1; q += kWave) dsum += diag[amem[q]];
     dsum = group_sum<kWave>(dsum);
   }
+  // entries of the members' rows into the table
+  bool full = false;
+  for (int64_t q = m0; q < m1; q += kGalRows) {
+    int64_t k0[kGalRows], k1[kGalRows];
+    int32_t pc[kGalRows];
+    double v[kGalRows];
+    int64_t longest = 0;
+#pragma unroll
+    for (int u = 0; u < kGalRows; ++u) {
+      k0[u] = k1[u] = 0;
+      if (q + u < m1) {
+        const int32_t i = amem[q + u];
+        k0[u] = rp[i];
+        k1[u] = rp[i + 1];
+      }
+      longest = k1[u] - k0[u] > longest ? k1[u] - k0[u] : longest;
+    }
+    for (int64_t p = 0; p < longest; p += kWave) {   // the same for all lanes
+#pragma unroll
+      for (int u = 0; u < kGalRows; ++u) {
+        const int64_t k = k0[u] + p + lane;
+        pc[u] = k < k1[u] ? col[k] : -1;
+        v[u] = FILL && k < k1[u] ? val[k] : 0.0;
+      }
+#pragma unroll
+      for (int u = 0; u < kGalRows; ++u) pc[u] = pc[u] >= 0 ? pmap[pc[u]] : -1;
+#pragma unroll
+      for (int u = 0; u < kGalRows; ++u) {
+        const int s = pc[u] >= 0 ? gal_slot(pc[u], keys, &sdist[w]) : 0;
+        full |= s < 0;
+        if (FILL) RT_WAVE_LDS_ADD(pc[u] >= 0 && s >= 0, &sval[w][s < 0 ? 0 : s], v[u]);
+      }
+    }
+  }
+  full = __ballot(full) != 0;
+  __syncthreads();
+  const int distinct = sdist[w];
+  if (!full) {
+    if (!FILL) {
+      int self = 0;
+      for (int s = lane; s < kGalSlots; s += kWave) self += keys[s] == (int32_t)I;
+      self = group_sum<kWave>(self);
+      if (live && lane == 0) cnt[I] = distinct - self;
+    } else {
+      // occupied slots in slot order, then each key at its rank
+      int have = 0;
+      for (int s = lane; s < kGalSlots; s += kWave) {
+        const bool on = keys[s] != -1 && keys[s] != (int32_t)I;
+        const unsigned long long m = __ballot(on);
+        if (on) slist[w][have + __popcll(m & ((1ull << lane) - 1))] = (uint16_t)s;
+        if (keys[s] == (int32_t)I) sdist[w] = -1 - s;   // the diagonal's slot
+        have += __popcll(m);
+      }
+      __syncthreads();
+      const int64_t out = live ? crp[I] : 0;
+      for (int a = lane; a < have; a += kWave) {
+        const int s = slist[w][a], key = keys[s];
+        int rank = 0;
+        for (int b = 0; b < have; ++b) rank += keys[slist[w][b]] < key;
+        ccol[out + rank] = key;
+        cval[out + rank] = sval[w][s];
+      }
+      if (live && lane == 0) cdiag[I] = dsum + (sdist[w] < 0 ? sval[w][-1 - sdist[w]] : 0.0);
+    }
+    return;
+  }
+  if (FILL) __syncthreads();   // the other waves' barrier above
+  // more distinct columns than the table takes: the next larger column, then
+  // its sum, from all entries each time
   int32_t last = -1;
   int64_t out = FILL ? crp[I] : 0;
   int64_t count = 0;
@@ -588,27 +700,65 @@ __global__ void k_dense_fill(int64_t n, const int64_t* __restrict__ rp,
   for (int64_t k = rp[i]; k < rp[i + 1]; ++k) M[i * n + col[k]] = val[k];
 }
 
-// In-place Gauss-Jordan inversion of an SPD matrix (positive pivots, no
-// pivoting needed), one workgroup, n <= kDenseMax; colk holds column k of the step.
-__global__ void __launch_bounds__(1024) k_gauss_jordan(int n, double* __restrict__ M) {
-  __shared__ double colk[kDenseMax];
-  const int tid = threadIdx.x, nt = blockDim.x;
-  for (int k = 0; k < n; ++k) {
-    const double piv = 1.0 / M[(int64_t)k * n + k];
-    for (int i = tid; i < n; i += nt) colk[i] = M[(int64_t)i * n + k];
-    __syncthreads();
-    for (int j = tid; j < n; j += nt)
-      if (j != k) M[(int64_t)k * n + j] *= piv;
-    __syncthreads();
-    const int64_t nn = (int64_t)n * n;
-    for (int64_t idx = tid; idx < nn; idx += nt) {
-      const int i = (int)(idx / n), j = (int)(idx % n);
-      if (i == k) continue;
-      if (j == k) M[idx] = -colk[i] * piv;
-      else M[idx] -= colk[i] * M[(int64_t)k * n + j];
+// One step of a blocked Gauss-Jordan inversion of an SPD matrix (no pivoting
+// needed), n <= kDenseMax, from src into dst: with P the inverse of the
+// 32 x 32 pivot block K, block (K, K) becomes P, (K, J) P A_KJ, (I, K) -A_IK P
+// and (I, J) A_IJ - A_IK P A_KJ.  One workgroup per 32 x 32 block; each inverts
+// the pivot block itself (32 steps in LDS), so that a step is one launch of
+// about 30 us, bound by those steps' divisions and barriers.  A coarsest level
+// of 170 rows takes 6 of them (0.18 ms), where one workgroup eliminating
+// column after column in global memory took 1.9 ms.  Rows and columns past n
+// read as the identity.
+constexpr int kGjBlock = 32;
+
+__device__ __forceinline__ double gj_read(const double* M, int n, int i, int j) {
+  return i < n && j < n ? M[(int64_t)i * n + j] : (i == j ? 1.0 : 0.0);
+}
+
+__global__ void __launch_bounds__(kBlock)
+k_gj_step(int n, int kb, const double* __restrict__ src, double* __restrict__ dst) {
+  constexpr int B = kGjBlock, PER = B * B / kBlock;   // entries per thread
+  __shared__ double P[B][B + 1], L[B][B + 1], R[B][B + 1], Q[B][B + 1];
+  const int tid = threadIdx.x, j = tid % B, i0 = tid / B;   // entries (i0 + 8 e, j)
+  const int I = blockIdx.y, J = blockIdx.x, K = kb * B;
+  for (int e = 0; e < PER; ++e) {
+    const int i = i0 + e * (kBlock / B);
+    P[i][j] = gj_read(src, n, K + i, K + j);
+    L[i][j] = gj_read(src, n, I * B + i, K + j);
+    R[i][j] = gj_read(src, n, K + i, J * B + j);
+  }
+  __syncthreads();
+  for (int k = 0; k < B; ++k) {
+    const double piv = 1.0 / P[k][k];
+    double v[PER];
+    for (int e = 0; e < PER; ++e) {
+      const int i = i0 + e * (kBlock / B);
+      if (i == k) v[e] = j == k ? piv : P[k][j] * piv;
+      else if (j == k) v[e] = -P[i][k] * piv;
+      else v[e] = P[i][j] - P[i][k] * (P[k][j] * piv);
     }
-    if (tid == 0) M[(int64_t)k * n + k] = piv;
     __syncthreads();
+    for (int e = 0; e < PER; ++e) P[i0 + e * (kBlock / B)][j] = v[e];
+    __syncthreads();
+  }
+  // Q = P A_KJ (J != K), else P
+  for (int e = 0; e < PER; ++e) {
+    const int i = i0 + e * (kBlock / B);
+    double s = 0.0;
+    if (J == kb) s = P[i][j];
+    else
+      for (int k = 0; k < B; ++k) s += P[i][k] * R[k][j];
+    Q[i][j] = s;
+  }
+  __syncthreads();
+  for (int e = 0; e < PER; ++e) {
+    const int i = i0 + e * (kBlock / B), gi = I * B + i, gj = J * B + j;
+    double s = Q[i][j];
+    if (I != kb) {
+      s = J == kb ? 0.0 : gj_read(src, n, gi, gj);
+      for (int k = 0; k < B; ++k) s -= L[i][k] * Q[k][j];
+    }
+    if (gi < n && gj < n) dst[(int64_t)gi * n + gj] = s;
   }
 }
 
@@ -637,18 +787,25 @@ __global__ void k_scale(int64_t n, const T* __restrict__ s, const T* __restrict_
   if (i < n) x[i] = s[i] * b[i];
 }
 
-// bc[I] = sum of r over the members of aggregate I, in ascending order
+// bc[I] = sum of r over the members of aggregate I: kRestrictG lanes per
+// aggregate (about 16 members), each lane's members in ascending order, then
+// the lanes; with one lane per aggregate the members' loads queue up one
+// behind the other (8.9 us a call against 4.0 us at 64^3 particles)
+constexpr int kRestrictG = 16;
 template <typename T>
-__global__ void k_restrict(int64_t nc, const int64_t* __restrict__ crange,
-                           const int32_t* __restrict__ amem, const T* __restrict__ r,
-                           T* __restrict__ bc, const int32_t* __restrict__ tp,
-                           const int32_t* __restrict__ stop) {
-  if (stop && stop[tp ? tp[blockIdx.x] : 0]) return;
-  int64_t I = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (I >= nc) return;
+__global__ void __launch_bounds__(kBlock)
+k_restrict(int64_t nc, const int64_t* __restrict__ crange, const int32_t* __restrict__ amem,
+           const T* __restrict__ r, T* __restrict__ bc, const int32_t* __restrict__ tp,
+           const int32_t* __restrict__ stop) {
+  const int64_t I = (blockIdx.x * (int64_t)kBlock + threadIdx.x) / kRestrictG;
+  // a batch's flags are kept per kTileRows coarse rows; a block's rows share one
+  if (stop && stop[tp ? tp[blockIdx.x / kRestrictG] : 0]) return;
+  if (I >= nc) return;   // whole groups leave together
+  const int lane = threadIdx.x & (kRestrictG - 1);
   T s = 0;
-  for (int64_t q = crange[I]; q < crange[I + 1]; ++q) s += r[amem[q]];
-  bc[I] = s;
+  for (int64_t q = crange[I] + lane; q < crange[I + 1]; q += kRestrictG) s += r[amem[q]];
+  s = group_sum<kRestrictG>(s);
+  if (lane == 0) bc[I] = s;
 }
 
 // bc = P^T r with the transpose's rows (fine rows ascending)
@@ -1167,11 +1324,18 @@ int amg_setup(rt_ctx* ctx, rt_matrix* A) {
   if (A->coarse_direct) {
     const int64_t nn = Lc.n * Lc.n;
     RT_CHECK(A->coarse_inv.reserve(nn));
-    hipLaunchKernelGGL(k_dense_zero, dim3(grid_for(nn)), dim3(kBlock), 0, st, nn,
-                       A->coarse_inv.p);
+    // the steps alternate between two buffers and end in coarse_inv
+    DevBuf<double> other;
+    RT_CHECK(other.reserve(nn));
+    const int steps = (int)((Lc.n + kGjBlock - 1) / kGjBlock);
+    double* src = steps % 2 == 0 ? A->coarse_inv.p : other.p;
+    double* dst = steps % 2 == 0 ? other.p : A->coarse_inv.p;
+    hipLaunchKernelGGL(k_dense_zero, dim3(grid_for(nn)), dim3(kBlock), 0, st, nn, src);
     hipLaunchKernelGGL(k_dense_fill, dim3(grid_for(Lc.n)), dim3(kBlock), 0, st, Lc.n, Lc.rp.p,
-                       Lc.col.p, Lc.val64.p, Lc.diag64.p, A->coarse_inv.p);
-    hipLaunchKernelGGL(k_gauss_jordan, dim3(1), dim3(1024), 0, st, (int)Lc.n, A->coarse_inv.p);
+                       Lc.col.p, Lc.val64.p, Lc.diag64.p, src);
+    for (int k = 0; k < steps; ++k, std::swap(src, dst))
+      hipLaunchKernelGGL(k_gj_step, dim3(steps, steps), dim3(kBlock), 0, st, (int)Lc.n, k, src,
+                         dst);
     RT_LAUNCH_CHECK();
   }
   return RT_OK;
@@ -1310,7 +1474,7 @@ static int vcycle_level(rt_ctx* ctx, rt_matrix* A, size_t l, const T* b, T* out,
     hipLaunchKernelGGL((k_restrict_p<T, T>), dim3(grid_for(C.n)), dim3(kBlock), 0, st, C.n,
                        L.pt_rp.p, L.pt_row.p, B::ptv(L), r, B::b(C), stop);
   else
-    hipLaunchKernelGGL(k_restrict<T>, dim3(grid_for(C.n)), dim3(kBlock), 0, st, C.n, L.crange.p,
+    hipLaunchKernelGGL(k_restrict<T>, dim3(grid_for(C.n * kRestrictG)), dim3(kBlock), 0, st, C.n, L.crange.p,
                        L.amem.p, r, B::b(C), tpc, skc);
   RT_LAUNCH_CHECK();
   if (A->amg.cycle == 3 && l + 2 < nl)

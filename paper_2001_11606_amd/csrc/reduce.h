@@ -27,6 +27,17 @@ __device__ __forceinline__ T group_max(T v) {
   return v;
 }
 
+// v added to *p (LDS) in the lanes where active, called by all lanes of a wave.
+// The LDS adds of one wave execute in program order, so where no other wave
+// touches the address the order of the additions is fixed.  (unsafeAtomicAdd:
+// one ds_add instruction; a plain atomicAdd may be a compare-and-swap loop.)
+#ifndef RT_WAVE_LDS_ADD
+#define RT_WAVE_LDS_ADD(active, p, v)      \
+  do {                                     \
+    if (active) unsafeAtomicAdd((p), (v)); \
+  } while (0)
+#endif
+
 // Block-wide sum of one value per thread; result valid in thread 0.
 // `sh` must hold blockDim.x / 64 elements.
 template <typename T>

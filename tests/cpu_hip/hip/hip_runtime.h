@@ -198,6 +198,16 @@ inline int atomicMin(int* p, int v) {
   }
   return cur;
 }
+inline int atomicMax(int* p, int v) {
+  std::atomic_ref<int> a(*p);
+  int cur = a.load();
+  while (v > cur && !a.compare_exchange_weak(cur, v)) {
+  }
+  return cur;
+}
+inline unsigned long long atomicOr(unsigned long long* p, unsigned long long v) {
+  return std::atomic_ref<unsigned long long>(*p).fetch_or(v);
+}
 inline void __threadfence() {}
 
 template <typename T>
@@ -267,6 +277,22 @@ inline unsigned long long __ballot(int pred) {
   bar.arrive_and_wait();
   return m;
 }
+// LDS add of all lanes of a wave, in lane order (RT_WAVE_LDS_ADD in reduce.h)
+template <typename T>
+inline void wave_lds_add(bool active, T* p, T v) {
+  const int t = (int)threadIdx.x;
+  static std::vector<T*> ptr(1024);
+  static std::vector<T> val(1024);
+  auto& bar = *cpuhip::g_block.group_bar[6][t / 64];
+  ptr[t] = active ? p : nullptr;
+  val[t] = v;
+  bar.arrive_and_wait();
+  if (t % 64 == 0)
+    for (int l = t; l < t + 64 && l < (int)blockDim.x; ++l)
+      if (ptr[l]) *ptr[l] += val[l];
+  bar.arrive_and_wait();
+}
+#define RT_WAVE_LDS_ADD(active, p, v) wave_lds_add((active), (p), (v))
 inline int __popcll(unsigned long long x) { return __builtin_popcountll(x); }
 
 template <typename... KArgs, typename... Args>
