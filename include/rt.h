@@ -20,6 +20,8 @@
  *   - Positions are structure-of-arrays: pos[alpha * n_total + i].
  *   - Library objects (rt_ctx, rt_neighbors, rt_matrix) are opaque handles,
  *     created by the library and released with the matching *_free/destroy.
+ *     A matrix keeps the neighbour lists it was assembled on: their memory is
+ *     released with the last of the neighbour handle and its matrices.
  *   - Every call is ordered on the context's HIP stream.  Calls that return
  *     counts or statistics synchronise that stream before returning.
  *   - Return value: RT_OK (0); a positive soft status (outputs valid); or a
@@ -266,6 +268,10 @@ void rt_matrix_free(rt_matrix* A);
  * entries), x is read from LDS, and E is the number of rows a lane group
  * keeps in flight; a level without a tiled form runs its default plain shape
  * instead.
+ * A matrix assembled with max_levels 1 and tiled_spmv 1 keeps only the entries
+ * right of the diagonal (each pair once); its tiled shapes run on that form, E
+ * being the groups of four pairs a lane has in work, and its CSR rows are made
+ * when a plain shape, rt_matrix_tune or an export first asks for them.
  * rt_spmv_shapes writes the (G, E, tiled) of up to max shapes (any pointer
  * may be NULL) and returns how many exist.  rt_matrix_tune times the Krylov-loop product on every
  * level of A with every shape, in FP64 and, when A holds FP32 copies, FP32,

@@ -169,7 +169,7 @@ struct AsmArgs {
   const int32_t* nidx;
   const double *sp4, *VD, *sa, *f, *Eall;
   int32_t* col;                       // written when the structure is new, else NULL
-  double *val64, *diag64, *dinv64, *sinv64, *g;
+  double *val64, *diag64, *dinv64, *sinv64, *g;   // diag64 NULL: the values alone
   float *val32, *diag32, *dinv32, *sinv32;
   PeriodicBox box;                    // periodic axes of the neighbour lists
 };
@@ -235,7 +235,7 @@ k_assemble(int64_t nin, int64_t n, int kernel, double dt, double c, AsmArgs A, i
   suma = group_sum<G>(suma);
   gsum = group_sum<G>(gsum);
   absoff = group_sum<G>(absoff);
-  if (lane == 0) {
+  if (lane == 0 && A.diag64) {
     const double d = Vi * (1.0 / dt + c * A.sa[i] * A.f[i]) + Vi * suma;
     A.diag64[i] = d;
     A.dinv64[i] = 1.0 / d;                 // Jacobi preconditioner
@@ -286,13 +286,78 @@ int pick_group(double avg_row) {
   return 4;
 }
 
+// Row pointers, columns and values of the fine level as CSR rows; with_diag:
+// also the diagonal and ghost couplings (a level in pair form has them already).
+int assemble_csr(rt_ctx* ctx, rt_matrix* A, bool with_diag) {
+  hipStream_t st = ctx->stream;
+  const rt_neighbors* nb = A->nb;
+  const int64_t n = nb->n_total, nin = nb->n_interior;
+  Level& L = A->levels[0];
+  const bool new_rows = !L.csr_rows;
+  if (new_rows) {
+    RT_CHECK(L.rp.reserve(nin + 1));
+    DevBuf<int64_t> cnt;
+    RT_CHECK(cnt.reserve(nin + 1));
+    RT_CHECK_HIP(hipMemsetAsync(cnt.p + nin, 0, sizeof(int64_t), st));
+    if (nin > 0) {
+      hipLaunchKernelGGL(k_int_counts, dim3(grid_for(nin)), dim3(kBlock), 0, st, nin,
+                         nb->n_int_nbrs.p, cnt.p);
+      RT_LAUNCH_CHECK();
+    }
+    RT_CHECK((scan<int64_t, int64_t>(ctx, cnt.p, L.rp.p, nin + 1, false)));
+    RT_CHECK(ctx->sync_read(L.rp.p + nin, sizeof(int64_t)));
+    int64_t nnz = 0;
+    std::memcpy(&nnz, ctx->host, sizeof(int64_t));
+    L.nnz = nnz;
+    RT_CHECK(max_nonneg<int64_t>(ctx, cnt.p, nin, &L.max_row));
+    RT_CHECK(L.col.reserve(nnz));
+  }
+  RT_CHECK(L.val64.reserve(L.nnz + kSpmvPad));
+  const bool fp32 = A->has_fp32;
+  if (with_diag)
+    for (auto* b : {&L.diag64, &L.dinv64, &L.sinv64}) RT_CHECK(b->reserve(nin));
+  if (fp32) {
+    RT_CHECK(L.val32.reserve(L.nnz + kSpmvPad));
+    if (with_diag)
+      for (auto* b : {&L.diag32, &L.dinv32, &L.sinv32}) RT_CHECK(b->reserve(nin));
+  }
+  if (nin > 0) {
+    AsmArgs aa{nb->ptr.p, L.rp.p, nb->idx.p, nb->sp4.p, A->VD.p, A->sa.p,
+               A->f.p, A->Eall.p, new_rows ? L.col.p : nullptr, L.val64.p,
+               with_diag ? L.diag64.p : nullptr, L.dinv64.p, L.sinv64.p, A->g.p,
+               fp32 ? L.val32.p : nullptr, fp32 ? L.diag32.p : nullptr,
+               fp32 ? L.dinv32.p : nullptr, fp32 ? L.sinv32.p : nullptr, nb->box};
+    const double avg = nin ? (double)nb->npairs / (double)n : 0.0;
+    const int G = pick_group(avg);
+    const int per = (grid_for(nin * (int64_t)G, kBlock) + kXcd - 1) / kXcd;
+    const int grid = per * kXcd;
+#define RT_ASM(D_, G_)                                                                           \
+  hipLaunchKernelGGL((k_assemble<D_, G_, 4>), dim3(grid), dim3(kBlock), 0, st, nin, n, nb->kernel, \
+                     A->dt, A->c, aa, per)
+    if (nb->dim == 3) {
+      if (G == 64) RT_ASM(3, 64); else if (G == 16) RT_ASM(3, 16);
+      else if (G == 8) RT_ASM(3, 8); else RT_ASM(3, 4);
+    } else {
+      if (G == 64) RT_ASM(2, 64); else if (G == 16) RT_ASM(2, 16);
+      else if (G == 8) RT_ASM(2, 8); else RT_ASM(2, 4);
+    }
+#undef RT_ASM
+    RT_LAUNCH_CHECK();
+  }
+  L.csr_rows = L.csr_vals = true;
+  return RT_OK;
+}
+
 }  // namespace
 
 int assemble(rt_ctx* ctx, const rt_neighbors* nb, const rt_step_inputs* in, rt_matrix* A,
              bool new_structure) {
   hipStream_t st = ctx->stream;
   const int64_t n = nb->n_total, nin = nb->n_interior;
-  A->nb = nb;
+  if (A->nb != nb) {
+    const_cast<rt_neighbors*>(nb)->refs.fetch_add(1);
+    A->nb = nb;
+  }
   A->n = nin;
   A->n_total = n;
   A->dt = in->dt;
@@ -334,58 +399,32 @@ int assemble(rt_ctx* ctx, const rt_neighbors* nb, const rt_step_inputs* in, rt_m
 
   if (A->levels.empty()) A->levels.resize(1);
   Level& L = A->levels[0];
-  if (new_structure) {
-    L.n = nin;
-    RT_CHECK(L.rp.reserve(nin + 1));
-    DevBuf<int64_t> cnt;
-    RT_CHECK(cnt.reserve(nin + 1));
-    RT_CHECK_HIP(hipMemsetAsync(cnt.p + nin, 0, sizeof(int64_t), st));
-    if (nin > 0) {
-      hipLaunchKernelGGL(k_int_counts, dim3(grid_for(nin)), dim3(kBlock), 0, st, nin,
-                         nb->n_int_nbrs.p, cnt.p);
-      RT_LAUNCH_CHECK();
-    }
-    RT_CHECK((scan<int64_t, int64_t>(ctx, cnt.p, L.rp.p, nin + 1, false)));
-    RT_CHECK(ctx->sync_read(L.rp.p + nin, sizeof(int64_t)));
-    int64_t nnz = 0;
-    std::memcpy(&nnz, ctx->host, sizeof(int64_t));
-    L.nnz = nnz;
-    RT_CHECK(max_nonneg<int64_t>(ctx, cnt.p, nin, &L.max_row));
-    RT_CHECK(L.col.reserve(nnz));
-  }
-  RT_CHECK(L.val64.reserve(L.nnz + kSpmvPad));
-  for (auto* b : {&L.diag64, &L.dinv64, &L.sinv64}) RT_CHECK(b->reserve(nin));
+  L.n = nin;
   const bool fp32 = A->amg.build_fp32 != 0;
-  if (fp32) {
-    RT_CHECK(L.val32.reserve(L.nnz + kSpmvPad));
-    for (auto* b : {&L.diag32, &L.dinv32, &L.sinv32}) RT_CHECK(b->reserve(nin));
-  }
   A->has_fp32 = fp32;
-  if (nin > 0) {
-    AsmArgs aa{nb->ptr.p, L.rp.p, nb->idx.p, nb->sp4.p, A->VD.p, A->sa.p,
-               A->f.p, A->Eall.p, new_structure ? L.col.p : nullptr, L.val64.p, L.diag64.p,
-               L.dinv64.p, L.sinv64.p, A->g.p, fp32 ? L.val32.p : nullptr,
-               fp32 ? L.diag32.p : nullptr, fp32 ? L.dinv32.p : nullptr,
-               fp32 ? L.sinv32.p : nullptr, nb->box};
-    const double avg = nin ? (double)nb->npairs / (double)n : 0.0;
-    const int G = pick_group(avg);
-    const int per = (grid_for(nin * (int64_t)G, kBlock) + kXcd - 1) / kXcd;
-    const int grid = per * kXcd;
-#define RT_ASM(D_, G_)                                                                           \
-  hipLaunchKernelGGL((k_assemble<D_, G_, 4>), dim3(grid), dim3(kBlock), 0, st, nin, n, nb->kernel, \
-                     in->dt, in->c, aa, per)
-    if (nb->dim == 3) {
-      if (G == 64) RT_ASM(3, 64); else if (G == 16) RT_ASM(3, 16);
-      else if (G == 8) RT_ASM(3, 8); else RT_ASM(3, 4);
-    } else {
-      if (G == 64) RT_ASM(2, 64); else if (G == 16) RT_ASM(2, 16);
-      else if (G == 8) RT_ASM(2, 8); else RT_ASM(2, 4);
-    }
-#undef RT_ASM
-    RT_LAUNCH_CHECK();
+  // A matrix without a hierarchy is kept in pair form: half the bytes per
+  // product and each pair evaluated once.  The set-up of a hierarchy reads
+  // CSR rows, and so does a matrix asked to be untiled or whose tiles do not
+  // fit the form.
+  const bool pairs = A->amg.max_levels == 1 && A->amg.tiled_spmv;
+  bool tiles = new_structure && A->amg.tiled_spmv;
+  if (new_structure) {
+    L.csr_rows = false;
+    L.pair.on = false;
+    if (pairs) RT_CHECK(build_pairs(ctx, nb, L));
+  } else if (L.pair.on && !pairs) {   // re-assembled with other options
+    L.pair.on = false;
+    tiles = true;
   }
-  if (new_structure && A->amg.tiled_spmv) RT_CHECK(build_tiles(ctx, L));
+  L.csr_vals = false;
+  if (L.pair.on) return assemble_pairs(ctx, A);
+  RT_CHECK(assemble_csr(ctx, A, true));
+  if (tiles) RT_CHECK(build_tiles(ctx, L));
   return RT_OK;
+}
+
+int ensure_csr(rt_ctx* ctx, rt_matrix* A) {
+  return A->levels[0].csr_vals ? RT_OK : assemble_csr(ctx, A, false);
 }
 
 int matrix_export(rt_ctx* ctx, const rt_matrix* A, int64_t* urp, int32_t* ucol, double* uval,
@@ -394,6 +433,7 @@ int matrix_export(rt_ctx* ctx, const rt_matrix* A, int64_t* urp, int32_t* ucol, 
   const rt_neighbors* nb = A->nb;
   const Level& L = A->levels[0];
   const int64_t nin = A->n;
+  RT_CHECK(ensure_csr(ctx, const_cast<rt_matrix*>(A)));   // made on demand for a pair-form level
   DevBuf<int64_t> cnt;
   RT_CHECK(cnt.reserve(nin + 1));
   RT_CHECK_HIP(hipMemsetAsync(cnt.p + nin, 0, sizeof(int64_t), st));
@@ -490,7 +530,8 @@ int rt_matrix_get_info(const rt_matrix* A, rt_matrix_info* info) {
   for (size_t l = 0; l < A->levels.size() && l < 16; ++l) {
     info->level_n[l] = A->levels[l].n;
     info->level_nnz[l] = A->levels[l].nnz + A->levels[l].n;
-    info->level_tile_cols[l] = A->levels[l].tiled ? A->levels[l].tile_cols_total : 0;
+    info->level_tile_cols[l] =
+        A->levels[l].tiled || A->levels[l].pair.on ? A->levels[l].tile_cols_total : 0;
     info->level_p_nnz[l] = A->levels[l].smoothed ? A->levels[l].p_nnz : 0;
   }
   return RT_OK;

@@ -24,6 +24,7 @@
 
 #include "internal.h"
 #include "material.h"
+#include "pair.h"
 #include "prim.h"
 #include "reduce.h"
 #include "spmv.h"
@@ -91,7 +92,7 @@ namespace {
 
 struct CopyArgs {
   // source problem (sorted order)
-  const int64_t* rp;
+  const int64_t* rp;   // NULL: the batch is in pair form
   const double *diag64, *dinv64, *V, *sa, *f, *rho, *cv, *m, *e_prev, *E_prev, *Qe, *QE, *g;
   const float *diag32, *dinv32;
   const int32_t* perm;
@@ -110,7 +111,7 @@ __global__ void k_b_copy_rows(CopyArgs A) {
   if (s >= A.nrows) return;
   const int64_t i = A.row0 + s;
   if (s < A.nin) {
-    A.rp_d[i] = A.nnz0 + A.rp[s];
+    if (A.rp) A.rp_d[i] = A.nnz0 + A.rp[s];
     A.diag64_d[i] = A.diag64[s];
     A.dinv64_d[i] = A.dinv64[s];
     if (A.diag32_d) {
@@ -130,7 +131,7 @@ __global__ void k_b_copy_rows(CopyArgs A) {
     A.g_d[i] = A.g[s];
     A.perm_d[i] = (int32_t)(A.user0 + A.perm[s]);
   } else {
-    A.rp_d[i] = A.nnz_end;
+    if (A.rp) A.rp_d[i] = A.nnz_end;
     A.diag64_d[i] = 1.0;
     A.dinv64_d[i] = 1.0;
     if (A.diag32_d) {
@@ -150,6 +151,58 @@ __global__ void k_b_copy_rows(CopyArgs A) {
     A.g_d[i] = 0.0;
     A.perm_d[i] = -1;
   }
+}
+
+// Pair form of one problem (see pair.h), one block per tile: its groups,
+// external columns and rows' incoming sums at the batch's offsets.
+struct PairCopy {
+  PairArgs src;
+  PairIn in;
+  const double* val64;
+  const float* val32;   // NULL: no FP32 copies
+  int64_t nin, row0, tile0, group0, ext0, ext_end;
+  // destination
+  int64_t *goff, *xoff;
+  int32_t *gcnt, *xcol, *in_ptr, *in_pos;
+  uint16_t* col;
+  uint8_t* row;
+  double* val64_d;
+  float* val32_d;
+};
+
+__global__ void __launch_bounds__(kBlock) k_b_copy_pairs(PairCopy A) {
+  const int64_t t = blockIdx.x;
+  const int64_t g0 = A.src.goff[t], d0 = A.group0 + g0;
+  const int ng = A.src.gcnt[t];
+  if (threadIdx.x == 0) {
+    A.goff[A.tile0 + t] = d0;
+    A.gcnt[A.tile0 + t] = ng;
+    A.xoff[A.tile0 + t] = A.ext0 + A.src.xoff[t];
+    if (t == (int64_t)gridDim.x - 1) A.xoff[A.tile0 + t + 1] = A.ext_end;
+  }
+  // a tile's two FP64 planes are one run of 4 ng values
+  const rt_f64x2_t* v = reinterpret_cast<const rt_f64x2_t*>(A.val64 + 4 * g0);
+  rt_f64x2_t* vd = reinterpret_cast<rt_f64x2_t*>(A.val64_d + 4 * d0);
+  for (int k = threadIdx.x; k < 2 * ng; k += kBlock) vd[k] = v[k];
+  const rt_u16x4* c = reinterpret_cast<const rt_u16x4*>(A.src.col + 4 * g0);
+  rt_u16x4* cd = reinterpret_cast<rt_u16x4*>(A.col + 4 * d0);
+  const rt_f32x4* w = reinterpret_cast<const rt_f32x4*>(A.val32 ? A.val32 + 4 * g0 : nullptr);
+  rt_f32x4* wd = reinterpret_cast<rt_f32x4*>(A.val32 ? A.val32_d + 4 * d0 : nullptr);
+  for (int k = threadIdx.x; k < ng; k += kBlock) {
+    cd[k] = c[k];
+    A.row[d0 + k] = A.src.row[g0 + k];
+    if (w) wd[k] = w[k];
+  }
+  const int64_t x0 = A.src.xoff[t], x1 = A.src.xoff[t + 1];
+  for (int64_t k = x0 + threadIdx.x; k < x1; k += kBlock)
+    A.xcol[A.ext0 + k] = (int32_t)(A.row0 + A.src.xcol[k]);
+  const int64_t i = t * kTileRows + threadIdx.x;
+  const int64_t r0 = t * kTileRows, r1 = r0 + kTileRows < A.nin ? r0 + kTileRows : A.nin;
+  A.in_ptr[A.row0 + i] = (int32_t)(i < A.nin ? A.ext0 + A.in.ptr[i] : A.ext_end);
+  if (i == r0 + kTileRows - 1 && t == (int64_t)gridDim.x - 1)
+    A.in_ptr[A.row0 + i + 1] = (int32_t)A.ext_end;
+  for (int64_t k = A.in.ptr[r0] + threadIdx.x; k < A.in.ptr[r1]; k += kBlock)
+    A.in_pos[A.ext0 + k] = (int32_t)(A.ext0 + A.in.pos[k]);
 }
 
 __global__ void k_b_copy_cols(int64_t nnz, const int32_t* __restrict__ col, int64_t nnz0,
@@ -311,9 +364,11 @@ k_b_init_jacobi(int64_t n, const int32_t* __restrict__ tprob, const int32_t* __r
   if (threadIdx.x == 0) part[blockIdx.x] = acc;
 }
 
-template <typename T>
+// PAIR: q holds each tile's own part of A p, completed here (pair_in)
+template <typename T, bool PAIR>
 __global__ void __launch_bounds__(kBlock)
-k_b_update(int64_t n, int nprob, const int32_t* __restrict__ tprob,
+k_b_update(int64_t n, int nprob, PairIn P, const T* __restrict__ qsum,
+           const int32_t* __restrict__ tprob,
            const int32_t* __restrict__ done, const double* __restrict__ ps, T* __restrict__ x,
            T* __restrict__ r, const T* __restrict__ p, const T* __restrict__ q,
            const T* __restrict__ dinv, double* __restrict__ partA, double* __restrict__ partB) {
@@ -325,7 +380,9 @@ k_b_update(int64_t n, int nprob, const int32_t* __restrict__ tprob,
   double rr = 0.0, rz = 0.0;
   if (i < n) {
     x[i] += alpha * p[i];
-    const T ri = r[i] - alpha * q[i];
+    T qi = q[i];
+    if (PAIR) qi += pair_in<T>(P, i, qsum);
+    const T ri = r[i] - alpha * qi;
     r[i] = ri;
     rr = (double)ri * (double)ri;
     if (dinv) rz = (double)ri * (double)(dinv[i] * ri);
@@ -540,18 +597,27 @@ int b_iteration(rt_ctx* ctx, hipStream_t st, rt_batch* B, T* x, T* r, bool amg =
   const Level& L = B->L;
   const int32_t* done = B->flags.p + F_INNER * B->nprob;
   const int shape = S::shape(L);
-  const int rpb = spmv_rows_per_block(L, shape);
-  RT_CHECK((launch_spmv_level<T, SP_DOT>(st, L, S::val(L), S::diag(L), S::p(B), nullptr, nullptr,
-                                         S::q(B), nullptr, B->partA.p, nullptr, shape,
-                                         B->tprob.p, done)));
+  const bool pair = pair_serves(L, shape);
+  const int rpb = pair ? kTileRows : spmv_rows_per_block(L, shape);
+  if (pair)
+    RT_CHECK((launch_pair<T, PP_DOT>(st, L, S::diag(L), S::p(B), S::q(B), B->partA.p, nullptr,
+                                     shape, B->tprob.p, done)));
+  else
+    RT_CHECK((launch_spmv_level<T, SP_DOT>(st, L, S::val(L), S::diag(L), S::p(B), nullptr, nullptr,
+                                           S::q(B), nullptr, B->partA.p, nullptr, shape,
+                                           B->tprob.p, done)));
   hipLaunchKernelGGL(k_b_seg, dim3(B->nprob), dim3(kBlock), 0, st, (int)BOP_ALPHA, B->nprob,
                      B->d_row_off.p, rpb, B->partA.p, (const double*)nullptr, B->ps.p,
                      B->flags.p, 0.0, 0, 0.0);
   RT_LAUNCH_CHECK();
   const unsigned nt = (unsigned)B->ntiles;
-  hipLaunchKernelGGL((k_b_update<T>), dim3(nt), dim3(kBlock), 0, st, B->n, B->nprob, B->tprob.p,
-                     done, B->ps.p, x, r, S::p(B), S::q(B), amg ? nullptr : S::dinv(L),
-                     B->partA.p, B->partB.p);
+#define RT_B_UPDATE(PAIR_)                                                                        \
+  hipLaunchKernelGGL((k_b_update<T, PAIR_>), dim3(nt), dim3(kBlock), 0, st, B->n, B->nprob,        \
+                     L.pair.in(), PairSel<T>::sum(L.pair), B->tprob.p, done, B->ps.p, x, r,        \
+                     S::p(B), S::q(B), amg ? nullptr : S::dinv(L), B->partA.p, B->partB.p)
+  if (pair) RT_B_UPDATE(true);
+  else RT_B_UPDATE(false);
+#undef RT_B_UPDATE
   RT_LAUNCH_CHECK();
   if (amg) {
     RT_CHECK(b_chunk_flags(st, B));
@@ -654,15 +720,22 @@ int b_solve(rt_ctx* ctx, rt_batch* B, const rt_solve_opts* o, int graph_k, rt_so
   RT_LAUNCH_CHECK();
   RT_CHECK(b_seg(ctx, B, BOP_BB, kTileRows, B->partA.p, nullptr, o->tol * o->tol));
   const int32_t* outer_done = B->flags.p + F_OUTER * np;
-  const int rpb64 = spmv_rows_per_block(L, resid_shape(L));
+  const bool pair = pair_serves(L, resid_shape(L));
+  const int rpb64 = pair ? kTileRows : spmv_rows_per_block(L, resid_shape(L));
   std::vector<int32_t> fl;
   bool all = false;
   int refine = 0;
   for (;;) {
-    RT_CHECK((launch_spmv_level<double, SP_RESID>(st, L, L.val64.p, L.diag64.p, B->xs.p, B->bs.p,
-                                                  nullptr, B->r64.p, mixed ? B->r32.p : nullptr,
-                                                  B->partA.p, nullptr, resid_shape(L), B->tprob.p,
-                                                  refine > 0 ? outer_done : nullptr)));
+    const int32_t* skip = refine > 0 ? outer_done : nullptr;
+    if (pair) {
+      int np_ = 0;
+      RT_CHECK(pair_resid(ctx, L, B->xs.p, B->bs.p, B->r64.p, mixed ? B->r32.p : nullptr, nullptr,
+                          B->partA.p, nullptr, &np_, resid_shape(L), B->tprob.p, skip));
+    } else {
+      RT_CHECK((launch_spmv_level<double, SP_RESID>(
+          st, L, L.val64.p, L.diag64.p, B->xs.p, B->bs.p, nullptr, B->r64.p,
+          mixed ? B->r32.p : nullptr, B->partA.p, nullptr, resid_shape(L), B->tprob.p, skip)));
+    }
     RT_CHECK(b_seg(ctx, B, BOP_OUTER, rpb64, B->partA.p, nullptr, 0.0, mixed ? 1 : 0,
                    o->inner_tol));
     RT_CHECK(b_read_flags(ctx, B, F_OUTER, &fl, &all));
@@ -944,6 +1017,17 @@ int rt_batch_create(rt_ctx* ctx, int nprob, rt_matrix* const* mats, rt_batch** o
     set_error("rt_batch_create: the ensemble exceeds the int32 index range");
     return RT_E_ARG;
   }
+  // matrices in pair form make a batch in pair form; else every matrix's CSR
+  // rows are copied (made on demand where a matrix has the pair form)
+  bool pair = true;
+  std::vector<int64_t> group_off(nprob + 1, 0), ext_off(nprob + 1, 0);
+  for (int p = 0; p < nprob; ++p) {
+    const Level& S = mats[p]->levels[0];
+    pair = pair && S.pair.on;
+    group_off[p + 1] = group_off[p] + (S.pair.on ? (mats[p]->nb->npairs >> 2) + S.n + 1 : 0);
+    ext_off[p + 1] = ext_off[p] + (S.pair.on ? S.pair.ext_total : 0);
+  }
+  pair = pair && ext_off[nprob] < INT32_MAX;
   Level& L = B->L;
   L.n = B->n;
   L.nnz = nnz_off[nprob];
@@ -959,13 +1043,30 @@ int rt_batch_create(rt_ctx* ctx, int nprob, rt_matrix* const* mats, rt_batch** o
     s = (expr);         \
     if (s < 0) return fail(s); \
   } while (0)
-  RT_B(L.rp.reserve(n + 1));
-  RT_B(L.col.reserve(std::max<int64_t>(L.nnz, 1)));
-  RT_B(L.val64.reserve(L.nnz + kSpmvPad));
+  PairForm& PF = L.pair;
+  if (pair) {
+    for (auto* b : {&PF.goff, &PF.xoff}) RT_B(b->reserve(B->ntiles + 1));
+    RT_B(PF.gcnt.reserve(B->ntiles));
+    RT_B(PF.xcol.reserve(ext_off[nprob]));
+    RT_B(PF.in_ptr.reserve(n + 1));
+    RT_B(PF.in_pos.reserve(ext_off[nprob]));
+    RT_B(PF.col.reserve((size_t)4 * group_off[nprob]));
+    RT_B(PF.row.reserve(group_off[nprob]));
+    RT_B(PF.val64.reserve((size_t)4 * group_off[nprob]));
+    RT_B(PF.sum64.reserve(ext_off[nprob]));
+    if (fp32) {
+      RT_B(PF.val32.reserve((size_t)4 * group_off[nprob]));
+      RT_B(PF.sum32.reserve(ext_off[nprob]));
+    }
+  } else {
+    RT_B(L.rp.reserve(n + 1));
+    RT_B(L.col.reserve(std::max<int64_t>(L.nnz, 1)));
+    RT_B(L.val64.reserve(L.nnz + kSpmvPad));
+    if (fp32) RT_B(L.val32.reserve(L.nnz + kSpmvPad));
+  }
   RT_B(L.diag64.reserve(n));
   RT_B(L.dinv64.reserve(n));
   if (fp32) {
-    RT_B(L.val32.reserve(L.nnz + kSpmvPad));
     RT_B(L.diag32.reserve(n));
     RT_B(L.dinv32.reserve(n));
   }
@@ -1012,7 +1113,8 @@ int rt_batch_create(rt_ctx* ctx, int nprob, rt_matrix* const* mats, rt_batch** o
   for (int p = 0; p < nprob; ++p) {
     rt_matrix* A = mats[p];
     const Level& S = A->levels[0];
-    CopyArgs ca{S.rp.p, S.diag64.p, S.dinv64.p, A->V.p, A->sa.p, A->f.p, A->rho.p, A->cv.p,
+    if (!pair) RT_B(ensure_csr(ctx, A));
+    CopyArgs ca{pair ? nullptr : S.rp.p, S.diag64.p, S.dinv64.p, A->V.p, A->sa.p, A->f.p, A->rho.p, A->cv.p,
                 A->m.p, A->e_prev.p, A->E_prev.p, A->Qe.p, A->QE.p, A->g.p,
                 fp32 ? S.diag32.p : nullptr, fp32 ? S.dinv32.p : nullptr, A->nb->perm.p,
                 A->n, B->row_off[p + 1] - B->row_off[p], B->row_off[p], nnz_off[p],
@@ -1024,7 +1126,19 @@ int rt_batch_create(rt_ctx* ctx, int nprob, rt_matrix* const* mats, rt_batch** o
       set_error("rt_batch_create: launch failed");
       return fail(RT_E_DEVICE);
     }
-    if (S.nnz > 0) {
+    if (pair) {
+      PairCopy pc{S.pair.args(), S.pair.in(), S.pair.val64.p, fp32 ? S.pair.val32.p : nullptr,
+                  S.n, B->row_off[p], B->row_off[p] / kTileRows, group_off[p], ext_off[p],
+                  ext_off[p + 1], PF.goff.p, PF.xoff.p, PF.gcnt.p, PF.xcol.p, PF.in_ptr.p,
+                  PF.in_pos.p, PF.col.p, PF.row.p, PF.val64.p, PF.val32.p};
+      hipLaunchKernelGGL(k_b_copy_pairs, dim3((unsigned)S.pair.ntiles), dim3(kBlock), 0, st, pc);
+      if (hipGetLastError() != hipSuccess) {
+        set_error("rt_batch_create: copy of problem %d failed", p);
+        return fail(RT_E_DEVICE);
+      }
+      PF.max_ext = std::max(PF.max_ext, S.pair.max_ext);
+      L.tile_cols_total += S.tile_cols_total;
+    } else if (S.nnz > 0) {
       hipLaunchKernelGGL(k_b_copy_cols, dim3(grid_for(S.nnz)), dim3(kBlock), 0, st, S.nnz,
                          S.col.p, nnz_off[p], B->row_off[p], L.col.p);
       if (hipGetLastError() != hipSuccess ||
@@ -1037,12 +1151,19 @@ int rt_batch_create(rt_ctx* ctx, int nprob, rt_matrix* const* mats, rt_batch** o
       }
     }
   }
-  hipLaunchKernelGGL(k_b_set_i64, dim3(1), dim3(1), 0, st, L.rp.p + n, L.nnz);
+  if (!pair) hipLaunchKernelGGL(k_b_set_i64, dim3(1), dim3(1), 0, st, L.rp.p + n, L.nnz);
   if (hipGetLastError() != hipSuccess || hipStreamSynchronize(st) != hipSuccess) {
     set_error("rt_batch_create: device error");
     return fail(RT_E_DEVICE);
   }
-  RT_B(build_tiles(ctx, L));
+  if (pair) {
+    PF.ntiles = B->ntiles;
+    PF.ext_total = ext_off[nprob];
+    PF.on = true;
+  } else {
+    L.csr_rows = L.csr_vals = true;
+    RT_B(build_tiles(ctx, L));
+  }
   RT_B(build_hierarchy(ctx, B));
 #undef RT_B
   *out = B;
@@ -1063,7 +1184,7 @@ int rt_batch_get_info(const rt_batch* B, int64_t* rows, int64_t* nnz, int64_t* t
   }
   if (rows) *rows = B->n;
   if (nnz) *nnz = B->L.nnz;
-  if (tile_cols) *tile_cols = B->L.tiled ? B->L.tile_cols_total : 0;
+  if (tile_cols) *tile_cols = B->L.tiled || B->L.pair.on ? B->L.tile_cols_total : 0;
   return RT_OK;
 }
 

@@ -26,6 +26,7 @@
 
 #include "internal.h"
 #include "reduce.h"
+#include "pair.h"
 #include "spmv.h"
 
 namespace rt {
@@ -170,9 +171,15 @@ struct Gmres {
   // out = U v = (A v) / V
   int apply(const double* v, double* out) {
     const Level& L = A->levels[0];
-    RT_CHECK((launch_spmv_level<double, SP_PLAIN>(ctx->stream, L, L.val64.p, L.diag64.p, v,
-                                                  nullptr, nullptr, t.p, nullptr, nullptr,
-                                                  nullptr, L.shape64)));
+    if (pair_serves(L, L.shape64)) {
+      RT_CHECK((launch_pair<double, PP_PLAIN>(ctx->stream, L, L.diag64.p, v, t.p, nullptr, nullptr,
+                                              L.shape64)));
+      RT_CHECK(pair_finish(ctx, L, t.p));
+    } else {
+      RT_CHECK((launch_spmv_level<double, SP_PLAIN>(ctx->stream, L, L.val64.p, L.diag64.p, v,
+                                                    nullptr, nullptr, t.p, nullptr, nullptr,
+                                                    nullptr, L.shape64)));
+    }
     hipLaunchKernelGGL(k_div_v, dim3(grid_for(n)), dim3(kBlock), 0, ctx->stream, n, t.p, A->V.p,
                        out);
     RT_LAUNCH_CHECK();
@@ -182,9 +189,13 @@ struct Gmres {
   int residual(const double* b, const double* x, double* out) {
     const Level& L = A->levels[0];
     int nbk = 0;
-    RT_CHECK((launch_spmv_level<double, SP_RESID>(ctx->stream, L, L.val64.p, L.diag64.p, x, b,
-                                                  nullptr, t.p, nullptr, A->partA.p, &nbk,
-                                                  L.shape64)));
+    if (pair_serves(L, L.shape64))
+      RT_CHECK(pair_resid(ctx, L, x, b, t.p, nullptr, nullptr, A->partA.p, nullptr, &nbk,
+                          L.shape64));
+    else
+      RT_CHECK((launch_spmv_level<double, SP_RESID>(ctx->stream, L, L.val64.p, L.diag64.p, x, b,
+                                                    nullptr, t.p, nullptr, A->partA.p, &nbk,
+                                                    L.shape64)));
     hipLaunchKernelGGL(k_div_v, dim3(grid_for(n)), dim3(kBlock), 0, ctx->stream, n, t.p, A->V.p,
                        out);
     RT_LAUNCH_CHECK();
@@ -210,6 +221,7 @@ int gmres_sorted(rt_ctx* ctx, rt_matrix* A, const double* b, double* x,
   Gmres G{ctx, A, A->n, o->restart, o->precond == 1 && cycle_depth(A) > 1};
   RT_CHECK(A->partA.reserve(max_partials(A->n)));
   RT_CHECK(G.init());
+  if (A->levels[0].pair.on && plain_shape(A->levels[0].shape64)) RT_CHECK(ensure_csr(ctx, A));
   const int64_t n = A->n;
   const int m = G.m;
   // ||c||

@@ -16,6 +16,7 @@
 
 #include <hip/hip_runtime.h>
 
+#include <atomic>
 #include <cstdint>
 #include <cstdio>
 #include <vector>
@@ -247,6 +248,9 @@ __device__ __forceinline__ double periodic_disp(double d, const PeriodicBox& box
 }  // namespace rt
 
 struct rt_neighbors {
+  // one reference of the caller's handle and one per matrix assembled on the
+  // lists, which reads them after the handle may have been freed
+  std::atomic<int> refs{1};
   int dim = 3;
   int kernel = RT_KERNEL_CUBIC_SPLINE;
   double kappa = 2.0;
@@ -267,6 +271,45 @@ struct rt_neighbors {
 };
 
 namespace rt {
+// Pair form of a symmetric level (see pair.h): the entries right of the
+// diagonal only, tile by tile.
+constexpr int kPairSegs = 64;     // earlier tiles that may hold columns of one tile
+constexpr int kPairBlocks = 256;  // 64-column blocks with external columns of one tile
+constexpr int kPairMaxExt = 2048; // external columns a tile may have
+// The sums one earlier tile left for rows of a tile: row 64 w + l has one if
+// bit l of mask[w] is set, at pos + off[w] + (set bits below l) of the exchange
+// buffer.
+struct PairSeg {
+  int64_t pos;
+  uint16_t off[4];
+  uint64_t mask[4];
+};
+struct PairArgs {
+  const int64_t* goff;    // per tile: its first group
+  const int32_t* gcnt;    // and number of groups
+  const int64_t* xoff;    // ntiles + 1: external columns
+  const int32_t* xcol;
+  const uint16_t* col;    // four local columns per group
+  const uint8_t* row;     // row of each group
+};
+struct PairIn {
+  const int32_t* ptr;     // n + 1: the sums left for each row,
+  const int32_t* pos;     // their places in the exchange buffer
+};
+struct PairForm {
+  bool on = false;
+  int64_t ntiles = 0, ext_total = 0;
+  int max_ext = 0;
+  DevBuf<int64_t> goff, xoff;
+  DevBuf<int32_t> gcnt, xcol, in_ptr, in_pos;
+  DevBuf<uint16_t> col;
+  DevBuf<uint8_t> row;
+  DevBuf<double> val64, sum64;   // values; exchange buffer (ext_total)
+  DevBuf<float> val32, sum32;
+  PairArgs args() const { return PairArgs{goff.p, gcnt.p, xoff.p, xcol.p, col.p, row.p}; }
+  PairIn in() const { return PairIn{in_ptr.p, in_pos.p}; }
+};
+
 // One level of the operator hierarchy.  Level 0 is the assembled fine system;
 // level l+1 has one node per aggregate of level-l nodes: pmap maps a node to
 // its aggregate (-1: left out of the coarse space), and the members of
@@ -287,6 +330,12 @@ struct Level {
   DevBuf<int32_t> col;
   DevBuf<double> val64, diag64, sinv64, dinv64;   // sinv = l1-Jacobi smoother, dinv = 1/diag
   DevBuf<float> val32, diag32, sinv32, dinv32;
+  // pair form (fine level of a matrix without a hierarchy): products run on
+  // it, and the CSR above is made from the neighbour lists when something asks
+  // for it (csr_rows: rp and col hold this structure, csr_vals: the values are
+  // those of the last assembly)
+  PairForm pair;
+  bool csr_rows = false, csr_vals = false;
   DevBuf<uint64_t> code;        // Morton code of each node's cell block (candidate blocks)
   DevBuf<int32_t> pmap;         // node -> aggregate on the next level (-1: none)
   DevBuf<int64_t> crange;       // next-level aggregate -> offset of its members (n_next + 1)
@@ -318,8 +367,18 @@ inline int level_shape(const Level& L) {
 inline int resid_shape(const Level& L) { return L.shape_res >= 0 ? L.shape_res : L.shape64; }
 }  // namespace rt
 
+namespace rt {
+inline void release_neighbors(const rt_neighbors* nb) {
+  auto* p = const_cast<rt_neighbors*>(nb);
+  if (p && p->refs.fetch_sub(1) == 1) delete p;
+}
+}  // namespace rt
+
 struct rt_matrix {
-  const rt_neighbors* nb = nullptr;
+  rt_matrix() = default;
+  rt_matrix(const rt_matrix&) = delete;
+  ~rt_matrix() { rt::release_neighbors(nb); }
+  const rt_neighbors* nb = nullptr;   // holds a reference
   int64_t n = 0;          // interior unknowns
   int64_t n_total = 0;
   double dt = 0, c = 1, a = 1;
@@ -365,6 +424,20 @@ namespace rt {
 // tiled SpMV form of a level whose rp/col are final (tile.hip); leaves the
 // level untiled when a tile has more than kTileMaxCols distinct columns
 int build_tiles(rt_ctx* ctx, Level& L);
+// pair form of a level from the interior neighbour lists (pair.hip): the
+// structure (*L.pair.on = false when a tile does not fit it), then per
+// assembly the values, diagonal and ghost couplings
+int build_pairs(rt_ctx* ctx, const rt_neighbors* nb, Level& L);
+int assemble_pairs(rt_ctx* ctx, rt_matrix* A);
+// y += the sums the last FP64 pair product left for its rows
+int pair_finish(rt_ctx* ctx, const Level& L, double* y);
+// r = b - A x from the pair form (FP64), with the outputs of the CSR residual
+// product: r32 and w32 may be NULL, part and pmax receive *nparts values
+int pair_resid(rt_ctx* ctx, const Level& L, const double* x, const double* b, double* r,
+               float* r32, float* w32, double* part, double* pmax, int* nparts, int shape,
+               const int32_t* tprob = nullptr, const int32_t* skip = nullptr);
+// the CSR form of a level in pair form, made on demand (assemble.hip)
+int ensure_csr(rt_ctx* ctx, rt_matrix* A);
 
 // neighbours
 int build_neighbors(rt_ctx* ctx, int dim, int64_t n_total, int64_t n_interior,

@@ -955,7 +955,7 @@ int rt_neighbors_export(rt_ctx* ctx, const rt_neighbors* nb, int64_t* nbr_ptr, i
 void rt_neighbors_free(rt_neighbors* nb) {
   if (!nb) return;
   rt::IdleScope idle;   // one wait for the device, then every buffer goes back to the cache
-  delete nb;
+  rt::release_neighbors(nb);
 }
 
 }  // extern "C"

@@ -33,6 +33,7 @@
 #include <cstring>
 
 #include "internal.h"
+#include "pair.h"
 #include "reduce.h"
 #include "spmv.h"
 
@@ -237,9 +238,10 @@ k_dot(int64_t n, const T* __restrict__ a, const T* __restrict__ b, double* __res
 // x += alpha p; r -= alpha q; partA = r.r; (Jacobi) partB = r.(dinv r);
 // CW != CW_NONE: partC = the block maximum of the componentwise measure, with
 // w = dinv (CW_X: |r_i| w_i / |x_i| of the updated x) or fixed weights (CW_W)
-template <typename T, bool JAC, int CW>
+// PAIR: q holds each tile's own part of A p, completed here (pair_in)
+template <typename T, bool JAC, int CW, bool PAIR>
 __global__ void __launch_bounds__(kBlock)
-k_update(int64_t n, const double* __restrict__ s, T* __restrict__ x, T* __restrict__ r,
+k_update(int64_t n, PairIn P, const T* __restrict__ qsum, const double* __restrict__ s, T* __restrict__ x, T* __restrict__ r,
          const T* __restrict__ p, const T* __restrict__ q, const T* __restrict__ dinv,
          const T* __restrict__ w, double* __restrict__ partA, double* __restrict__ partB,
          double* __restrict__ partC, const int32_t* __restrict__ stop) {
@@ -250,7 +252,9 @@ k_update(int64_t n, const double* __restrict__ s, T* __restrict__ x, T* __restri
   RT_VEC_LOOP(i) {
     const T xi = x[i] + alpha * p[i];
     x[i] = xi;
-    const T ri = r[i] - alpha * q[i];
+    T qi = q[i];
+    if (PAIR) qi += pair_in<T>(P, i, qsum);
+    const T ri = r[i] - alpha * qi;
     r[i] = ri;
     rr += (double)ri * (double)ri;
     if (JAC) rz += (double)ri * (double)(dinv[i] * ri);
@@ -445,17 +449,27 @@ int pcg_iteration(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r
   int nbk = 0;
   Prof pf(ctx, S::kind);
   RT_CHECK(pf.begin());
-  RT_CHECK((launch_spmv_level<T, SP_DOT>(st, L, S::val(L), S::diag(L), p, nullptr, nullptr, q,
-                                         nullptr, W.partA, &nbk, level_shape<T>(L), nullptr,
-                                         stop)));
+  const bool pair = pair_serves(L, level_shape<T>(L));
+  if (pair)
+    RT_CHECK((launch_pair<T, PP_DOT>(st, L, S::diag(L), p, q, W.partA, &nbk, level_shape<T>(L),
+                                     nullptr, stop)));
+  else
+    RT_CHECK((launch_spmv_level<T, SP_DOT>(st, L, S::val(L), S::diag(L), p, nullptr, nullptr, q,
+                                           nullptr, W.partA, &nbk, level_shape<T>(L), nullptr,
+                                           stop)));
   RT_CHECK(pf.end());
   RT_CHECK(finalize(ctx, W, FIN_ALPHA, nbk, W.partA, nullptr));
   const T* w = static_cast<const T*>(cw.w);
   double* pc = cw.mode == CW_NONE ? nullptr : W.partC;
-#define RT_UPD(JAC_, CW_)                                                                      \
-  hipLaunchKernelGGL((k_update<T, JAC_, CW_>), dim3(gv), dim3(kBlock), 0, st, n, W.scal, x, r, \
-                     p, q, JAC_ ? S::dinv(L) : nullptr, w, W.partA,                          \
-                     JAC_ ? W.partB : nullptr, pc, stop)
+#define RT_UPD1(JAC_, CW_, PAIR_)                                                               \
+  hipLaunchKernelGGL((k_update<T, JAC_, CW_, PAIR_>), dim3(gv), dim3(kBlock), 0, st, n,          \
+                     L.pair.in(), PairSel<T>::sum(L.pair), W.scal, x, r, p, q,                   \
+                     JAC_ ? S::dinv(L) : nullptr, w, W.partA, JAC_ ? W.partB : nullptr, pc, stop)
+#define RT_UPD(JAC_, CW_)                   \
+  do {                                      \
+    if (pair) RT_UPD1(JAC_, CW_, true);     \
+    else RT_UPD1(JAC_, CW_, false);         \
+  } while (0)
   if (amg) {
     if (cw.mode == CW_X) RT_UPD(false, CW_X);
     else if (cw.mode == CW_W) RT_UPD(false, CW_W);
@@ -469,6 +483,7 @@ int pcg_iteration(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r
     else RT_UPD(true, CW_NONE);
   }
 #undef RT_UPD
+#undef RT_UPD1
   RT_LAUNCH_CHECK();
   RT_CHECK(finalize(ctx, W, FIN_BETA, gv, W.partA, W.partB, thr2, pc, cw.thr));
   if (amg)
@@ -588,6 +603,14 @@ int ensure_work(rt_matrix* A, bool mixed) {
   return RT_OK;
 }
 
+// The CSR rows of a level in pair form, when a plain shape asks for them.
+int ensure_shapes(rt_ctx* ctx, rt_matrix* A, bool mixed) {
+  const Level& L = A->levels[0];
+  if (!L.pair.on || !(plain_shape(resid_shape(L)) || plain_shape(mixed ? L.shape32 : L.shape64)))
+    return RT_OK;
+  return ensure_csr(ctx, A);
+}
+
 // The matrix's own work buffers (after ensure_work)
 Work work_of(rt_matrix* A) {
   Work W;
@@ -618,9 +641,12 @@ int residual64(rt_ctx* ctx, rt_matrix* A, const Work& W, const double* b, const 
   int nbk = 0;
   Prof pf(ctx, PROF_RESID64);
   RT_CHECK(pf.begin());
-  RT_CHECK((launch_spmv_level<double, SP_RESID>(ctx->stream, L, L.val64.p, L.diag64.p, x, b,
-                                                nullptr, W.r64, r32, W.partA, &nbk,
-                                                resid_shape(L), nullptr, nullptr, W.partC, w32)));
+  if (pair_serves(L, resid_shape(L)))
+    RT_CHECK(pair_resid(ctx, L, x, b, W.r64, r32, w32, W.partA, W.partC, &nbk, resid_shape(L)));
+  else
+    RT_CHECK((launch_spmv_level<double, SP_RESID>(ctx->stream, L, L.val64.p, L.diag64.p, x, b,
+                                                  nullptr, W.r64, r32, W.partA, &nbk,
+                                                  resid_shape(L), nullptr, nullptr, W.partC, w32)));
   RT_CHECK(pf.end());
   RT_CHECK(finalize(ctx, W, FIN_RR, nbk, W.partA, nullptr, 0.0, W.partC));
   RT_CHECK(ctx->sync_read(W.scal, sizeof(double) * S_COUNT));
@@ -765,6 +791,7 @@ int residual_norms(rt_ctx* ctx, rt_matrix* A, const double* b, const double* x, 
   A->resid_ok = false;
   A->r64_valid = false;
   RT_CHECK(ensure_work(A, false));
+  RT_CHECK(ensure_shapes(ctx, A, true));
   const Work W = work_of(A);
   double cw = 0.0;
   RT_CHECK(residual64(ctx, A, W, b, x, nullptr, nullptr, rr, &cw));
@@ -785,6 +812,7 @@ int solve_sorted(rt_ctx* ctx, rt_matrix* A, const double* b, double* x, const rt
     return RT_E_STATE;
   }
   RT_CHECK(ensure_work(A, mixed));
+  RT_CHECK(ensure_shapes(ctx, A, mixed));
   bool valid = false;
   int rec = A->rec_steps;
   const int s = solve_work(ctx, A, work_of(A), b, x, o, stt, b_prev, mismatch, &valid, &rec);

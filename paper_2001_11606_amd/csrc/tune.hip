@@ -8,6 +8,7 @@
 #include <cstring>
 
 #include "internal.h"
+#include "pair.h"
 #include "spmv.h"
 
 namespace rt {
@@ -21,7 +22,14 @@ template <typename T, int MODE>
 int time_shape(rt_ctx* ctx, const Level& L, const T* val, const T* diag, T* y, float* y32,
                double* part, double* pmax, int shape, int reps, double* us) {
   hipStream_t st = ctx->stream;
-  auto launch = [&]() {
+  auto launch = [&]() -> int {
+    if (pair_serves(L, shape)) {   // a level in pair form: its product of this shape
+      int np = 0;
+      if constexpr (MODE == SP_RESID)
+        return pair_resid(ctx, L, diag, diag, y, y32, nullptr, part, pmax, &np, shape);
+      else
+        return launch_pair<T, PP_DOT>(st, L, diag, diag, y, part, &np, shape);
+    }
     return launch_spmv_level<T, MODE>(st, L, val, diag, diag, diag, nullptr, y, y32, part, nullptr,
                                       shape, nullptr, nullptr, pmax, nullptr);
   };
@@ -93,13 +101,16 @@ int rt_matrix_tune(rt_ctx* ctx, rt_matrix* A, int reps, rt_tune_report* rep) {
     Level& L = A->levels[l];
     r->chosen[l][0] = r->chosen[l][1] = r->chosen[l][2] = -1;
     if (L.n == 0) continue;
+    // the plain shapes' rows (a batch in pair form has none: the pair form serves
+    // every shape)
+    if (L.pair.on && A->nb) RT_CHECK(ensure_csr(ctx, A));
     for (int p = 0; p < 3; ++p) {
       if (p == 1 && !A->has_fp32) continue;
       if (p == 2 && (l > 0 || !A->has_fp32)) continue;   // refinement residuals: fine level
       double best = 0.0;
       int arg = -1;
       for (int s = 0; s < r->shapes; ++s) {
-        if (kSpmvShapes[s].tiled && !L.tiled) continue;
+        if (kSpmvShapes[s].tiled && !L.tiled && !L.pair.on) continue;
         double us = 0.0;
         if (p == 0)
           RT_CHECK((time_shape<double, SP_DOT>(ctx, L, L.val64.p, L.diag64.p, y.p, nullptr, part.p,
