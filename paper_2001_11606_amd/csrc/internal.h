@@ -173,6 +173,7 @@ constexpr int kBlock = 256;            // threads per block (4 wavefronts)
 constexpr int kMaxPartials = 2048;     // cap on blocks of reduction kernels
 constexpr int kTileRows = kBlock;      // rows per tile of the tiled SpMV format
 constexpr int kTileMaxCols = 3072;     // distinct columns a tile may have
+constexpr int kScalars = 48;           // device scalars of a solve and a Newton step
 constexpr int kSpmvPad = 8;            // spare entries after values / lcol
 
 // Dynamic LDS of a kernel (bytes set at launch).
@@ -403,6 +404,7 @@ struct rt_matrix {
   rt::DevBuf<float> r32, p32, q32, z32, d32;
   rt::DevBuf<double> partA, partB;   // block partials of the reductions
   rt::DevBuf<double> partC;          // block maxima of the componentwise residual measure
+  rt::DevBuf<double> partD;          // block partials of the PCG loop's products
   rt::DevBuf<double> partF;          // second level of the partial reductions
   rt::DevBuf<float> w32;             // weights 1/(a_ii |x_i|) of the FP32 inner solve
   rt::DevBuf<double> scal;           // device scalars (see solve.hip)

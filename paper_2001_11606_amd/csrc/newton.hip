@@ -26,7 +26,7 @@ __global__ void k_rhs(int64_t n, double dt, double c, double a, const double* __
                       const double* __restrict__ cv, const double* __restrict__ E_prev,
                       const double* __restrict__ QE, const double* __restrict__ g,
                       const double* __restrict__ e_l, const double* __restrict__ E_l,
-                      double* __restrict__ b, const double* __restrict__ x_last,
+                      double* __restrict__ b, double* __restrict__ x, int carry,
                       int32_t* __restrict__ mismatch) {
   int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i >= n) return;
@@ -36,8 +36,9 @@ __global__ void k_rhs(int64_t n, double dt, double c, double a, const double* __
   const double El = E_l[i];
   const double P = E_prev[i] / dt + ca * (a * (T2 * T2)) - (1.0 - f[i]) * ca * El + QE[i];
   b[i] = V[i] * P + g[i];
-  // the carried residual is valid only if E^l is the last solution, bit for bit
-  if (x_last && El != x_last[i]) atomicAdd(mismatch, 1);
+  // the carried residual is valid only if E^l is the last solution (x), bit for bit
+  if (carry && El != x[i]) atomicAdd(mismatch, 1);
+  if (x) x[i] = El;   // the solve's starting guess
 }
 
 // Block maxima of the material residual of the backward-Euler system,
@@ -80,7 +81,7 @@ enum { R_DE = 0, R_DEE, R_ITS, R_BAD, R_NONPHYS, R_EN, R_EN0, R_WIDTH };
 struct MatArgs {
   const double *e_prev, *rho, *cv, *sa, *Qe, *m, *V, *E_prev;
   const double *E_new, *E_old, *e_start;
-  double* e_out;
+  double *e_out, *E_out;   // may be e_start and E_old; E_out NULL: not written
   double dt, c, a, tol;
   int max_iter;
 };
@@ -91,16 +92,17 @@ __global__ void __launch_bounds__(kBlock) k_material(int64_t n, MatArgs A, doubl
   for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
        i += (int64_t)gridDim.x * blockDim.x) {
     const double ep = A.e_prev[i];
-    const double Enew = A.E_new[i];
-    const MaterialResult mr = material_solve(A.rho[i], A.cv[i], A.sa[i], ep, A.Qe[i], Enew,
-                                             A.e_start[i], A.dt, A.c, A.a, A.tol, A.max_iter);
+    const double Enew = A.E_new[i], Eold = A.E_old[i], es = A.e_start[i];
+    const MaterialResult mr = material_solve(A.rho[i], A.cv[i], A.sa[i], ep, A.Qe[i], Enew, es,
+                                             A.dt, A.c, A.a, A.tol, A.max_iter);
     const double e = mr.e;
     const int it = mr.iterations;
     if (mr.nonphysical) nonphys += 1.0;
     if (!mr.converged) bad += 1.0;
     A.e_out[i] = e;
-    de = fmax(de, fabs(e - A.e_start[i]) / fabs(e));
-    dE = fmax(dE, fabs(Enew - A.E_old[i]) / fabs(Enew));
+    if (A.E_out) A.E_out[i] = Enew;
+    de = fmax(de, fabs(e - es) / fabs(e));
+    dE = fmax(dE, fabs(Enew - Eold) / fabs(Enew));
     its_max = fmax(its_max, (double)it);
     en += A.m[i] * e + A.V[i] * Enew;
     en0 += A.m[i] * ep + A.V[i] * A.E_prev[i];
@@ -125,37 +127,41 @@ __global__ void __launch_bounds__(kBlock) k_material(int64_t n, MatArgs A, doubl
 }
 
 // column-wise combination of the block partials (max for the first three
-// columns, sum for the rest), one block, fixed order
-__global__ void __launch_bounds__(kBlock) k_material_final(int np, const double* __restrict__ part,
-                                                           double* __restrict__ out) {
-  __shared__ double red[kBlock / kWave];
-  for (int c = 0; c < R_WIDTH; ++c) {
-    const bool is_max = c <= R_ITS;
-    double v = 0.0;
-    for (int i = threadIdx.x; i < np; i += blockDim.x) {
-      const double x = part[(int64_t)i * R_WIDTH + c];
-      v = is_max ? fmax(v, x) : v + x;
-    }
-    v = is_max ? block_max(v, red) : block_sum(v, red);
-    if (threadIdx.x == 0) out[c] = v;
+// columns, sum for the rest), one wave per column, fixed order
+constexpr int kMatFinal = 8 * kWave;
+static_assert(R_WIDTH <= kMatFinal / kWave, "one wave per column");
+__global__ void __launch_bounds__(kMatFinal)
+k_material_final(int np, const double* __restrict__ part, double* __restrict__ out) {
+  const int c = threadIdx.x / kWave, lane = threadIdx.x & (kWave - 1);
+  if (c >= R_WIDTH) return;
+  const bool is_max = c <= R_ITS;
+  double v = 0.0;
+#pragma unroll 4
+  for (int i = lane; i < np; i += kWave) {
+    const double x = part[(int64_t)i * R_WIDTH + c];
+    v = is_max ? fmax(v, x) : v + x;
   }
+  v = is_max ? group_max<kWave>(v) : group_sum<kWave>(v);
+  if (lane == 0) out[c] = v;
 }
 
+// results of the two material solves of a step, behind the solver's scalars
+constexpr int kMatFirst = 32, kMatLast = 40;
+static_assert(kMatLast + R_WIDTH <= kScalars, "room for both results");
+
+// queue the material solves of all particles; the results go to scal[at ...)
 int material(rt_ctx* ctx, rt_matrix* A, const double* E_new, const double* E_old,
-             const double* e_start, double* e_out, double tol, int max_iter, double* res) {
+             const double* e_start, double* e_out, double* E_out, double tol, int max_iter, int at) {
   const int64_t n = A->n;
   const int gv = grid_for(n, kBlock, kMaxPartials);
   RT_CHECK(A->partA.reserve(std::max<int64_t>((int64_t)kMaxPartials * R_WIDTH, max_partials(n))));
-  RT_CHECK(A->scal.reserve(16));
   MatArgs ma{A->e_prev.p, A->rho.p, A->cv.p, A->sa.p, A->Qe.p, A->m.p, A->V.p, A->E_prev.p,
-             E_new, E_old, e_start, e_out, A->dt, A->c, A->a, tol, max_iter};
+             E_new, E_old, e_start, e_out, E_out, A->dt, A->c, A->a, tol, max_iter};
   hipLaunchKernelGGL(k_material, dim3(gv), dim3(kBlock), 0, ctx->stream, n, ma, A->partA.p);
   RT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_material_final, dim3(1), dim3(kBlock), 0, ctx->stream, gv, A->partA.p,
-                     A->scal.p + 8);
+  hipLaunchKernelGGL(k_material_final, dim3(1), dim3(kMatFinal), 0, ctx->stream, gv, A->partA.p,
+                     A->scal.p + at);
   RT_LAUNCH_CHECK();
-  RT_CHECK(ctx->sync_read(A->scal.p + 8, sizeof(double) * R_WIDTH));
-  for (int c = 0; c < R_WIDTH; ++c) res[c] = ctx->host[c];
   return RT_OK;
 }
 
@@ -282,15 +288,12 @@ extern "C" int rt_newton_step(rt_ctx* ctx, rt_matrix* A, double* e, double* E, i
     RT_CHECK(gather_sorted(ctx, A->nb, n, e, ecur));
     RT_CHECK(gather_sorted(ctx, A->nb, n, E, Ecur));
   }
-  double res[8];
-  int status = RT_OK;
-  if (ell == 0) {
-    // initial material solve with E^{n,0} from e^{n-1} (Algorithm 1, before the loop)
-    RT_CHECK(material(ctx, A, Ecur, Ecur, A->e_prev.p, ecur, opts->material_tol,
-                      opts->material_max_iter, res));
-    if (res[3] > 0) status = RT_NOT_CONVERGED;
-    if (res[4] > 0) status = RT_NONPHYSICAL;
-  }
+  RT_CHECK(A->scal.reserve(kScalars));
+  if (ell == 0)
+    // initial material solve with E^{n,0} from e^{n-1} (Algorithm 1, before the
+    // loop); its results are read with the last one's
+    RT_CHECK(material(ctx, A, Ecur, Ecur, A->e_prev.p, ecur, nullptr, opts->material_tol,
+                      opts->material_max_iter, kMatFirst));
   // Outer iterations after the first start from the last solution with the
   // same matrix, so the last solve's residual b^l - A E^{l+1} turns into the
   // new initial residual by adding b^{l+1} - b^l: no product needed.
@@ -304,34 +307,36 @@ extern "C" int rt_newton_step(rt_ctx* ctx, rt_matrix* A, double* e, double* E, i
   }
   hipLaunchKernelGGL(k_rhs, dim3(grid_for(n)), dim3(kBlock), 0, st, n, A->dt, A->c, A->a, A->V.p,
                      A->sa.p, A->f.p, A->cv.p, A->E_prev.p, A->QE.p, A->g.p, ecur, Ecur,
-                     A->bs.p, carry ? A->xs.p : nullptr, carry ? A->xmis.p : nullptr);
+                     A->bs.p, A->xs.p, carry ? 1 : 0, carry ? A->xmis.p : nullptr);
   RT_LAUNCH_CHECK();
-  RT_CHECK_HIP(hipMemcpyAsync(A->xs.p, Ecur, sizeof(double) * n, hipMemcpyDeviceToDevice, st));
   RT_CHECK_HIP(hipEventRecord(ctx->ev0, st));
   int s = solve_sorted(ctx, A, A->bs.p, A->xs.p, &opts->solve, &stt->solve,
                        carry ? A->bs_prev.p : nullptr, carry ? A->xmis.p : nullptr);
   if (s < 0) return s;
   const bool resid_after = A->r64_valid;
   RT_CHECK_HIP(hipEventRecord(ctx->ev1, st));
-  if (s == RT_NOT_CONVERGED) status = RT_NOT_CONVERGED;
-  RT_CHECK(material(ctx, A, A->xs.p, Ecur, ecur, A->enew.p, opts->material_tol,
-                    opts->material_max_iter, res));
-  stt->delta_e = res[0];
-  stt->delta_E = res[1];
-  stt->material_iterations = (int)res[2];
-  stt->nonphysical = (int64_t)res[4];
-  stt->energy = res[5];
-  stt->energy_prev = res[6];
-  if (res[3] > 0 && status == RT_OK) status = RT_NOT_CONVERGED;
-  if (res[4] > 0) status = RT_NONPHYSICAL;
-  if (in_sorted) {
-    RT_CHECK_HIP(hipMemcpyAsync(e, A->enew.p, sizeof(double) * n, hipMemcpyDeviceToDevice, st));
-    RT_CHECK_HIP(hipMemcpyAsync(E, A->xs.p, sizeof(double) * n, hipMemcpyDeviceToDevice, st));
-  } else {
+  // into the caller's arrays, in sorted order directly
+  RT_CHECK(material(ctx, A, A->xs.p, Ecur, ecur, in_sorted ? e : A->enew.p, in_sorted ? E : nullptr,
+                    opts->material_tol, opts->material_max_iter, kMatLast));
+  if (!in_sorted) {
     RT_CHECK(scatter_user(ctx, A->nb, n, A->enew.p, e));
     RT_CHECK(scatter_user(ctx, A->nb, n, A->xs.p, E));
   }
-  RT_CHECK_HIP(hipStreamSynchronize(st));
+  RT_CHECK(ctx->sync_read(A->scal.p + kMatFirst, sizeof(double) * (kMatLast - kMatFirst + R_WIDTH)));
+  const double* init = ctx->host;
+  const double* res = ctx->host + (kMatLast - kMatFirst);
+  int status = RT_OK;
+  if (ell == 0 && init[R_BAD] > 0) status = RT_NOT_CONVERGED;
+  if (ell == 0 && init[R_NONPHYS] > 0) status = RT_NONPHYSICAL;
+  if (s == RT_NOT_CONVERGED) status = RT_NOT_CONVERGED;
+  stt->delta_e = res[R_DE];
+  stt->delta_E = res[R_DEE];
+  stt->material_iterations = (int)res[R_ITS];
+  stt->nonphysical = (int64_t)res[R_NONPHYS];
+  stt->energy = res[R_EN];
+  stt->energy_prev = res[R_EN0];
+  if (res[R_BAD] > 0 && status == RT_OK) status = RT_NOT_CONVERGED;
+  if (res[R_NONPHYS] > 0) status = RT_NONPHYSICAL;
   float solve_ms = 0.f;
   RT_CHECK_HIP(hipEventElapsedTime(&solve_ms, ctx->ev0, ctx->ev1));
   stt->solve.seconds = 1e-3 * solve_ms;
@@ -375,7 +380,7 @@ extern "C" int rt_newton_residual(rt_ctx* ctx, rt_matrix* A, const double* e, co
   // A E - b = V r (the f terms cancel)
   hipLaunchKernelGGL(k_rhs, dim3(grid_for(n)), dim3(kBlock), 0, st, n, A->dt, A->c, A->a, A->V.p,
                      A->sa.p, A->f.p, A->cv.p, A->E_prev.p, A->QE.p, A->g.p, es, Es, A->bs.p,
-                     nullptr, nullptr);
+                     nullptr, 0, nullptr);
   RT_LAUNCH_CHECK();
   double rr = 0.0, bb = 0.0;
   RT_CHECK(residual_norms(ctx, A, A->bs.p, Es, &rr, &bb));

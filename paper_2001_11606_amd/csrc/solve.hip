@@ -18,15 +18,21 @@
 // under ||r|| <= 1e-14 ||b||.  The FP32 inner solve then measures its
 // residual with the weights 1/(a_ii |x_i|) of the refinement's start.
 //
-// Scalars (alpha, beta, r.z, ...) stay on the device; block partials of the
-// dot products are combined in FP64 by a one-block kernel in a fixed order.
-// The stopping test runs on the device too: the kernel that forms ||r||^2
-// sets a stop flag once it meets the threshold (or on breakdown), and every
-// kernel of the iteration does nothing once the flag is set.  The host queues
+// Scalars (alpha, beta, r.z, ...) and thresholds stay on the device; block
+// partials of the dot products are combined in FP64 in a fixed order.  Up to
+// kFusedPartials of them, every block of the kernel that needs a scalar
+// combines them itself (all get the same bits, block 0 keeps the record);
+// beyond that a one-block kernel does.  An iteration is then three launches
+// instead of five: below 1M rows the one-block kernels took 5.5 us each, as
+// long as a vector pass.
+// The stopping test runs on the device too: the residual's first reduction
+// (k_start) sets the thresholds and a stop flag, the kernel that forms ||r||^2
+// sets the flag once the threshold is met (or on breakdown), and every kernel
+// of the iteration does nothing once it is set.  The host queues the start and
 // several iterations between reads of the state -- as many as the observed
 // convergence rate says are still needed, scaled down so that it rarely
-// queues past the end -- so an iteration costs no host round trip, and the
-// arithmetic is the same as stopping after each iteration.
+// queues past the end -- so neither a start nor an iteration costs a host
+// round trip, and the arithmetic is the same as stopping after each iteration.
 #include <algorithm>
 #include <chrono>
 #include <cmath>
@@ -40,32 +46,31 @@
 namespace rt {
 namespace {
 
-enum { S_RZ = 0, S_PQ, S_ALPHA, S_BETA, S_RR, S_RR0, S_BB, S_BAD, S_ITS, S_STOP, S_CW, S_RZ_PREV,
-       S_COUNT };
+// device scalars; S_RZ holds r.z in two places that the iterations alternate
+// between (a kernel whose blocks read one writes the other)
+enum { S_RZ = 0, S_RZ_ALT, S_PQ, S_ALPHA, S_BETA, S_RR, S_RR0, S_CW0, S_BB, S_BAD, S_ITS, S_STOP,
+       S_CW, S_RZ_PREV, S_RZ_LAST, S_THR, S_CWTHR, S_DONE, S_MIS, S_COUNT };
 // componentwise measure of the update kernel: none, |r_i| w_i / |x_i| with
 // w = 1/diag (the iterate's own measure), or |r_i| w_i with fixed weights
 enum { CW_NONE = 0, CW_X = 1, CW_W = 2 };
 enum { FIN_ALPHA = 0, FIN_BETA, FIN_RZ, FIN_RR, FIN_BB, FIN_RESUME };
 enum { PROF_SPMV64 = 0, PROF_SPMV32 = 1, PROF_RESID64 = 2, PROF_KINDS = 3 };
 
-// One block: combine the partials and update the scalars.  In the loop
-// (FIN_ALPHA, FIN_BETA) nothing happens once *stop is set; FIN_BETA counts the
-// iteration and sets *stop when ||r||^2 <= thr2 (or is not a number);
-// FIN_ALPHA sets it on breakdown (p.Ap not positive).  FIN_RZ starts a loop.
-__global__ void __launch_bounds__(kBlock)
-k_finalize(int op, int np, const double* __restrict__ pa, const double* __restrict__ pb,
-           const double* __restrict__ pc, double* __restrict__ s, int32_t* __restrict__ stop,
-           double thr2, double cwthr) {
-  __shared__ double red[kBlock / kWave];
-  if ((op == FIN_ALPHA || op == FIN_BETA) && *stop) return;
-  // pc (else NULL): block maxima of the componentwise measure
+// Sums of up to np partials in every block that calls it, and the largest of
+// pc (pb, pc: NULL, none).  Four independent running sums per thread keep
+// four loads in flight; they are combined in a fixed order.
+struct Combined {
+  double a, b, c;
+};
+__device__ __forceinline__ Combined combine(int np, const double* __restrict__ pa,
+                                            const double* __restrict__ pb,
+                                            const double* __restrict__ pc, double* red) {
+  __shared__ Combined out;
   double c = 0.0;
   if (pc) {
     for (int k = threadIdx.x; k < np; k += kBlock) c = fmax(c, pc[k]);
     c = block_max(c, red);
   }
-  // four independent running sums per thread keep four loads in flight; they
-  // are combined in a fixed order, so the result is the same on every run
   double a4[4] = {0.0, 0.0, 0.0, 0.0}, b4[4] = {0.0, 0.0, 0.0, 0.0};
   int i = threadIdx.x;
   for (; i + 3 * kBlock < np; i += 4 * kBlock) {
@@ -80,67 +85,143 @@ k_finalize(int op, int np, const double* __restrict__ pa, const double* __restri
     a4[u] += pa[i];
     if (pb) b4[u] += pb[i];
   }
-  double a = (a4[0] + a4[1]) + (a4[2] + a4[3]);
-  double b = (b4[0] + b4[1]) + (b4[2] + b4[3]);
-  a = block_sum(a, red);
-  if (pb) b = block_sum(b, red);
-  if (threadIdx.x != 0) return;
+  double a = block_sum((a4[0] + a4[1]) + (a4[2] + a4[3]), red);
+  double b = 0.0;
+  if (pb) b = block_sum((b4[0] + b4[1]) + (b4[2] + b4[3]), red);
+  if (threadIdx.x == 0) out = Combined{a, b, c};
+  __syncthreads();
+  return out;
+}
+
+// alpha = r.z / p.Ap for the iteration that reads r.z from s[S_RZ + slot];
+// returns false (and the record, by the calling block's thread 0 if keep, sets
+// the stop flag) on breakdown: p.Ap not positive
+__device__ __forceinline__ bool take_alpha(double pq, int slot, double* __restrict__ s,
+                                           int32_t* __restrict__ stop, bool keep, double* alpha) {
+  const bool ok = pq > 0.0 && isfinite(pq);
+  *alpha = ok ? s[S_RZ + slot] / pq : 0.0;
+  if (keep && threadIdx.x == 0) {
+    s[S_PQ] = pq;
+    s[S_ALPHA] = *alpha;
+    if (!ok) {
+      s[S_BAD] = 1.0;
+      s[S_STOP] = 1.0;
+      *stop = 1;
+    }
+  }
+  return ok;
+}
+
+// beta of the iteration from rr = ||r||^2, rz = r.z (new) and the componentwise
+// measure cw (tested if has_cw); returns false when the loop ends here
+__device__ __forceinline__ bool take_beta(double rr, double rz, double cw, bool has_cw, int slot,
+                                          double* __restrict__ s, int32_t* __restrict__ stop,
+                                          bool keep, double* beta) {
+  const double last = s[S_RZ + slot];
+  const bool ends = !(rr > s[S_THR]) && (!has_cw || !(cw > s[S_CWTHR]));
+  *beta = rz / last;
+  if (keep && threadIdx.x == 0) {
+    s[S_RR] = rr;
+    s[S_BETA] = *beta;
+    s[S_RZ_PREV] = last;
+    s[S_RZ_LAST] = rz;
+    s[S_RZ + (slot ^ 1)] = rz;
+    s[S_ITS] += 1.0;
+    if (has_cw) s[S_CW] = cw;
+    if (ends) {
+      s[S_STOP] = 1.0;
+      *stop = 1;
+    }
+  }
+  return !ends;
+}
+
+// One block: combine the partials and update the scalars; nothing happens
+// once *stop is set, except for the norms (FIN_RR, FIN_BB).
+__global__ void __launch_bounds__(kBlock)
+k_finalize(int op, int np, const double* __restrict__ pa, const double* __restrict__ pb,
+           const double* __restrict__ pc, double* __restrict__ s, int32_t* __restrict__ stop,
+           int slot) {
+  __shared__ double red[kBlock / kWave];
+  if (op != FIN_RR && op != FIN_BB && *stop) return;
+  const Combined v = combine(np, pa, pb, pc, red);
+  double unused;
   switch (op) {
     case FIN_ALPHA:
-      s[S_PQ] = a;
-      if (a > 0.0 && isfinite(a)) {
-        s[S_ALPHA] = s[S_RZ] / a;
-      } else {
-        s[S_ALPHA] = 0.0;
-        s[S_BAD] = 1.0;
-        s[S_STOP] = 1.0;
-        *stop = 1;
+      (void)take_alpha(v.a, slot, s, stop, true, &unused);
+      break;
+    case FIN_BETA:
+      (void)take_beta(v.a, v.b, v.c, pc != nullptr, slot, s, stop, true, &unused);
+      break;
+    default:
+      if (threadIdx.x != 0) return;
+      if (op == FIN_RZ) {   // r.z at the start
+        s[S_RZ] = v.a;
+      } else if (op == FIN_RR) {
+        s[S_RR] = v.a;
+        if (pc) s[S_CW] = v.c;
+      } else if (op == FIN_BB) {
+        s[S_BB] = v.a;
+      } else {   // FIN_RESUME: r.z of a residual that replaced the recursive one
+        // The loop that stopped kept its last search direction and, in
+        // S_RZ_PREV, the r.z it was formed with: beta continues from it, but
+        // only while the replacement agrees with the recursion (S_RZ_LAST, the
+        // recursive r.z it stopped at, within 25%).  The FP32 operator's own
+        // error can make the two differ by far more than rounding; then
+        // beta = 0, a restart (p = z).
+        s[S_BETA] = s[S_RZ_PREV] > 0.0 && isfinite(s[S_RZ_PREV]) && v.a >= 0.75 * s[S_RZ_LAST] &&
+                            v.a <= 1.25 * s[S_RZ_LAST]
+                        ? v.a / s[S_RZ_PREV]
+                        : 0.0;
+        s[S_RZ] = v.a;
       }
-      break;
-    case FIN_BETA:   // a = ||r||^2, b = r.z (new), c = componentwise measure
-      s[S_RR] = a;
-      s[S_BETA] = b / s[S_RZ];
-      s[S_RZ_PREV] = s[S_RZ];
-      s[S_RZ] = b;
-      s[S_ITS] += 1.0;
-      if (pc) s[S_CW] = c;
-      if (!(a > thr2) && (!pc || !(c > cwthr))) {
-        s[S_STOP] = 1.0;
-        *stop = 1;
-      }
-      break;
-    case FIN_RZ:     // a = r.z at the start
-      s[S_RZ] = a;
-      s[S_BAD] = 0.0;
-      s[S_ITS] = 0.0;
-      s[S_STOP] = 0.0;
-      *stop = 0;
-      break;
-    case FIN_RR:
-      s[S_RR] = a;
-      if (pc) s[S_CW] = c;
-      break;
-    case FIN_BB:
-      s[S_BB] = a;
-      break;
-    case FIN_RESUME:   // a = r.z of a residual that replaced the recursive one
-      // The loop that stopped kept its last search direction and, in
-      // S_RZ_PREV, the r.z it was formed with: beta continues from it, but
-      // only while the replacement agrees with the recursion (S_RZ, the
-      // recursive r.z it stopped at, within 25%).  The FP32 operator's own
-      // error can make the two differ by far more than rounding; then
-      // beta = 0, a restart (p = z).
-      s[S_BETA] = s[S_RZ_PREV] > 0.0 && isfinite(s[S_RZ_PREV]) && a >= 0.75 * s[S_RZ] &&
-                          a <= 1.25 * s[S_RZ]
-                      ? a / s[S_RZ_PREV]
-                      : 0.0;
-      s[S_RZ] = a;
-      s[S_BAD] = 0.0;
-      s[S_ITS] = 0.0;
-      s[S_STOP] = 0.0;
-      *stop = 0;
-      break;
   }
+}
+
+// Thresholds of a solve and of its inner loop.
+struct Tolerances {
+  double tol2, cwthr;    // ||r||^2 <= tol2 ||b||^2 and the componentwise measure <= cwthr
+  double inner_tol;      // MIXED: reduction asked of the inner loop; 0: FP64
+};
+
+// One block, before an inner loop: the residual's norm and componentwise
+// measure (pr, pc), with pb also ||b||^2; whether the solve is done, else the
+// inner loop's thresholds.  *mismatch (else NULL) non-zero: the residual is
+// not that of the caller's state, nothing runs on it.
+__global__ void __launch_bounds__(kBlock)
+k_start(int npr, const double* __restrict__ pr, const double* __restrict__ pc, int npb,
+        const double* __restrict__ pb, const int32_t* __restrict__ mismatch, Tolerances t,
+        double* __restrict__ s, int32_t* __restrict__ stop) {
+  __shared__ double red[kBlock / kWave];
+  const Combined v = combine(npr, pr, nullptr, pc, red);
+  __syncthreads();
+  double bb = 0.0;
+  if (pb) bb = combine(npb, pb, nullptr, nullptr, red).a;
+  if (threadIdx.x != 0) return;
+  if (pb) s[S_BB] = bb;
+  else bb = s[S_BB];
+  const double rr = v.a, cw = v.c, thr2 = t.tol2 * bb;
+  const bool mis = mismatch && *mismatch != 0;
+  const bool done = rr <= thr2 && !(cw > t.cwthr);
+  s[S_RR] = s[S_RR0] = rr;
+  s[S_CW] = s[S_CW0] = cw;
+  s[S_MIS] = mis ? 1.0 : 0.0;
+  s[S_DONE] = done ? 1.0 : 0.0;
+  if (t.inner_tol > 0.0) {
+    // reduce by inner_tol, or just enough (with margin) to reach the
+    // tolerance; the same for the componentwise measure when it is tested
+    const double f = fmax(t.inner_tol, 0.3 * sqrt(thr2 / rr));
+    s[S_THR] = f * f * rr;
+    s[S_CWTHR] = t.cwthr < INFINITY ? fmax(t.inner_tol, 0.3 * t.cwthr / cw) * cw : INFINITY;
+  } else {
+    s[S_THR] = thr2;
+    s[S_CWTHR] = t.cwthr;
+  }
+  const bool halt = mis || done || bb == 0.0 || !isfinite(bb);
+  s[S_BAD] = 0.0;
+  s[S_ITS] = 0.0;
+  s[S_STOP] = halt ? 1.0 : 0.0;
+  *stop = halt ? 1 : 0;
 }
 
 // Streaming vector kernels: kVec elements per thread (coalesced per element
@@ -184,8 +265,9 @@ k_partial_reduce(int np, int chunk, const double* __restrict__ pa, const double*
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
 k_init_jacobi(int64_t n, const T* __restrict__ dinv, const T* __restrict__ r, T* __restrict__ p,
-              double* __restrict__ part) {
+              double* __restrict__ part, const int32_t* __restrict__ stop) {
   __shared__ double red[kBlock / kWave];
+  if (*stop) return;
   double acc = 0.0;
   RT_VEC_LOOP(i) {
     const T z = dinv[i] * r[i];
@@ -200,8 +282,9 @@ k_init_jacobi(int64_t n, const T* __restrict__ dinv, const T* __restrict__ r, T*
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
 k_rz_jacobi(int64_t n, const T* __restrict__ dinv, const T* __restrict__ r,
-            double* __restrict__ part) {
+            double* __restrict__ part, const int32_t* __restrict__ stop) {
   __shared__ double red[kBlock / kWave];
+  if (*stop) return;
   double acc = 0.0;
   RT_VEC_LOOP(i) acc += (double)r[i] * (double)(dinv[i] * r[i]);
   acc = block_sum(acc, red);
@@ -212,8 +295,9 @@ k_rz_jacobi(int64_t n, const T* __restrict__ dinv, const T* __restrict__ r,
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
 k_copy_dot(int64_t n, const T* __restrict__ r, const T* __restrict__ z, T* __restrict__ p,
-           double* __restrict__ part) {
+           double* __restrict__ part, const int32_t* __restrict__ stop) {
   __shared__ double red[kBlock / kWave];
+  if (*stop) return;
   double acc = 0.0;
   RT_VEC_LOOP(i) {
     p[i] = z[i];
@@ -239,15 +323,25 @@ k_dot(int64_t n, const T* __restrict__ a, const T* __restrict__ b, double* __res
 // CW != CW_NONE: partC = the block maximum of the componentwise measure, with
 // w = dinv (CW_X: |r_i| w_i / |x_i| of the updated x) or fixed weights (CW_W)
 // PAIR: q holds each tile's own part of A p, completed here (pair_in)
+// npq > 0: alpha is formed here from the product's npq partials (block 0
+// keeps the record), else it is s[S_ALPHA]
 template <typename T, bool JAC, int CW, bool PAIR>
 __global__ void __launch_bounds__(kBlock)
-k_update(int64_t n, PairIn P, const T* __restrict__ qsum, const double* __restrict__ s, T* __restrict__ x, T* __restrict__ r,
+k_update(int64_t n, PairIn P, const T* __restrict__ qsum, int npq, const double* __restrict__ pq,
+         int slot, double* __restrict__ s, T* __restrict__ x, T* __restrict__ r,
          const T* __restrict__ p, const T* __restrict__ q, const T* __restrict__ dinv,
          const T* __restrict__ w, double* __restrict__ partA, double* __restrict__ partB,
-         double* __restrict__ partC, const int32_t* __restrict__ stop) {
+         double* __restrict__ partC, int32_t* __restrict__ stop) {
   __shared__ double red[kBlock / kWave];
   if (*stop) return;
-  const T alpha = (T)s[S_ALPHA];
+  double al = 0.0;
+  if (npq > 0) {
+    const Combined v = combine(npq, pq, nullptr, nullptr, red);
+    if (!take_alpha(v.a, slot, s, stop, blockIdx.x == 0, &al)) return;
+  } else {
+    al = s[S_ALPHA];
+  }
+  const T alpha = (T)al;
   double rr = 0.0, rz = 0.0, cw = 0.0;
   RT_VEC_LOOP(i) {
     const T xi = x[i] + alpha * p[i];
@@ -277,13 +371,24 @@ k_update(int64_t n, PairIn P, const T* __restrict__ qsum, const double* __restri
 }
 
 // p = z + beta p, with z = dinv r (Jacobi) or the preconditioned vector
+// np > 0: beta is formed here from the np partials of r.r, r.z and, with pc,
+// the componentwise measure (block 0 keeps the record), else it is s[S_BETA]
 template <typename T, bool JAC>
 __global__ void __launch_bounds__(kBlock)
-k_pupdate(int64_t n, const double* __restrict__ s, const T* __restrict__ r,
-          const T* __restrict__ dinv, const T* __restrict__ z, T* __restrict__ p,
-          const int32_t* __restrict__ stop) {
+k_pupdate(int64_t n, int np, const double* __restrict__ pa, const double* __restrict__ pb,
+          const double* __restrict__ pc, int slot, double* __restrict__ s,
+          const T* __restrict__ r, const T* __restrict__ dinv, const T* __restrict__ z,
+          T* __restrict__ p, int32_t* __restrict__ stop) {
+  __shared__ double red[kBlock / kWave];
   if (*stop) return;
-  const T beta = (T)s[S_BETA];
+  double be = 0.0;
+  if (np > 0) {
+    const Combined v = combine(np, pa, pb, pc, red);
+    if (!take_beta(v.a, v.b, v.c, pc != nullptr, slot, s, stop, blockIdx.x == 0, &be)) return;
+  } else {
+    be = s[S_BETA];
+  }
+  const T beta = (T)be;
   RT_VEC_LOOP(i) {
     const T zi = JAC ? dinv[i] * r[i] : z[i];
     p[i] = zi + beta * p[i];
@@ -323,9 +428,13 @@ k_resid_shift(int64_t n, const double* __restrict__ b, const double* __restrict_
   }
 }
 
-__global__ void k_add_f32(int64_t n, const float* __restrict__ d, double* __restrict__ x) {
+// x += d, d = 0 for the next inner loop
+__global__ void k_add_f32(int64_t n, float* __restrict__ d, double* __restrict__ x) {
   int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) x[i] += (double)d[i];
+  if (i < n) {
+    x[i] += (double)d[i];
+    d[i] = 0.f;
+  }
 }
 
 template <typename T>
@@ -368,7 +477,8 @@ struct Work {
   double *r64 = nullptr, *p64 = nullptr, *q64 = nullptr, *z64 = nullptr;
   float *r32 = nullptr, *p32 = nullptr, *q32 = nullptr, *z32 = nullptr, *d32 = nullptr,
         *w32 = nullptr;
-  double *partA = nullptr, *partB = nullptr, *partC = nullptr, *partF = nullptr, *scal = nullptr;
+  double *partA = nullptr, *partB = nullptr, *partC = nullptr, *partD = nullptr, *partF = nullptr,
+         *scal = nullptr;
   int32_t* stop = nullptr;
 };
 
@@ -392,51 +502,86 @@ template <> struct Sel<float> {
   static constexpr int kind = PROF_SPMV32;
 };
 
-int read_scalar(rt_ctx* ctx, const Work& W, int idx, double* out) {
-  RT_CHECK(ctx->sync_read(W.scal + idx, sizeof(double)));
-  *out = ctx->host[0];
-  return RT_OK;
-}
-
 // partial counts above which a second reduction level runs first
 #ifndef RT_PARTIAL_FOLD_MIN
 #define RT_PARTIAL_FOLD_MIN (4 * kMaxPartials)
 #endif
 
-// pc (else NULL): block maxima of the componentwise measure; the loop stops
-// only when it is <= cwthr as well
+// partials a kernel's blocks combine themselves (32 KB read by every block)
+#ifndef RT_FUSED_PARTIALS
+#define RT_FUSED_PARTIALS 4096
+#endif
+
+// np partials folded to at most kMaxPartials when they are many
+struct Partials {
+  int np;
+  const double *a, *b, *c;
+};
+int fold(rt_ctx* ctx, const Work& W, Partials* p, double* out, const int32_t* stop) {
+  if (p->np <= RT_PARTIAL_FOLD_MIN) return RT_OK;
+  const int nb2 = std::min(kMaxPartials, std::max(1, p->np / 8));
+  const int chunk = (p->np + nb2 - 1) / nb2;
+  hipLaunchKernelGGL(k_partial_reduce, dim3(nb2), dim3(kBlock), 0, ctx->stream, p->np, chunk, p->a,
+                     p->b, p->c, out, stop);
+  RT_LAUNCH_CHECK();
+  *p = Partials{nb2, out, p->b ? out + nb2 : nullptr, p->c ? out + 2 * nb2 : nullptr};
+  return RT_OK;
+}
+
+// pc (else NULL): block maxima of the componentwise measure
 int finalize(rt_ctx* ctx, const Work& W, int op, int np, const double* pa, const double* pb,
-             double thr2 = 0.0, const double* pc = nullptr, double cwthr = 0.0) {
+             const double* pc = nullptr, int slot = 0) {
   const bool in_loop = op == FIN_ALPHA || op == FIN_BETA;
-  if (np > RT_PARTIAL_FOLD_MIN) {
-    // first fold the partials into at most kMaxPartials values per array
-    const int nb2 = std::min(kMaxPartials, std::max(1, np / 8));
-    const int chunk = (np + nb2 - 1) / nb2;
-    hipLaunchKernelGGL(k_partial_reduce, dim3(nb2), dim3(kBlock), 0, ctx->stream, np, chunk, pa,
-                       pb, pc, W.partF, in_loop ? W.stop : nullptr);
-    RT_LAUNCH_CHECK();
-    pa = W.partF;
-    pb = pb ? W.partF + nb2 : nullptr;
-    pc = pc ? W.partF + 2 * nb2 : nullptr;
-    np = nb2;
-  }
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kBlock), 0, ctx->stream, op, np, pa, pb, pc,
-                     W.scal, W.stop, thr2, cwthr);
+  Partials p{np, pa, pb, pc};
+  RT_CHECK(fold(ctx, W, &p, W.partF, in_loop ? W.stop : nullptr));
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kBlock), 0, ctx->stream, op, p.np, p.a, p.b, p.c,
+                     W.scal, W.stop, slot);
   RT_LAUNCH_CHECK();
   return RT_OK;
 }
 
-// Componentwise test of a PCG loop: the update kernel's measure (mode), its
-// weights and the threshold (infinity: measured, never binding).
+// residual partials (npr of pr and pc), with pb also ||b||^2 (npb partials)
+int start(rt_ctx* ctx, const Work& W, int npr, const double* pr, const double* pc, int npb,
+          const double* pb, const int32_t* mismatch, const Tolerances& t) {
+  Partials a{npr, pr, nullptr, pc}, b{npb, pb, nullptr, nullptr};
+  RT_CHECK(fold(ctx, W, &a, W.partF, nullptr));
+  if (pb) RT_CHECK(fold(ctx, W, &b, W.partF + 3 * kMaxPartials, nullptr));
+  hipLaunchKernelGGL(k_start, dim3(1), dim3(kBlock), 0, ctx->stream, a.np, a.a, a.c, b.np, b.a,
+                     mismatch, t, W.scal, W.stop);
+  RT_LAUNCH_CHECK();
+  return RT_OK;
+}
+
+// Componentwise test of a PCG loop: the update kernel's measure (mode) and its
+// weights; the threshold is s[S_CWTHR] (infinity: measured, never binding).
 struct CwTest {
   int mode = CW_NONE;
   const void* w = nullptr;
-  double thr = INFINITY;
 };
 
-// One PCG iteration, queued; a no-op on the device once the stop flag is set.
+// p = z + beta p, beta from np partials (partA, partB, pc), or from the
+// scalars when np = 0
 template <typename T>
-int pcg_iteration(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r, double thr2, const CwTest& cw) {
+int pupdate(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, int np, const double* pc, int slot,
+            const T* r) {
+  using S = Sel<T>;
+  const Level& L = A->levels[0];
+  const int gv = vec_blocks(L.n);
+  if (amg)
+    hipLaunchKernelGGL((k_pupdate<T, false>), dim3(gv), dim3(kBlock), 0, ctx->stream, L.n, np,
+                       W.partA, W.partB, pc, slot, W.scal, r, nullptr, S::z(W), S::p(W), W.stop);
+  else
+    hipLaunchKernelGGL((k_pupdate<T, true>), dim3(gv), dim3(kBlock), 0, ctx->stream, L.n, np,
+                       W.partA, W.partB, pc, slot, W.scal, r, S::dinv(L), nullptr, S::p(W), W.stop);
+  RT_LAUNCH_CHECK();
+  return RT_OK;
+}
+
+// One PCG iteration, queued; a no-op on the device once the stop flag is set.
+// slot: the place of r.z it starts from (0, 1, 0, ... over the loop).
+template <typename T>
+int pcg_iteration(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r, const CwTest& cw,
+                  int slot) {
   using S = Sel<T>;
   hipStream_t st = ctx->stream;
   const Level& L = A->levels[0];
@@ -444,26 +589,30 @@ int pcg_iteration(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r
   T* p = S::p(W);
   T* q = S::q(W);
   T* z = S::z(W);
-  const int32_t* stop = W.stop;
+  int32_t* stop = W.stop;
   const int gv = vec_blocks(n);
   int nbk = 0;
   Prof pf(ctx, S::kind);
   RT_CHECK(pf.begin());
   const bool pair = pair_serves(L, level_shape<T>(L));
   if (pair)
-    RT_CHECK((launch_pair<T, PP_DOT>(st, L, S::diag(L), p, q, W.partA, &nbk, level_shape<T>(L),
+    RT_CHECK((launch_pair<T, PP_DOT>(st, L, S::diag(L), p, q, W.partD, &nbk, level_shape<T>(L),
                                      nullptr, stop)));
   else
     RT_CHECK((launch_spmv_level<T, SP_DOT>(st, L, S::val(L), S::diag(L), p, nullptr, nullptr, q,
-                                           nullptr, W.partA, &nbk, level_shape<T>(L), nullptr,
+                                           nullptr, W.partD, &nbk, level_shape<T>(L), nullptr,
                                            stop)));
   RT_CHECK(pf.end());
-  RT_CHECK(finalize(ctx, W, FIN_ALPHA, nbk, W.partA, nullptr));
+  // the product's partials go to partD, so that the update's blocks can read
+  // them while others already write theirs
+  const bool fa = nbk <= RT_FUSED_PARTIALS, fb = gv <= RT_FUSED_PARTIALS;
+  if (!fa) RT_CHECK(finalize(ctx, W, FIN_ALPHA, nbk, W.partD, nullptr, nullptr, slot));
   const T* w = static_cast<const T*>(cw.w);
   double* pc = cw.mode == CW_NONE ? nullptr : W.partC;
 #define RT_UPD1(JAC_, CW_, PAIR_)                                                               \
   hipLaunchKernelGGL((k_update<T, JAC_, CW_, PAIR_>), dim3(gv), dim3(kBlock), 0, st, n,          \
-                     L.pair.in(), PairSel<T>::sum(L.pair), W.scal, x, r, p, q,                   \
+                     L.pair.in(), PairSel<T>::sum(L.pair), fa ? nbk : 0, W.partD, slot, W.scal, x, \
+                     r, p, q,                                                                    \
                      JAC_ ? S::dinv(L) : nullptr, w, W.partA, JAC_ ? W.partB : nullptr, pc, stop)
 #define RT_UPD(JAC_, CW_)                   \
   do {                                      \
@@ -485,14 +634,8 @@ int pcg_iteration(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r
 #undef RT_UPD
 #undef RT_UPD1
   RT_LAUNCH_CHECK();
-  RT_CHECK(finalize(ctx, W, FIN_BETA, gv, W.partA, W.partB, thr2, pc, cw.thr));
-  if (amg)
-    hipLaunchKernelGGL((k_pupdate<T, false>), dim3(gv), dim3(kBlock), 0, st, n, W.scal, r,
-                       nullptr, z, p, stop);
-  else
-    hipLaunchKernelGGL((k_pupdate<T, true>), dim3(gv), dim3(kBlock), 0, st, n, W.scal, r,
-                       S::dinv(L), nullptr, p, stop);
-  RT_LAUNCH_CHECK();
+  if (!fb) RT_CHECK(finalize(ctx, W, FIN_BETA, gv, W.partA, W.partB, pc, slot));
+  RT_CHECK(pupdate<T>(ctx, A, W, amg, fb ? gv : 0, pc, slot, r));
   return RT_OK;
 }
 
@@ -507,13 +650,34 @@ int next_chunk(double rr_prev, int its_prev, double rr, int its, double thr2) {
   return (int)std::min(64.0, std::max(1.0, std::floor(0.75 * need)));
 }
 
-// PCG iterations on A x = b given r = b - A x and s[S_RR] = ||r||^2 on entry.
-// Stops when ||r||^2 <= thr2 (and the componentwise measure, cw0 on entry,
-// is <= cw.thr) or after max_it iterations; *cw_out: the measure at the end.
+// What a loop found and did, read back from the device scalars.
+struct LoopState {
+  double bb = 0.0, rr0 = 0.0, cw0 = 0.0;   // at its start (k_start)
+  double rr = 0.0, cw = 0.0;               // at its end
+  int its = 0;
+  bool done = false, mismatch = false, bad = false;
+};
+int read_state(rt_ctx* ctx, const Work& W, LoopState* s) {
+  RT_CHECK(ctx->sync_read(W.scal, sizeof(double) * S_COUNT));
+  const double* h = ctx->host;
+  s->bb = h[S_BB];
+  s->rr0 = h[S_RR0];
+  s->cw0 = h[S_CW0];
+  s->rr = h[S_RR];
+  s->cw = h[S_CW];
+  s->its = (int)h[S_ITS];
+  s->done = h[S_DONE] != 0.0;
+  s->mismatch = h[S_MIS] != 0.0;
+  s->bad = h[S_BAD] != 0.0;
+  return RT_OK;
+}
+
+// PCG iterations on A x = b given r = b - A x, after start() has set the
+// thresholds: until the device stops or max_it iterations ran.  first: the
+// iterations queued before the first read of the state.
 template <typename T>
-int pcg_core(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r, double rr0, double thr2,
-             int max_it, int* its_out, double* rr_out, const CwTest& cw = CwTest{},
-             double cw0 = 0.0, double* cw_out = nullptr, bool resume = false) {
+int pcg_core(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r, int max_it,
+             const CwTest& cw, int first, bool resume, LoopState* out) {
   using S = Sel<T>;
   hipStream_t st = ctx->stream;
   const Level& L = A->levels[0];
@@ -521,71 +685,58 @@ int pcg_core(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r, dou
   T* p = S::p(W);
   T* z = S::z(W);
   const int gv = vec_blocks(n);
-  *its_out = 0;
-  *rr_out = rr0;
-  if (cw_out) *cw_out = cw0;
-  if ((rr0 <= thr2 && !(cw0 > cw.thr)) || max_it <= 0) return RT_OK;
+  *out = LoopState{};
+  if (max_it <= 0) return read_state(ctx, W, out);
+  if (amg) RT_CHECK(vcycle<T>(ctx, A, r, z, W.stop));
   if (resume) {
     // the last loop on this system ended at a residual replacement: its
     // search direction p carries over, p = z + beta p with the new r.z
-    if (amg) {
-      RT_CHECK(vcycle<T>(ctx, A, r, z));
-      hipLaunchKernelGGL(k_dot<T>, dim3(gv), dim3(kBlock), 0, st, n, r, z, W.partB, nullptr);
-    } else {
-      hipLaunchKernelGGL(k_rz_jacobi<T>, dim3(gv), dim3(kBlock), 0, st, n, S::dinv(L), r,
-                         W.partB);
-    }
-    RT_LAUNCH_CHECK();
-    RT_CHECK(finalize(ctx, W, FIN_RESUME, gv, W.partB, nullptr));   // clears the stop flag
     if (amg)
-      hipLaunchKernelGGL((k_pupdate<T, false>), dim3(gv), dim3(kBlock), 0, st, n, W.scal, r,
-                         nullptr, z, p, W.stop);
+      hipLaunchKernelGGL(k_dot<T>, dim3(gv), dim3(kBlock), 0, st, n, r, z, W.partB, W.stop);
     else
-      hipLaunchKernelGGL((k_pupdate<T, true>), dim3(gv), dim3(kBlock), 0, st, n, W.scal, r,
-                         S::dinv(L), nullptr, p, W.stop);
-  } else if (amg) {
-    RT_CHECK(vcycle<T>(ctx, A, r, z));
-    hipLaunchKernelGGL(k_copy_dot<T>, dim3(gv), dim3(kBlock), 0, st, n, r, z, p, W.partB);
+      hipLaunchKernelGGL(k_rz_jacobi<T>, dim3(gv), dim3(kBlock), 0, st, n, S::dinv(L), r, W.partB,
+                         W.stop);
+    RT_LAUNCH_CHECK();
+    RT_CHECK(finalize(ctx, W, FIN_RESUME, gv, W.partB, nullptr));
+    RT_CHECK(pupdate<T>(ctx, A, W, amg, 0, nullptr, 0, r));
   } else {
-    hipLaunchKernelGGL(k_init_jacobi<T>, dim3(gv), dim3(kBlock), 0, st, n, S::dinv(L), r, p,
-                       W.partB);
+    if (amg)
+      hipLaunchKernelGGL(k_copy_dot<T>, dim3(gv), dim3(kBlock), 0, st, n, r, z, p, W.partB, W.stop);
+    else
+      hipLaunchKernelGGL(k_init_jacobi<T>, dim3(gv), dim3(kBlock), 0, st, n, S::dinv(L), r, p,
+                         W.partB, W.stop);
+    RT_LAUNCH_CHECK();
+    RT_CHECK(finalize(ctx, W, FIN_RZ, gv, W.partB, nullptr));
   }
-  RT_LAUNCH_CHECK();
-  if (!resume) RT_CHECK(finalize(ctx, W, FIN_RZ, gv, W.partB, nullptr));   // clears the stop flag
   const size_t spans0 = ctx->prof_spans.size();
-  double rr = rr0, rr_prev = rr0;
-  int its = 0, its_prev = 0, queued = 0, chunk = 1;
-  bool stopped = false, bad = false;
+  double rr_prev = 0.0;
+  int its_prev = 0, queued = 0, chunk = first;
   while (queued < max_it) {
     const int k = std::min(chunk, max_it - queued);
-    for (int j = 0; j < k; ++j) RT_CHECK(pcg_iteration<T>(ctx, A, W, amg, x, r, thr2, cw));
+    for (int j = 0; j < k; ++j)
+      RT_CHECK(pcg_iteration<T>(ctx, A, W, amg, x, r, cw, (queued + j) & 1));
+    const bool start_read = queued == 0;
     queued += k;
-    RT_CHECK(ctx->sync_read(W.scal, sizeof(double) * S_COUNT));
-    const double* hs = ctx->host;
-    rr = hs[S_RR];
-    its = (int)hs[S_ITS];
-    stopped = hs[S_STOP] != 0.0;
-    bad = hs[S_BAD] != 0.0;
-    if (its > 0 && !std::isfinite(rr)) {
+    RT_CHECK(read_state(ctx, W, out));
+    if (start_read) rr_prev = out->rr0;
+    if (out->its > 0 && !std::isfinite(out->rr)) {
       set_error("PCG breakdown: non-finite residual");
-      *its_out = its;
-      *rr_out = rr;
       return RT_E_DEVICE;
     }
-    if (cw_out && its > 0) *cw_out = hs[S_CW];
-    if (stopped) break;
+    if (ctx->host[S_STOP] != 0.0) break;
     // while the componentwise test still binds, go by one iteration at a time
-    chunk = rr > thr2 ? next_chunk(rr_prev, its_prev, rr, its, thr2) : 1;
-    rr_prev = rr;
-    its_prev = its;
+    const double thr2 = ctx->host[S_THR];
+    chunk = out->rr > thr2 ? next_chunk(rr_prev, its_prev, out->rr, out->its, thr2) : 1;
+    // an estimate from few iterations is often far too long: at most double
+    chunk = std::min(chunk, std::max(2, out->its));
+    rr_prev = out->rr;
+    its_prev = out->its;
   }
-  if (its == 0) rr = rr0;
-  if (bad && rr > thr2) set_error("PCG breakdown: p.Ap not positive after %d iterations", its);
+  if (out->bad && out->rr > ctx->host[S_THR])
+    set_error("PCG breakdown: p.Ap not positive after %d iterations", out->its);
   // product timings of queued iterations that did not run are dropped
-  if (ctx->profiling && ctx->prof_spans.size() > spans0 + (size_t)its)
-    ctx->prof_spans.resize(spans0 + (size_t)its);
-  *its_out = its;
-  *rr_out = rr;
+  if (ctx->profiling && ctx->prof_spans.size() > spans0 + (size_t)out->its)
+    ctx->prof_spans.resize(spans0 + (size_t)out->its);
   return RT_OK;
 }
 
@@ -595,8 +746,9 @@ int ensure_work(rt_matrix* A, bool mixed) {
   RT_CHECK(A->partA.reserve(max_partials(n)));
   RT_CHECK(A->partB.reserve(max_partials(n)));
   RT_CHECK(A->partC.reserve(max_partials(n)));
-  RT_CHECK(A->partF.reserve(3 * kMaxPartials));
-  RT_CHECK(A->scal.reserve(S_COUNT));
+  RT_CHECK(A->partD.reserve(max_partials(n)));
+  RT_CHECK(A->partF.reserve(6 * kMaxPartials));
+  RT_CHECK(A->scal.reserve(std::max<int>(S_COUNT, kScalars)));
   RT_CHECK(A->stop.reserve(1));
   if (mixed)
     for (auto* b : {&A->r32, &A->p32, &A->q32, &A->z32, &A->d32, &A->w32}) RT_CHECK(b->reserve(n));
@@ -627,32 +779,28 @@ Work work_of(rt_matrix* A) {
   W.partA = A->partA.p;
   W.partB = A->partB.p;
   W.partC = A->partC.p;
+  W.partD = A->partD.p;
   W.partF = A->partF.p;
   W.scal = A->scal.p;
   W.stop = A->stop.p;
   return W;
 }
 
-// r = b - A x in FP64 (optionally also r32 and the componentwise weights w32);
-// returns ||r||^2 and the componentwise measure max_i |r_i| / (a_ii |x_i|)
+// r = b - A x in FP64 (optionally also r32 and the componentwise weights
+// w32), with *nparts partials of ||r||^2 and of the componentwise measure
+// max_i |r_i| / (a_ii |x_i|) in partA and partC
 int residual64(rt_ctx* ctx, rt_matrix* A, const Work& W, const double* b, const double* x, float* r32,
-               float* w32, double* rr, double* cw) {
+               float* w32, int* nparts) {
   const Level& L = A->levels[0];
-  int nbk = 0;
   Prof pf(ctx, PROF_RESID64);
   RT_CHECK(pf.begin());
   if (pair_serves(L, resid_shape(L)))
-    RT_CHECK(pair_resid(ctx, L, x, b, W.r64, r32, w32, W.partA, W.partC, &nbk, resid_shape(L)));
+    RT_CHECK(pair_resid(ctx, L, x, b, W.r64, r32, w32, W.partA, W.partC, nparts, resid_shape(L)));
   else
     RT_CHECK((launch_spmv_level<double, SP_RESID>(ctx->stream, L, L.val64.p, L.diag64.p, x, b,
-                                                  nullptr, W.r64, r32, W.partA, &nbk,
+                                                  nullptr, W.r64, r32, W.partA, nparts,
                                                   resid_shape(L), nullptr, nullptr, W.partC, w32)));
-  RT_CHECK(pf.end());
-  RT_CHECK(finalize(ctx, W, FIN_RR, nbk, W.partA, nullptr, 0.0, W.partC));
-  RT_CHECK(ctx->sync_read(W.scal, sizeof(double) * S_COUNT));
-  *rr = ctx->host[S_RR];
-  *cw = ctx->host[S_CW];
-  return RT_OK;
+  return pf.end();
 }
 
 // FP64 CG steps after which the recursive residual is replaced by a
@@ -680,32 +828,42 @@ int solve_work(rt_ctx* ctx, rt_matrix* A, const Work& W, const double* b, double
   // componentwise test: its threshold, infinity when only measured
   const bool use_cw = o->cw_tol > 0.0;
   const double cwthr = use_cw ? o->cw_tol : INFINITY;
+  float* r32 = mixed ? W.r32 : nullptr;
   float* w32 = mixed && use_cw ? W.w32 : nullptr;
-  double bb = 0.0, rr = 0.0, cw = 0.0;
-  bool have_r = false;   // r64 (and r32) hold b - A x, rr = ||r||^2, cw its measure
-  if (b_prev) {
-    hipLaunchKernelGGL(k_resid_shift, dim3(gv), dim3(kBlock), 0, st, n, b, b_prev, x,
-                       L0.diag64.p, W.r64, mixed ? W.r32 : nullptr, w32, W.partA,
-                       W.partB, W.partC);
+  const Tolerances t{o->tol * o->tol, cwthr, mixed ? o->inner_tol : 0.0};
+  const CwTest cwt = mixed ? (use_cw ? CwTest{CW_W, w32} : CwTest{}) : CwTest{CW_X, L0.dinv64.p};
+  if (mixed) {
+    hipLaunchKernelGGL(k_zero<float>, dim3(grid_for(n)), dim3(kBlock), 0, st, n, W.d32);
     RT_LAUNCH_CHECK();
-    RT_CHECK(finalize(ctx, W, FIN_RR, gv, W.partA, nullptr, 0.0, W.partC));
-    RT_CHECK(finalize(ctx, W, FIN_BB, gv, W.partB, nullptr));
-    RT_CHECK_HIP(hipMemcpyAsync(ctx->host + S_COUNT, mismatch, sizeof(int32_t),
-                                hipMemcpyDeviceToHost, st));
-    RT_CHECK(ctx->sync_read(W.scal, sizeof(double) * S_COUNT));
-    int32_t mis = 0;
-    std::memcpy(&mis, ctx->host + S_COUNT, sizeof(int32_t));
-    bb = ctx->host[S_BB];
-    rr = ctx->host[S_RR];
-    cw = ctx->host[S_CW];
-    have_r = mis == 0;
-  } else {
-    hipLaunchKernelGGL(k_dot<double>, dim3(gv), dim3(kBlock), 0, st, n, b, b, W.partB,
-                       nullptr);
-    RT_LAUNCH_CHECK();
-    RT_CHECK(finalize(ctx, W, FIN_BB, gv, W.partB, nullptr));
-    RT_CHECK(read_scalar(ctx, W, S_BB, &bb));
   }
+  // one inner loop (a whole solve in FP64) on the residual that start() saw
+  auto loop = [&](int max_it, int first, bool resume, LoopState* ls) {
+    return mixed ? pcg_core<float>(ctx, A, W, amg, W.d32, W.r32, max_it, cwt, first, resume, ls)
+                 : pcg_core<double>(ctx, A, W, amg, x, W.r64, max_it, cwt, first, resume, ls);
+  };
+  // the first residual: the last one shifted by the change of b, or a product
+  bool shifted = b_prev != nullptr;
+  int nbk = 0;
+  LoopState ls;
+  const int first = mixed ? 2 : 3;
+  for (;;) {
+    if (shifted) {
+      hipLaunchKernelGGL(k_resid_shift, dim3(gv), dim3(kBlock), 0, st, n, b, b_prev, x,
+                         L0.diag64.p, W.r64, r32, w32, W.partA, W.partB, W.partC);
+      RT_LAUNCH_CHECK();
+      RT_CHECK(start(ctx, W, gv, W.partA, W.partC, gv, W.partB, mismatch, t));
+    } else {
+      hipLaunchKernelGGL(k_dot<double>, dim3(gv), dim3(kBlock), 0, st, n, b, b, W.partB, nullptr);
+      RT_LAUNCH_CHECK();
+      RT_CHECK(residual64(ctx, A, W, b, x, r32, w32, &nbk));
+      RT_CHECK(start(ctx, W, nbk, W.partA, W.partC, gv, W.partB, nullptr, t));
+    }
+    const int s = loop(mixed && o->max_refine <= 0 ? 0 : o->max_iter, first, false, &ls);
+    if (std::isfinite(ls.bb) && s < 0) return s;
+    if (!ls.mismatch) break;
+    shifted = false;   // E^l is not the last solution: form the residual
+  }
+  const double bb = ls.bb;
   if (!std::isfinite(bb)) {
     set_error("rt_solve: right-hand side is not finite");
     return RT_E_ARG;
@@ -716,58 +874,52 @@ int solve_work(rt_ctx* ctx, rt_matrix* A, const Work& W, const double* b, double
     return RT_OK;
   }
   const double thr2 = o->tol * o->tol * bb;
+  stt->init_rel_residual = std::sqrt(ls.rr0 / bb);
   int status = RT_OK;
+  double rr = ls.rr, cw = ls.cw;
   if (!mixed) {
-    int rec = have_r ? *rec_steps : 0;
-    if (!have_r) RT_CHECK(residual64(ctx, A, W, b, x, nullptr, nullptr, &rr, &cw));
-    stt->init_rel_residual = std::sqrt(rr / bb);
-    const CwTest t{CW_X, L0.dinv64.p, cwthr};
-    int total = 0;
-    for (int pass = 0;; ++pass) {
-      int its = 0;
-      RT_CHECK(pcg_core<double>(ctx, A, W, amg, x, W.r64, rr, thr2, o->max_iter - total, &its,
-                                &rr, t, cw, &cw));
-      total += its;
-      rec += its;
-      if (rec <= kReplaceSteps || pass == 2) break;
+    int rec = shifted ? *rec_steps : 0;
+    int total = ls.its;
+    rec += ls.its;
+    for (int pass = 0; rec > kReplaceSteps && pass < 2; ++pass) {
       // residual replacement; CG restarts from the computed residual if it
       // misses the tolerance
-      RT_CHECK(residual64(ctx, A, W, b, x, nullptr, nullptr, &rr, &cw));
+      RT_CHECK(residual64(ctx, A, W, b, x, nullptr, nullptr, &nbk));
+      RT_CHECK(start(ctx, W, nbk, W.partA, W.partC, 0, nullptr, nullptr, t));
       rec = 0;
       ++stt->replacements;
-      if (!(rr > thr2 || cw > cwthr) || total >= o->max_iter) break;
+      RT_CHECK(loop(o->max_iter - total, first, false, &ls));
+      rr = ls.rr;
+      cw = ls.cw;
+      total += ls.its;
+      rec += ls.its;
+      if (ls.done || total >= o->max_iter) break;
     }
     stt->iterations = total;
     *rec_steps = rec;
   } else {
-    if (!have_r) RT_CHECK(residual64(ctx, A, W, b, x, W.r32, w32, &rr, &cw));
-    stt->init_rel_residual = std::sqrt(rr / bb);
     *rec_steps = 0;
     int total = 0, refine = 0;
     // After the first inner solve each one continues the last: the FP64
     // residual replaces CG's recursive one (reliable update) and the search
     // direction carries over, so the refinements do not restart the Krylov
     // space.
-    bool resume = false;
-    while ((rr > thr2 || cw > cwthr) && total < o->max_iter && refine < o->max_refine) {
-      // reduce by inner_tol, or just enough (with margin) to reach tol; the
-      // same for the componentwise measure when it is tested
-      const double red = std::max(o->inner_tol, 0.3 * std::sqrt(thr2 / rr));
-      CwTest t{};
-      if (use_cw) t = CwTest{CW_W, w32, std::max(o->inner_tol, 0.3 * cwthr / cw) * cw};
-      hipLaunchKernelGGL(k_zero<float>, dim3(grid_for(n)), dim3(kBlock), 0, st, n, W.d32);
-      RT_LAUNCH_CHECK();
-      int its = 0;
-      double rr_in = 0.0;
-      RT_CHECK(pcg_core<float>(ctx, A, W, amg, W.d32, W.r32, rr, red * red * rr,
-                               o->max_iter - total, &its, &rr_in, t, cw, nullptr, resume));
+    rr = ls.rr0;
+    cw = ls.cw0;
+    while (!ls.done && total < o->max_iter && refine < o->max_refine) {
+      const int its = ls.its;
       total += its;
-      resume = its > 0;
       hipLaunchKernelGGL(k_add_f32, dim3(grid_for(n)), dim3(kBlock), 0, st, n, W.d32, x);
       RT_LAUNCH_CHECK();
-      RT_CHECK(residual64(ctx, A, W, b, x, W.r32, w32, &rr, &cw));
+      RT_CHECK(residual64(ctx, A, W, b, x, W.r32, w32, &nbk));
+      RT_CHECK(start(ctx, W, nbk, W.partA, W.partC, 0, nullptr, nullptr, t));
       ++refine;
-      if (its == 0) break;
+      // the next inner loop, queued before the host knows whether it is needed
+      const bool more = its > 0 && total < o->max_iter && refine < o->max_refine;
+      RT_CHECK(loop(more ? o->max_iter - total : 0, first, its > 0, &ls));
+      rr = ls.rr0;
+      cw = ls.cw0;
+      if (!more) break;
     }
     stt->iterations = total;
     stt->refinements = refine;
@@ -793,14 +945,19 @@ int residual_norms(rt_ctx* ctx, rt_matrix* A, const double* b, const double* x, 
   RT_CHECK(ensure_work(A, false));
   RT_CHECK(ensure_shapes(ctx, A, true));
   const Work W = work_of(A);
-  double cw = 0.0;
-  RT_CHECK(residual64(ctx, A, W, b, x, nullptr, nullptr, rr, &cw));
+  int nbk = 0;
+  RT_CHECK(residual64(ctx, A, W, b, x, nullptr, nullptr, &nbk));
+  RT_CHECK(finalize(ctx, W, FIN_RR, nbk, W.partA, nullptr, W.partC));
   const int gv = vec_blocks(A->n);
   hipLaunchKernelGGL(k_dot<double>, dim3(gv), dim3(kBlock), 0, ctx->stream, A->n, b, b, W.partB,
                      nullptr);
   RT_LAUNCH_CHECK();
   RT_CHECK(finalize(ctx, W, FIN_BB, gv, W.partB, nullptr));
-  return read_scalar(ctx, W, S_BB, bb);
+  LoopState ls;
+  RT_CHECK(read_state(ctx, W, &ls));
+  *rr = ls.rr;
+  *bb = ls.bb;
+  return RT_OK;
 }
 
 int solve_sorted(rt_ctx* ctx, rt_matrix* A, const double* b, double* x, const rt_solve_opts* o,
@@ -877,8 +1034,11 @@ int check_solve_opts(const rt_solve_opts* o) {
 namespace rt {
 namespace {
 
+// Largest systems of the no-allocation solve.
+constexpr int64_t kScratchMaxFp64 = 4968256, kScratchMaxMixed = 3439552;
+
 // Bytes of scratch the no-allocation solve carves for n unknowns: the gathered
-// b and x, four FP64 work vectors (six FP32 ones in mixed precision), three
+// b and x, four FP64 work vectors (six FP32 ones in mixed precision), four
 // arrays of block partials, the fold buffer, the scalars and the stop flag,
 // each piece 256-byte aligned.
 struct Carve {
@@ -909,10 +1069,10 @@ Work carve_work(Carve& c, int64_t n, bool mixed, double** bs, double** xs) {
     W.d32 = c.take<float>(n);
     W.w32 = c.take<float>(n);
   }
-  W.partA = c.take<double>(max_partials(n));
-  W.partB = c.take<double>(max_partials(n));
-  W.partC = c.take<double>(max_partials(n));
-  W.partF = c.take<double>(3 * kMaxPartials);
+  // partials of products (at most one per four rows) and of vector passes
+  for (double** p : {&W.partA, &W.partC, &W.partD}) *p = c.take<double>(spmv_blocks(n, 64));
+  W.partB = c.take<double>(vec_blocks(n));
+  W.partF = c.take<double>(6 * kMaxPartials);
   W.scal = c.take<double>(S_COUNT);
   W.stop = c.take<int32_t>(1);
   return W;
@@ -946,7 +1106,9 @@ extern "C" int rt_solve_noalloc(rt_ctx* ctx, rt_matrix* A, const double* b, doub
   Carve size{nullptr};
   double *bs = nullptr, *xs = nullptr;
   (void)carve_work(size, n, mixed, &bs, &xs);
-  if (size.used > kScratchBytes) {
+  // the documented limits (the pieces just fit the array at them)
+  const int64_t most = mixed ? kScratchMaxMixed : kScratchMaxFp64;
+  if (n > most || size.used > kScratchBytes) {
     set_error("rt_solve_noalloc: %lld unknowns need %zu bytes of scratch in %s, above the "
               "%zu-byte scratch array", (long long)n, size.used,
               mixed ? "mixed precision" : "FP64", kScratchBytes);
