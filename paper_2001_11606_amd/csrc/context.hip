@@ -235,7 +235,8 @@ int rt_create(rt_ctx** ctx, int device, void* hip_stream) {
   rt_ctx* c = new rt_ctx();
   c->device = device;
   c->stream = (hipStream_t)hip_stream;
-  if (hipHostMalloc((void**)&c->host, 64 * sizeof(double), hipHostMallocDefault) != hipSuccess) {
+  if (hipHostMalloc((void**)&c->host, rt_ctx::kHostDoubles * sizeof(double),
+                    hipHostMallocDefault) != hipSuccess) {
     delete c;
     rt::set_error("rt_create: pinned host allocation failed");
     return RT_E_OOM;

@@ -217,7 +217,8 @@ struct rt_ctx {
   bool profiling = false;
   hipEvent_t ev0 = nullptr, ev1 = nullptr;
   // small pinned host staging area for scalar read-backs
-  double* host = nullptr;     // 64 doubles
+  double* host = nullptr;     // kHostDoubles doubles
+  static constexpr int kHostDoubles = 4608;
   int sync_read(const void* dev, size_t bytes);   // async copy to host + stream sync
   // profiling: events recorded around timed launches, resolved at the end of a call
   std::vector<hipEvent_t> prof_ev;
@@ -431,8 +432,6 @@ int build_tiles(rt_ctx* ctx, Level& L);
 // assembly the values, diagonal and ghost couplings
 int build_pairs(rt_ctx* ctx, const rt_neighbors* nb, Level& L);
 int assemble_pairs(rt_ctx* ctx, rt_matrix* A);
-// y += the sums the last FP64 pair product left for its rows
-int pair_finish(rt_ctx* ctx, const Level& L, double* y);
 // r = b - A x from the pair form (FP64), with the outputs of the CSR residual
 // product: r32 and w32 may be NULL, part and pmax receive *nparts values
 int pair_resid(rt_ctx* ctx, const Level& L, const double* x, const double* b, double* r,

@@ -540,13 +540,6 @@ k_pair_diag(int64_t nin, int kernel, double dt, double c, DiagArgs A, PairIn P,
   A.g[i] = vd[0] * gsum;
 }
 
-// y += the sums earlier tiles left
-__global__ void __launch_bounds__(kBlock)
-k_pair_finish(int64_t n, PairIn P, const double* __restrict__ xsum, double* __restrict__ y) {
-  const int64_t i = blockIdx.x * (int64_t)kTileRows + threadIdx.x;
-  if (i < n) y[i] += pair_in<double>(P, i, xsum);
-}
-
 // r = b - (r + the sums earlier tiles left) with the residual product's block
 // partials and weights (see k_spmv)
 __global__ void __launch_bounds__(kBlock)
@@ -683,14 +676,6 @@ int pair_resid(rt_ctx* ctx, const Level& L, const double* x, const double* b, do
                      skip);
   RT_LAUNCH_CHECK();
   *nparts = (int)L.pair.ntiles;
-  return RT_OK;
-}
-
-int pair_finish(rt_ctx* ctx, const Level& L, double* y) {
-  if (L.n == 0) return RT_OK;
-  hipLaunchKernelGGL(k_pair_finish, dim3((unsigned)L.pair.ntiles), dim3(kBlock), 0, ctx->stream,
-                     L.n, L.pair.in(), L.pair.sum64.p, y);
-  RT_LAUNCH_CHECK();
   return RT_OK;
 }
 

@@ -123,6 +123,38 @@ def test_matrix_outlives_neighbour_handle(ctx):
         assert np.max(np.abs(x - xref)) / np.max(np.abs(xref)) <= 1e-12
 
 
+@pytest.mark.parametrize("n,restart", [(1, 4), (20, 4), (93, 12)])
+def test_gmres_sizes(ctx, n, restart):
+    """GMRES with one and with four elements per thread in its basis passes
+    (804k rows), cut off inside a cycle and run to the end: the residual it
+    reports is that of the exported matrix (summation order apart)."""
+    import scipy.sparse as sp
+    import torch
+    from paper_2001_11606_amd import rt
+    dp, nb, A = gpu_system(ctx, synth.config3(n=n), amg=rt.amg_opts(max_levels=1))
+    nin = dp.n_interior
+    rp, col, val, _ = (t.cpu().numpy() for t in ctx.export_matrix(A))
+    mat = sp.csr_matrix((val, col, rp), shape=(nin, nin))
+    V = (dp.arrays["m"] / dp.arrays["rho"])[:nin].cpu().numpy()
+    bt = torch.tensor(np.random.default_rng(8).standard_normal(nin) * V, device=ctx.device)
+
+    def run(max_iter):
+        xt = torch.zeros_like(bt)
+        status, st = ctx.solve_gmres(A, bt, xt, rt.gmres_opts(0, 1e-11, max_iter, restart))
+        b, x = bt.cpu().numpy(), xt.cpu().numpy()
+        rel = np.linalg.norm((b - mat @ x) / V) / np.linalg.norm(b / V)
+        assert abs(rel - st.rel_residual) <= 1e-6 * rel + 1e-14
+        return status, st, x
+
+    status, st, x = run(3000)
+    assert status == rt.RT_OK and st.rel_residual <= 1e-11
+    assert np.array_equal(x, run(3000)[2])   # the same bits
+    for cut in (1, 3, restart + 1):
+        if cut < st.iterations:
+            s, c, _ = run(cut)
+            assert s == rt.RT_NOT_CONVERGED and c.iterations == cut
+
+
 @pytest.mark.parametrize("mixed_forms", [False, True])
 def test_batch_of_pair_form_matrices(ctx, mixed_forms):
     """A batch whose matrices all have the pair form takes it over (also after
