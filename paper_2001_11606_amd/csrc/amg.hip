@@ -778,15 +778,6 @@ __global__ void k_coarse_solve(int64_t n, const double* __restrict__ M, const T*
 
 // The vector passes below take one row per thread; stop (else NULL) holds
 // the flag of the block's 256-row chunk at tp[block] (tp NULL: one flag).
-template <typename T>
-__global__ void k_scale(int64_t n, const T* __restrict__ s, const T* __restrict__ b,
-                        T* __restrict__ x, const int32_t* __restrict__ tp,
-                        const int32_t* __restrict__ stop) {
-  if (stop && stop[tp ? tp[blockIdx.x] : 0]) return;
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) x[i] = s[i] * b[i];
-}
-
 // bc[I] = sum of r over the members of aggregate I: kRestrictG lanes per
 // aggregate (about 16 members), each lane's members in ascending order, then
 // the lanes; with one lane per aggregate the members' loads queue up one
@@ -845,31 +836,70 @@ __global__ void k_axpy1(int64_t n, const T* __restrict__ y, T* __restrict__ x,
   if (i < n) x[i] += y[i];
 }
 
-// x += P xc (rows left out of the coarse space get nothing)
+// bc[I] = sum of b - A x over the members of aggregate I, for a small level
+// (plain shapes): a block per aggregate, 16 lanes per member row, x as the
+// cycle's products gather it (CycleArgs).  One launch where the residual
+// product and its restriction took two.  Blocks past the aggregates write
+// Q.xout (where asked for), a row per thread: rows outside every aggregate
+// have an x too.
+constexpr int kDownG = 16, kDownE = 4;
 template <typename T>
-__global__ void k_prolong(int64_t n, const int32_t* __restrict__ pmap, const T* __restrict__ xc,
-                          T* __restrict__ x, const int32_t* __restrict__ tp,
-                          const int32_t* __restrict__ stop) {
-  if (stop && stop[tp ? tp[blockIdx.x] : 0]) return;
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i < n) {
-    const int32_t I = pmap[i];
-    if (I >= 0) x[i] += xc[I];
+__global__ void __launch_bounds__(kBlock)
+k_resid_restrict(int64_t n, int64_t nc, const int64_t* __restrict__ crange, const int32_t* __restrict__ amem,
+                 const int64_t* __restrict__ rp, const int32_t* __restrict__ col,
+                 const T* __restrict__ val, const T* __restrict__ diag, const T* __restrict__ x,
+                 const T* __restrict__ b, const T* __restrict__ s, const CycleArgs<T> Q,
+                 T* __restrict__ bc, const int32_t* __restrict__ tp,
+                 const int32_t* __restrict__ stop, const int32_t* __restrict__ tpc,
+                 const int32_t* __restrict__ stopc) {
+  constexpr int NG = kBlock / kDownG;
+  __shared__ T sg[NG];
+  const int64_t I = blockIdx.x;
+  if (I >= nc) {
+    if (stop && stop[tp ? tp[I - nc] : 0]) return;
+    const int64_t i = (I - nc) * kTileRows + threadIdx.x;
+    if (i >= n) return;
+    const int32_t own[1] = {(int32_t)i};
+    T xo[1];
+    gather_x<T, SP_CYCLE, false>(own, x, b, s, Q, xo);
+    Q.xout[i] = xo[0];
+    return;
   }
-}
-
-// Chebyshev step: d = c1 d + c2 D1^-1 r (c1 = 0 on the first step), then
-// xout = xin + d (xin NULL: from zero).  xin and xout may alias.
-template <typename T>
-__global__ void k_cheb(int64_t n, T c1, T c2, const T* __restrict__ s, const T* __restrict__ r,
-                       T* __restrict__ d, const T* xin, T* xout,
-                       const int32_t* __restrict__ stop) {
-  if (stop && *stop) return;
-  int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  const T di = (c1 != T(0) ? c1 * d[i] : T(0)) + c2 * s[i] * r[i];
-  d[i] = di;
-  xout[i] = (xin ? xin[i] : T(0)) + di;
+  if (stopc && stopc[tpc ? tpc[I / kTileRows] : 0]) return;
+  const int lane = threadIdx.x & (kDownG - 1), g = threadIdx.x / kDownG;
+  const int64_t q1 = crange[I + 1];
+  T acc = 0;
+  for (int64_t q = crange[I] + g; q < q1; q += NG) {
+    const int32_t i = amem[q];
+    const int64_t k0 = rp[i], k1 = rp[i + 1];
+    T xo[1];
+    const int32_t own[1] = {i};
+    gather_x<T, SP_CYCLE, false>(own, x, b, s, Q, xo);
+    const T di = diag[i], bi = b[i];
+    T sum = 0;
+    for (int64_t base = k0 + lane; base < k1; base += kDownG * kDownE) {
+      int32_t c[kDownE];
+      T v[kDownE], xv[kDownE];
+#pragma unroll
+      for (int e = 0; e < kDownE; ++e) {
+        const int64_t k = base + e * kDownG;
+        const int64_t kc = k < k1 ? k : k1 - 1;
+        c[e] = col[kc];
+        v[e] = k < k1 ? val[kc] : T(0);
+      }
+      gather_x<T, SP_CYCLE, false>(c, x, b, s, Q, xv);
+#pragma unroll
+      for (int e = 0; e < kDownE; ++e) sum += v[e] * xv[e];
+    }
+    sum = group_sum<kDownG>(sum);
+    acc += bi - (di * xo[0] + sum);
+  }
+  if (lane == 0) sg[g] = acc;
+  __syncthreads();
+  if (threadIdx.x < NG) {
+    const T t = group_sum<NG>(sg[threadIdx.x]);
+    if (threadIdx.x == 0) bc[I] = t;
+  }
 }
 
 // ---- K-cycle -------------------------------------------------------------------
@@ -1341,38 +1371,57 @@ int amg_setup(rt_ctx* ctx, rt_matrix* A) {
   return RT_OK;
 }
 
-// Chebyshev smoothing of A x = b on level L, degree steps: from zero into x
-// (xin NULL), or from xin into x.  Each step after a start from zero costs
-// one residual product.
-template <typename T>
-static int cheb_smooth(hipStream_t st, rt_matrix* A, Level& L, int degree, const T* b,
-                       const T* xin, T* x, const int32_t* stop) {
-  using B = LevelBufs<T>;
-  const int64_t n = L.n;
-  const double hi = 1.0, lo = 0.25;   // interval of D1^-1 A to damp
-  const double theta = 0.5 * (hi + lo), delta = 0.5 * (hi - lo), sigma = theta / delta;
-  double rho = 1.0 / sigma;
-  T* r = B::r(L);
-  const T* r0 = b;   // residual of the zero start
-  if (xin) {
-    RT_CHECK((launch_spmv_level<T, SP_RESID>(st, L, B::val(L), B::diag(L), xin, b, nullptr, r,
-                                             nullptr, nullptr, nullptr, level_shape<T>(L),
-                                             nullptr, stop)));
-    r0 = r;
+// The smoother as step sizes: l1-Jacobi, one step, or Chebyshev.  Step k is
+// d = c1 d + c2 D1^-1 (b - A x), x += d, with c1 = 0 at k = 0 (from zero,
+// x = c2 D1^-1 b).
+struct Smoother {
+  int steps = 1;
+  double c1[16] = {0.0}, c2[16] = {1.0};
+  explicit Smoother(const rt_amg_opts& o) {
+    if (o.smoother != RT_SMOOTHER_CHEBYSHEV) return;
+    steps = o.smoother_degree;
+    const double hi = 1.0, lo = 0.25;   // interval of D1^-1 A to damp
+    const double theta = 0.5 * (hi + lo), delta = 0.5 * (hi - lo), sigma = theta / delta;
+    double rho = 1.0 / sigma;
+    c2[0] = 1.0 / theta;
+    for (int k = 1; k < steps; ++k) {
+      const double next = 1.0 / (2.0 * sigma - rho);
+      c1[k] = next * rho;
+      c2[k] = 2.0 * next / delta;
+      rho = next;
+    }
   }
-  hipLaunchKernelGGL(k_cheb<T>, dim3(grid_for(n)), dim3(kBlock), 0, st, n, T(0),
-                     (T)(1.0 / theta), B::sinv(L), r0, B::d(L), xin, x, stop);
-  RT_LAUNCH_CHECK();
-  for (int k = 1; k < degree; ++k) {
-    RT_CHECK((launch_spmv_level<T, SP_RESID>(st, L, B::val(L), B::diag(L), x, b, nullptr, r,
-                                             nullptr, nullptr, nullptr, level_shape<T>(L),
-                                             nullptr, stop)));
-    const double rho_next = 1.0 / (2.0 * sigma - rho);
-    hipLaunchKernelGGL(k_cheb<T>, dim3(grid_for(n)), dim3(kBlock), 0, st, n,
-                       (T)(rho_next * rho), (T)(2.0 * rho_next / delta), B::sinv(L), r, B::d(L),
-                       x, x, stop);
-    RT_LAUNCH_CHECK();
-    rho = rho_next;
+};
+
+// a product of the cycle on level L (CycleArgs)
+template <typename T>
+static int cycle_product(hipStream_t st, Level& L, const T* x, const T* b, T* y,
+                         const CycleArgs<T>& Q, const int32_t* tp, const int32_t* sk) {
+  using B = LevelBufs<T>;
+  return launch_spmv_level<T, SP_CYCLE>(st, L, B::val(L), B::diag(L), x, b, B::sinv(L), y, nullptr,
+                                        nullptr, nullptr, level_shape<T>(L), tp, sk, nullptr,
+                                        nullptr, Q);
+}
+
+// Smoothing steps first .. S.steps - 1 on level L, x (described by Q: CX_SCALED
+// stands for the step before the first one) to out; the steps between
+// alternate between tmp and out, neither of which may be x's own vector where
+// steps remain after the first of them.
+template <typename T>
+static int cycle_smooth(hipStream_t st, Level& L, const Smoother& S, int first, const T* x,
+                        const T* b, T* tmp, T* out, CycleArgs<T> Q, const int32_t* tp,
+                        const int32_t* sk) {
+  using B = LevelBufs<T>;
+  Q.step = CS_STEP;
+  Q.d = B::d(L);
+  for (int k = first; k < S.steps; ++k) {
+    T* y = (S.steps - 1 - k) % 2 == 0 ? out : tmp;
+    Q.c1 = (T)S.c1[k];
+    Q.c2 = (T)S.c2[k];
+    Q.keep_d = k + 1 < S.steps;
+    RT_CHECK(cycle_product<T>(st, L, x, b, y, Q, tp, sk));
+    x = y;
+    Q.x = CX_PLAIN;
   }
   return RT_OK;
 }
@@ -1436,22 +1485,13 @@ static int vcycle_level(rt_ctx* ctx, rt_matrix* A, size_t l, const T* b, T* out,
     }
     // four l1-Jacobi sweeps from zero (a symmetric positive-definite operator)
     T* t = B::t(L);
-    hipLaunchKernelGGL(k_scale<T>, dim3(grid_for(n)), dim3(kBlock), 0, st, n, B::sinv(L), b, t,
-                       tp, sk);
-    RT_LAUNCH_CHECK();
-    T* src = t;
-    T* dst = out;
-    for (int sweep = 0; sweep < 3; ++sweep) {
-      RT_CHECK((launch_spmv_level<T, SP_SMOOTH>(st, L, B::val(L), B::diag(L), src, b, B::sinv(L),
-                                                dst, nullptr, nullptr, nullptr,
-                                                level_shape<T>(L), tp, sk)));
-      T* tmp = src;
-      src = dst;
-      dst = tmp;
-    }
-    if (src != out)
-      RT_CHECK_HIP(hipMemcpyAsync(out, src, sizeof(T) * n, hipMemcpyDeviceToDevice, st));
-    return RT_OK;
+    CycleArgs<T> Q;
+    Q.step = CS_STEP;
+    Q.x = CX_SCALED;
+    RT_CHECK(cycle_product<T>(st, L, b, b, out, Q, tp, sk));
+    Q.x = CX_PLAIN;
+    RT_CHECK(cycle_product<T>(st, L, out, b, t, Q, tp, sk));
+    return cycle_product<T>(st, L, t, b, out, Q, tp, sk);
   }
   Level& C = A->levels[l + 1];
   const bool cskip = l + 1 < A->lvl_skip.size();
@@ -1459,23 +1499,36 @@ static int vcycle_level(rt_ctx* ctx, rt_matrix* A, size_t l, const T* b, T* out,
   const int32_t* skc = cskip ? A->lvl_skip[l + 1] : stop;
   T* t = B::t(L);
   T* r = B::r(L);
-  const bool cheb = A->amg.smoother == RT_SMOOTHER_CHEBYSHEV;
-  if (cheb) {
-    RT_CHECK(cheb_smooth<T>(st, A, L, A->amg.smoother_degree, b, nullptr, t, stop));
+  const Smoother S(A->amg);
+  // pre-smoothing from zero into t; its first step is formed in the gathers of
+  // the product that follows it (a second step, or the residual)
+  CycleArgs<T> Q;
+  Q.x = CX_SCALED;
+  Q.f = (T)S.c2[0];
+  const T* x = b;
+  if (S.steps > 1) {
+    RT_CHECK(cycle_smooth<T>(st, L, S, 1, x, b, out, t, Q, tp, sk));
+    x = t;
+    Q = CycleArgs<T>();
   } else {
-    hipLaunchKernelGGL(k_scale<T>, dim3(grid_for(n)), dim3(kBlock), 0, st, n, B::sinv(L), b, t,
-                       tp, sk);
-    RT_LAUNCH_CHECK();
+    Q.xout = t;
   }
-  RT_CHECK((launch_spmv_level<T, SP_RESID>(st, L, B::val(L), B::diag(L), t, b, nullptr, r,
-                                           nullptr, nullptr, nullptr, level_shape<T>(L),
-                                           tp, sk)));
-  if (L.smoothed)
-    hipLaunchKernelGGL((k_restrict_p<T, T>), dim3(grid_for(C.n)), dim3(kBlock), 0, st, C.n,
-                       L.pt_rp.p, L.pt_row.p, B::ptv(L), r, B::b(C), stop);
-  else
-    hipLaunchKernelGGL(k_restrict<T>, dim3(grid_for(C.n * kRestrictG)), dim3(kBlock), 0, st, C.n, L.crange.p,
-                       L.amem.p, r, B::b(C), tpc, skc);
+  const int shape = spmv_effective_shape(L, level_shape<T>(L));
+  if (!L.smoothed && !kSpmvShapes[shape].tiled && L.nnz <= kSmallNnz) {
+    static_assert(kTileRows == kBlock, "a block of the row pass is a tile of the skip flags");
+    const int64_t rowb = Q.xout ? (n + kTileRows - 1) / kTileRows : 0;
+    hipLaunchKernelGGL(k_resid_restrict<T>, dim3((unsigned)(C.n + rowb)), dim3(kBlock), 0, st, n,
+                       C.n, L.crange.p, L.amem.p, L.rp.p, L.col.p, B::val(L), B::diag(L), x, b,
+                       B::sinv(L), Q, B::b(C), tp, sk, tpc, skc);
+  } else {
+    RT_CHECK(cycle_product<T>(st, L, x, b, r, Q, tp, sk));
+    if (L.smoothed)
+      hipLaunchKernelGGL((k_restrict_p<T, T>), dim3(grid_for(C.n)), dim3(kBlock), 0, st, C.n,
+                         L.pt_rp.p, L.pt_row.p, B::ptv(L), r, B::b(C), stop);
+    else
+      hipLaunchKernelGGL(k_restrict<T>, dim3(grid_for(C.n * kRestrictG)), dim3(kBlock), 0, st, C.n,
+                         L.crange.p, L.amem.p, r, B::b(C), tpc, skc);
+  }
   RT_LAUNCH_CHECK();
   if (A->amg.cycle == 3 && l + 2 < nl)
     RT_CHECK(kcycle_correct<T>(ctx, A, l + 1, stop));
@@ -1491,18 +1544,18 @@ static int vcycle_level(rt_ctx* ctx, rt_matrix* A, size_t l, const T* b, T* out,
                        B::x(C), stop);
     RT_LAUNCH_CHECK();
   }
-  if (L.smoothed)
+  // the correction is added in the gathers of the first post-smoothing step
+  Q = CycleArgs<T>();
+  if (L.smoothed) {
     hipLaunchKernelGGL((k_prolong_p<T, T>), dim3(grid_for(n)), dim3(kBlock), 0, st, n, L.p_rp.p,
                        L.p_col.p, B::pv(L), B::x(C), t, stop);
-  else
-    hipLaunchKernelGGL(k_prolong<T>, dim3(grid_for(n)), dim3(kBlock), 0, st, n, L.pmap.p,
-                       B::x(C), t, tp, sk);
-  RT_LAUNCH_CHECK();
-  if (cheb) return cheb_smooth<T>(st, A, L, A->amg.smoother_degree, b, t, out, stop);
-  RT_CHECK((launch_spmv_level<T, SP_SMOOTH>(st, L, B::val(L), B::diag(L), t, b, B::sinv(L), out,
-                                            nullptr, nullptr, nullptr, level_shape<T>(L),
-                                            tp, sk)));
-  return RT_OK;
+    RT_LAUNCH_CHECK();
+  } else {
+    Q.x = CX_PROLONG;
+    Q.xc = B::x(C);
+    Q.pmap = L.pmap.p;
+  }
+  return cycle_smooth<T>(st, L, S, 0, t, b, r, out, Q, tp, sk);
 }
 
 template <typename T>

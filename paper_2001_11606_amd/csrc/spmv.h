@@ -32,7 +32,27 @@ enum SpmvMode {
   SP_RESID = 2,   // y = b - A x (optionally y32 = (float) y), part[block] = sum y.y;
                   // optionally pmax[block] = max_i |y_i| / (a_ii |x_i|) and
                   // w32 = 1 / (a_ii |x_i|) (see cw_term)
-  SP_SMOOTH = 3,  // y = x + s (b - A x)
+  SP_CYCLE = 3,   // a product of the multigrid cycle (CycleArgs)
+};
+
+// A product of the multigrid cycle, with the vector passes around it done in
+// its gathers and its last step: x is x[c]; f s[c] b[c], the first smoothing
+// step from zero (CX_SCALED); or x[c] + xc[pmap[c]], the prolongation of the
+// coarse correction (CX_PROLONG, pmap < 0: nothing added).  Then y = b - A x
+// (CS_RESID; xout, else NULL, receives x where it was formed here), or the
+// smoothing step d = c1 d + c2 s (b - A x), y = x + d (CS_STEP; d is written
+// where keep_d, and starts as x with CX_SCALED).  y must not be gathered from.
+enum CycleX { CX_PLAIN = 0, CX_SCALED = 1, CX_PROLONG = 2 };
+enum CycleStep { CS_RESID = 0, CS_STEP = 1 };
+template <typename T>
+struct CycleArgs {
+  int x = CX_PLAIN, step = CS_RESID;
+  T f = 1, c1 = 0, c2 = 1;
+  const T* xc = nullptr;
+  const int32_t* pmap = nullptr;
+  T* xout = nullptr;
+  T* d = nullptr;
+  bool keep_d = false;
 };
 
 // Componentwise residual measure of row i: |r_i| / (a_ii |x_i|), the relative
@@ -57,6 +77,43 @@ constexpr int kXcd = 8;
 __device__ __forceinline__ int xcd_block(int per) {
   const int p = blockIdx.x;
   return (p % kXcd) * per + p / kXcd;
+}
+
+// xv[e] = the value of x at column c[e] (0 where CHECK and c[e] < 0)
+template <typename T, int MODE, bool CHECK, int N>
+__device__ __forceinline__ void gather_x(const int32_t (&c)[N], const T* __restrict__ x,
+                                         const T* __restrict__ b, const T* __restrict__ s,
+                                         const CycleArgs<T>& Q, T (&xv)[N]) {
+  if (MODE == SP_CYCLE && Q.x == CX_SCALED) {
+#pragma unroll
+    for (int e = 0; e < N; ++e) xv[e] = !CHECK || c[e] >= 0 ? (Q.f * s[c[e]]) * b[c[e]] : T(0);
+    return;
+  }
+#pragma unroll
+  for (int e = 0; e < N; ++e) xv[e] = !CHECK || c[e] >= 0 ? x[c[e]] : T(0);
+  if (MODE == SP_CYCLE && Q.x == CX_PROLONG) {
+    int32_t I[N];
+#pragma unroll
+    for (int e = 0; e < N; ++e) I[e] = !CHECK || c[e] >= 0 ? Q.pmap[c[e]] : -1;
+#pragma unroll
+    for (int e = 0; e < N; ++e) xv[e] += I[e] >= 0 ? Q.xc[I[e]] : T(0);
+  }
+}
+
+// The last step of a cycle product for row i with A x = ax; dv: d[i] (0 where
+// c1 = 0).
+template <typename T>
+__device__ __forceinline__ void cycle_out(const CycleArgs<T>& Q, int64_t i, T xi, T ax, T bi, T si,
+                                          T dv, T* __restrict__ y) {
+  const T r = bi - ax;
+  if (Q.step == CS_RESID) {
+    y[i] = r;
+    if (Q.xout) Q.xout[i] = xi;
+    return;
+  }
+  const T dn = (Q.c1 != T(0) ? Q.c1 * (Q.x == CX_SCALED ? xi : dv) : T(0)) + (Q.c2 * si) * r;
+  if (Q.keep_d) Q.d[i] = dn;
+  y[i] = xi + dn;
 }
 
 #ifndef RT_SPMV_STAGE
@@ -90,7 +147,8 @@ k_spmv(int64_t n, int per, const int64_t* __restrict__ rp, const int32_t* __rest
        const T* __restrict__ val, const T* __restrict__ diag, const T* __restrict__ x,
        const T* __restrict__ b, const T* __restrict__ s, T* __restrict__ y,
        float* __restrict__ y32, double* __restrict__ part, const int32_t* __restrict__ tprob,
-       const int32_t* __restrict__ skip, double* __restrict__ pmax, float* __restrict__ w32) {
+       const int32_t* __restrict__ skip, double* __restrict__ pmax, float* __restrict__ w32,
+       const CycleArgs<T> Q) {
   __shared__ double red[kBlock / kWave];
   constexpr int RPB = kBlock / G;
   const int lb = xcd_block(per);
@@ -103,11 +161,17 @@ k_spmv(int64_t n, int per, const int64_t* __restrict__ rp, const int32_t* __rest
   double acc = 0.0, cwm = 0.0;
   if (i < n) {
     const int64_t k0 = rp[i], k1 = rp[i + 1];
-    const T xi = x[i];
     const T di = diag[i];
-    T bi = 0, si = 0;
-    if (MODE == SP_RESID || MODE == SP_SMOOTH) bi = b[i];
-    if (MODE == SP_SMOOTH) si = s[i];
+    T bi = 0, si = 0, dv = 0;
+    if (MODE == SP_RESID || MODE == SP_CYCLE) bi = b[i];
+    if (MODE == SP_CYCLE) {
+      si = s[i];
+      if (Q.c1 != T(0) && Q.x != CX_SCALED) dv = Q.d[i];
+    }
+    T xo[1];
+    const int32_t own[1] = {(int32_t)i};
+    gather_x<T, MODE, false>(own, x, b, s, Q, xo);
+    const T xi = xo[0];
     T sum = 0;
     for (int64_t base = k0 + lane; base < k1; base += G * ENT) {
       int32_t c[ENT];
@@ -121,8 +185,7 @@ k_spmv(int64_t n, int per, const int64_t* __restrict__ rp, const int32_t* __rest
         v[e] = k < k1 ? w : T(0);
       }
       T xv[ENT];
-#pragma unroll
-      for (int e = 0; e < ENT; ++e) xv[e] = x[c[e]];
+      gather_x<T, MODE, false>(c, x, b, s, Q, xv);
 #pragma unroll
       for (int e = 0; e < ENT; ++e) sum += v[e] * xv[e];
     }
@@ -142,7 +205,7 @@ k_spmv(int64_t n, int per, const int64_t* __restrict__ rp, const int32_t* __rest
         if (pmax) cwm = cw_term((double)r, (double)di, (double)xi);
         if (w32) w32[i] = cw_weight((double)di, (double)xi);
       } else {
-        y[i] = xi + si * (bi - ax);
+        cycle_out(Q, i, xi, ax, bi, si, dv, y);
       }
     }
   }
@@ -248,15 +311,15 @@ k_spmv_tiled(int64_t n, int per, const int64_t* __restrict__ rp, const uint16_t*
              const T* __restrict__ x, const T* __restrict__ b, const T* __restrict__ s,
              T* __restrict__ y, float* __restrict__ y32, double* __restrict__ part,
              const int32_t* __restrict__ tprob, const int32_t* __restrict__ skip,
-             double* __restrict__ pmax, float* __restrict__ w32) {
+             double* __restrict__ pmax, float* __restrict__ w32, const CycleArgs<T> Q) {
   RT_DYNAMIC_LDS(dyn_lds);
   T* xs = reinterpret_cast<T*>(dyn_lds);
   __shared__ int srp[kTileRows + 1];      // row bounds relative to the tile's aligned base
   __shared__ int64_t sbase;
   __shared__ T sy[kTileRows];
-  constexpr bool kNeedB = MODE == SP_RESID || MODE == SP_SMOOTH;
+  constexpr bool kNeedB = MODE == SP_RESID || MODE == SP_CYCLE;
   // the rows' own data, fetched while the columns are staged
-  __shared__ T sdx[(kNeedB ? 3 : 2) + (MODE == SP_SMOOTH ? 1 : 0)][kTileRows];
+  __shared__ T sdx[(kNeedB ? 3 : 2) + (MODE == SP_CYCLE ? 2 : 0)][kTileRows];
   __shared__ double red[kBlock / kWave];
   constexpr int NG = kBlock / G;   // row groups per block; UNR rows per group in flight
   static_assert(kTileRows % (NG * UNR) == 0, "tile rows must split evenly over the groups");
@@ -274,9 +337,15 @@ k_spmv_tiled(int64_t n, int per, const int64_t* __restrict__ rp, const uint16_t*
     if (tid == 0) srp[kTileRows] = (int)(rp[r0 + kTileRows < n ? r0 + kTileRows : n] - base_e);
     if (live) {
       sdx[0][tid] = diag[i];
-      sdx[1][tid] = x[i];
+      T xo[1];
+      const int32_t own[1] = {(int32_t)i};
+      gather_x<T, MODE, false>(own, x, b, s, Q, xo);
+      sdx[1][tid] = xo[0];
       if (kNeedB) sdx[2][tid] = b[i];
-      if (MODE == SP_SMOOTH) sdx[kNeedB ? 3 : 2][tid] = s[i];
+      if (MODE == SP_CYCLE) {
+        sdx[kNeedB ? 3 : 2][tid] = s[i];
+        if (Q.c1 != T(0) && Q.x != CX_SCALED) sdx[kNeedB ? 4 : 3][tid] = Q.d[i];
+      }
     }
     // columns staged kStage per thread at a time: all index loads, then all
     // gathers, so that a thread keeps kStage gathers in flight
@@ -291,8 +360,7 @@ k_spmv_tiled(int64_t n, int per, const int64_t* __restrict__ rp, const uint16_t*
         c[q] = k < cnt ? tcols[u0 + k] : -1;
       }
       T xv[kStage];
-#pragma unroll
-      for (int q = 0; q < kStage; ++q) xv[q] = c[q] >= 0 ? x[c[q]] : T(0);
+      gather_x<T, MODE, true>(c, x, b, s, Q, xv);
 #pragma unroll
       for (int q = 0; q < kStage; ++q) {
         const int k = k0 + q * kBlock + tid;
@@ -359,7 +427,7 @@ k_spmv_tiled(int64_t n, int per, const int64_t* __restrict__ rp, const uint16_t*
     const T xi = sdx[1][tid];
     T bi = 0, si = 0;
     if (kNeedB) bi = sdx[2][tid];
-    if (MODE == SP_SMOOTH) si = sdx[kNeedB ? 3 : 2][tid];
+    if (MODE == SP_CYCLE) si = sdx[kNeedB ? 3 : 2][tid];
     const T ax = di * xi + sy[tid];
     if (MODE == SP_PLAIN) {
       out_store(y + i, ax);
@@ -374,7 +442,8 @@ k_spmv_tiled(int64_t n, int per, const int64_t* __restrict__ rp, const uint16_t*
       if (pmax) cwm = cw_term((double)r, (double)di, (double)xi);
       if (w32) out_store(w32 + i, cw_weight((double)di, (double)xi));
     } else {
-      out_store(y + i, xi + si * (bi - ax));
+      const T dv = Q.c1 != T(0) && Q.x != CX_SCALED ? sdx[MODE == SP_CYCLE ? 4 : 0][tid] : T(0);
+      cycle_out(Q, i, xi, ax, bi, si, dv, y);
     }
   }
   if (MODE == SP_DOT || MODE == SP_RESID) {
@@ -419,9 +488,22 @@ inline int spmv_tiled_shape_for(int64_t max_row) {
   if (max_row <= 2 * (4 * 32 - 3)) return 14;        // (32, 2)
   return kFirstTiledShape + 4;                        // (64, 4)
 }
+// Levels with at most this many off-diagonal entries take a plain shape: a
+// tile is a long chain of waits (bounds, columns, x, entries, row sums) for
+// 256 rows, and a small level has too few tiles for the chip to hide it.  FP64
+// product, plain | tiled: 0.1M entries 3.5 | 7 us; 1.1M (32^3 particles) 9.0 |
+// 16.5; 0.7M (the level under 64^3) 7.3 | 11.5; 2.5M (under 96^3) 17.4 | 12.8;
+// 8.6M (64^3) 52 | 27; FP32 at 2.5M 13.3 | 10.8.
+constexpr int64_t kSmallNnz = (int64_t)3 << 19;
+// rows beyond 64 entries loop over 16 lanes x 6 entries: every wider plain
+// shape measured slower on the coarse levels' uneven rows
+inline int spmv_small_shape_for(int64_t max_row) {
+  return max_row <= 16 ? 0 : max_row <= 32 ? 1 : max_row <= 64 ? 2 : 4;
+}
 // the shape a product over L runs with, given the requested one (-1: default)
 inline int spmv_effective_shape(const Level& L, int shape) {
   if (shape >= 0 && shape < kNumSpmvShapes && (!kSpmvShapes[shape].tiled || L.tiled)) return shape;
+  if (L.tiled && L.nnz <= kSmallNnz && !L.pair.on) return spmv_small_shape_for(L.max_row);
   return L.tiled ? spmv_tiled_shape_for(L.max_row) : spmv_plain_shape_for(L.max_row);
 }
 
@@ -452,7 +534,7 @@ int launch_spmv_level(hipStream_t st, const Level& L, const T* val, const T* dia
                       const T* b, const T* s, T* y, float* y32, double* part, int* nparts,
                       int shape = -1, const int32_t* tprob = nullptr,
                       const int32_t* skip = nullptr, double* pmax = nullptr,
-                      float* w32 = nullptr) {
+                      float* w32 = nullptr, const CycleArgs<T>& Q = CycleArgs<T>()) {
   const int64_t n = L.n;
   shape = spmv_effective_shape(L, shape);
   const SpmvShape sh = kSpmvShapes[shape];
@@ -465,7 +547,7 @@ int launch_spmv_level(hipStream_t st, const Level& L, const T* val, const T* dia
 #define RT_SPMV_T(G_, U_)                                                                     \
   hipLaunchKernelGGL((k_spmv_tiled<T, G_, U_, MODE>), dim3(grid), dim3(kBlock), lds, st, n, per, \
                      L.rp.p, L.lcol.p, val, diag, L.tile_off.p, L.tile_cols.p, x, b, s, y, y32,  \
-                     part, tprob, skip, pmax, w32)
+                     part, tprob, skip, pmax, w32, Q)
     switch (shape) {
       case 7: RT_SPMV_T(4, 4); break;
       case 8: RT_SPMV_T(8, 4); break;
@@ -483,7 +565,7 @@ int launch_spmv_level(hipStream_t st, const Level& L, const T* val, const T* dia
   } else {
 #define RT_SPMV_S(G_, E_)                                                                       \
   hipLaunchKernelGGL((k_spmv<T, G_, E_, MODE>), dim3(grid), dim3(kBlock), 0, st, n, per, L.rp.p, \
-                     L.col.p, val, diag, x, b, s, y, y32, part, tprob, skip, pmax, w32)
+                     L.col.p, val, diag, x, b, s, y, y32, part, tprob, skip, pmax, w32, Q)
     switch (shape) {
       case 0: RT_SPMV_S(4, 4); break;
       case 1: RT_SPMV_S(4, 8); break;

@@ -1,4 +1,4 @@
-"""Kernels of the hierarchy set-up at their edges: the blocked dense inverse of
+"""Kernels of the hierarchy set-up and the cycle at their edges: the blocked dense inverse of
 the coarsest level (blocks of 32 rows) at sizes below, at and above multiples
 of 32, and the Galerkin product where a coarse row has more distinct columns
 than its LDS table takes.  A wrong coarse operator or inverse costs
@@ -73,3 +73,45 @@ def test_galerkin_rows_beyond_the_table(ctx):
             f"entries per coarse row, iterations {its}")
         long_rows += row > 400
     assert long_rows, "no hierarchy with coarse rows beyond the table's 384 columns"
+
+
+@pytest.mark.parametrize("name", ["mms2d_40", "coldpatch3d_12"])
+@pytest.mark.parametrize("degree", [0, 1, 2, 3])   # 0: l1-Jacobi, else Chebyshev
+def test_cycle_products(ctx, name, degree):
+    """The cycle's products with the vector passes in their gathers, on every
+    kind of product shape: the small levels' default (plain, restriction in the
+    residual's launch), tiled ones (restriction on its own) and a mixture; rows
+    outside every aggregate (the cold patch); a coarsest level that is smoothed
+    instead of solved (depth 2)."""
+    import torch
+    from gpu_common import _cold_patch
+    from paper_2001_11606_amd import rt
+    say(f"[cycle] {name} degree={degree}")
+    prob = synth.config1(n=40) if name == "mms2d_40" else _cold_patch(12)
+    if name == "mms2d_40":
+        prob.dt = 0.05
+        prob.set_time(prob.dt)
+    sysm = oracle_system(prob)[3]
+    b = np.random.default_rng(7).standard_normal(prob.n_interior) * sysm.A.diagonal()
+    xref = linsolve.dense(sysm.A, b)
+    opts = dict(smoother=rt.RT_SMOOTHER_CHEBYSHEV, smoother_degree=degree) if degree else {}
+    dp, nb, A = gpu_system(ctx, prob, amg=rt.amg_opts(max_levels=8, coarse_size=16, **opts))
+    levels = ctx.matrix_info(A).levels
+    assert levels > 1
+    its = {}
+    for shapes in ((-1,), (7,), (13,), (4,), (2, 12)):
+        for level in range(levels):
+            for prec in (0, 1):
+                rt.rt_matrix_set_spmv_shape(A, level, prec, shapes[level % len(shapes)])
+        for depth in (0, 2):
+            rt.rt_matrix_set_cycle_depth(A, depth)
+            for prec, tol, bar in ((0, 1e-14, 1e-12), (1, 1e-12, 1e-10)):
+                bt = torch.tensor(b, device=ctx.device)
+                xt = torch.zeros_like(bt)
+                status, st = ctx.solve(A, bt, xt, rt.solve_opts(prec, 1, tol, 4000, 1e-4, 60))
+                assert status == rt.RT_OK, rt.rt_last_error()
+                assert np.max(np.abs(xt.cpu().numpy() - xref)) / np.max(np.abs(xref)) <= bar
+                # the same cycle on every shape: rounding may move a threshold by one
+                first = its.setdefault((depth, prec), st.iterations)
+                assert abs(st.iterations - first) <= 1 + (prec == 1), (shapes, depth, prec)
+    ctx.free(A, nb)
