@@ -26,8 +26,9 @@
 // exchange buffer.  The next kernel that reads y adds, for row j, the sums that
 // earlier tiles left for it (pair_in), in ascending order of the tiles.
 //
-// Bound: HBM and the LDS adds (about one lane per clock and CU) are close to
-// each other.  ds_add_f32 runs at a third of the rate of ds_add_f64 here (2.8
+// Bound: HBM in FP64 (4.5 TB/s of entries at 2.1M Wendland rows, 602 us, and
+// 4.4 TB/s at 16.8M cubic-spline rows, 1131 us), the LDS adds in FP32 (about
+// one lane per clock and CU: 374 and 732 us).  ds_add_f32 runs at a third of the rate of ds_add_f64 here (2.8
 // ms against 1.1 ms a product of 16.8M rows), so FP32 products add in FP64 as
 // well.  Plain LDS reads and writes with one row per 32 lanes and a set per row
 // need no atomics, but took 2.6 ms (FP64) and 1.27 ms (FP32).
@@ -91,7 +92,11 @@ inline size_t pair_lds(int ncol) {
   return (sizeof(double) * kPairSets + sizeof(T)) * (size_t)ncol;
 }
 
-// U groups of a thread: steps k .. k + U - 1 of its run
+// U groups of a thread: steps k .. k + U - 1 of its run.  The loads are not
+// predicated (past the end they read the tile's last group again, which add()
+// leaves out; an empty tile reads the first group after its own): behind a
+// branch the compiler cannot count the loads in flight and waits for all of
+// them, those just issued included.
 template <typename T, int U>
 struct PairBatch {
   PairLoad<T> v[U];
@@ -99,14 +104,13 @@ struct PairBatch {
   int r[U];
   __device__ __forceinline__ void load(const T* vt, const rt_u16x4* ct, const uint8_t* rows, int k,
                                        int ng) {
+    const int last = max(ng - 1, 0);
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      const int g = (k + u) * kBlock + (int)threadIdx.x;
-      if (g < ng) {
-        v[u].load(vt, g, ng);
-        c[u] = stream_load(ct + g);
-        r[u] = stream_load(rows + g);
-      }
+      const int g = min((k + u) * kBlock + (int)threadIdx.x, last);
+      v[u].load(vt, g, ng);
+      c[u] = stream_load(ct + g);
+      r[u] = stream_load(rows + g);
     }
   }
   // cur: the row whose sum s is, xr its x
@@ -226,13 +230,14 @@ inline bool plain_shape(int shape) {
 inline bool pair_serves(const Level& L, int shape) {
   return L.pair.on && (!plain_shape(shape) || !L.csr_vals);
 }
-// Groups in work per thread without a request (as many again are loading).
-// Measured per product, 1 / 2 / 4 groups: FP64 1137 / 1183 / 1169 us and FP32
-// 758 / 763 / 743 us at 16.8M cubic-spline rows; FP64 790 / 980 / 977 us and
-// FP32 456 / 452 / 414 us at 2.1M Wendland rows (the wider FP64 batches cost
-// registers and with them waves).
-template <typename T>
-constexpr int kPairGroups = sizeof(T) == 8 ? 1 : 4;
+// Groups in work per thread without a request (as many again are loading): two,
+// one where rows are so short (a thread takes about row/8 groups) that a run
+// ends before wider batches pay.  Measured per product, 1 / 2 / 4 groups: FP64
+// 698 / 602 / 604 us and FP32 424 / 374 / 362 us at 2.1M Wendland rows (255
+// neighbours), FP64 1136 / 1131 / 1160 us and FP32 754 / 732 / 756 us at 16.8M
+// cubic-spline rows (57), FP64 14.8 / 15.7 / 18.2 us and FP32 14.0 / 14.3 /
+// 16.1 us at 262k rows of 38.
+inline int pair_groups(const Level& L) { return L.nnz >= 50 * L.n ? 2 : 1; }
 
 // Own part of A x over the level into y and the exchange sums into the
 // level's buffer (PairMode); *nparts receives the partials written (PP_DOT).
@@ -245,7 +250,7 @@ int launch_pair(hipStream_t st, const Level& L, const T* diag, const T* x, T* y,
   const int per = grid / kXcd;
   if (nparts) *nparts = grid;
   if (L.n == 0) return RT_OK;
-  const int u = shape >= 0 && shape < kNumSpmvShapes ? kSpmvShapes[shape].ent : kPairGroups<T>;
+  const int u = shape >= 0 && shape < kNumSpmvShapes ? kSpmvShapes[shape].ent : pair_groups(L);
   const size_t lds = pair_lds<T>(kTileRows + P.max_ext);
 #define RT_PAIR_U(U_)                                                                            \
   hipLaunchKernelGGL((k_pair_spmv<T, U_, MODE>), dim3(grid), dim3(kBlock), lds, st, L.n, per,     \
