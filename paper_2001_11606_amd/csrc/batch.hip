@@ -32,7 +32,9 @@
 namespace rt {
 namespace {
 
-enum { B_RZ = 0, B_PQ, B_ALPHA, B_BETA, B_RR, B_THR, B_BB, B_THR2, B_COUNT };
+// RZ0 and ACT: r.z of the running iteration and whether it runs, kept by the
+// x, r update for the p update, whose own blocks replace r.z and the flags
+enum { B_RZ = 0, B_PQ, B_ALPHA, B_BETA, B_RR, B_THR, B_BB, B_THR2, B_RZ0, B_ACT, B_COUNT };
 enum { F_INNER = 0, F_OUTER, F_ITS, F_REFINE, F_COUNT };
 enum { BOP_BB = 0, BOP_OUTER, BOP_RZ, BOP_ALPHA, BOP_BETA };
 enum { M_DE = 0, M_DEE, M_ITS, M_BAD, M_NONPHYS, M_EN, M_EN0, M_WIDTH };
@@ -69,12 +71,13 @@ struct rt_batch {
   // first and last problem with rows in it, and whether all of them stopped
   rt::DevBuf<int32_t> crng, cdone, ciota;
   int64_t nchunks = 0;
+  int64_t max_tiles = 0;                // most tiles of one problem
   rt::DevBuf<int32_t> perm;             // row -> concatenated user index (-1: padding)
   rt::DevBuf<double> pdt, pc, pa;       // per-problem dt, c, a
   rt::DevBuf<double> V, sa, f, rho, cv, m, e_prev, E_prev, Qe, QE, g;
   rt::DevBuf<double> ecur, Ecur, enew, xs, bs, r64, p64, q64;
   rt::DevBuf<float> r32, p32, q32, d32;
-  rt::DevBuf<double> partA, partB, ps, mres;
+  rt::DevBuf<double> partA, partB, partD, ps, mres;
   rt::DevBuf<int32_t> flags;            // F_COUNT x nprob
   hipStream_t cap = nullptr;            // stream the graphs are captured on
   hipGraphExec_t graph[2] = {nullptr, nullptr};   // [FP64, FP32] PCG iterations
@@ -335,6 +338,10 @@ k_b_seg(int op, int nprob, const int64_t* __restrict__ row_off, int rpb,
       }
       break;
     case BOP_BETA:
+      if (PS(B_ACT) == 0.0) {   // breakdown in this iteration
+        inner[p] = 1;
+        break;
+      }
       PS(B_RR) = a;
       PS(B_BETA) = b / PS(B_RZ);
       PS(B_RZ) = b;
@@ -364,18 +371,77 @@ k_b_init_jacobi(int64_t n, const int32_t* __restrict__ tprob, const int32_t* __r
   if (threadIdx.x == 0) part[blockIdx.x] = acc;
 }
 
+// Sums of partials [q0, q1) of pa (and pb, else NULL), by all threads of a
+// block in a fixed order; every thread receives them.
+__device__ __forceinline__ void b_sums(int64_t q0, int64_t q1, const double* __restrict__ pa,
+                                       const double* __restrict__ pb, double* red, double* a,
+                                       double* b) {
+  double va = 0.0, vb = 0.0;
+  for (int64_t q = q0 + threadIdx.x; q < q1; q += kBlock) {
+    va += pa[q];
+    if (pb) vb += pb[q];
+  }
+  va = group_sum<kWave>(va);
+  vb = group_sum<kWave>(vb);
+  constexpr int W = kBlock / kWave;
+  if ((threadIdx.x & (kWave - 1)) == 0) {
+    red[threadIdx.x / kWave] = va;
+    red[W + threadIdx.x / kWave] = vb;
+  }
+  __syncthreads();
+  *a = *b = 0.0;
+#pragma unroll
+  for (int w = 0; w < W; ++w) {
+    *a += red[w];
+    *b += red[W + w];
+  }
+  __syncthreads();
+}
+
+// Most partials of one problem that the blocks of the update kernels sum
+// themselves; a one-block launch per reduction (k_b_seg) takes 4.3 us, twice an
+// iteration, and the sum of up to this many (8 KB, from L2) under 1 us.
+constexpr int64_t kFusedSeg = 1024;
+
+// rpq: rows per partial of q.p in partD, 0: alpha is in ps (k_b_seg).
 // PAIR: q holds each tile's own part of A p, completed here (pair_in)
 template <typename T, bool PAIR>
 __global__ void __launch_bounds__(kBlock)
 k_b_update(int64_t n, int nprob, PairIn P, const T* __restrict__ qsum,
            const int32_t* __restrict__ tprob,
-           const int32_t* __restrict__ done, const double* __restrict__ ps, T* __restrict__ x,
+           const int32_t* __restrict__ done, const int64_t* __restrict__ row_off, int rpq,
+           const double* __restrict__ partD, double* __restrict__ ps, T* __restrict__ x,
            T* __restrict__ r, const T* __restrict__ p, const T* __restrict__ q,
            const T* __restrict__ dinv, double* __restrict__ partA, double* __restrict__ partB) {
-  __shared__ double red[kBlock / kWave];
+  __shared__ double red[2 * (kBlock / kWave)];
   const int pr = tprob[blockIdx.x];
-  if (done[pr]) return;
-  const T alpha = (T)ps[B_ALPHA * nprob + pr];
+  const int64_t r0 = row_off[pr];
+  const bool lead = threadIdx.x == 0 && r0 / kTileRows == blockIdx.x;   // keeps the record
+  if (done[pr]) {
+    if (lead) ps[B_ACT * nprob + pr] = 0.0;
+    return;
+  }
+  const double rz0 = ps[B_RZ * nprob + pr];
+  double al;
+  if (rpq > 0) {
+    double pq, none;
+    b_sums(r0 / rpq, row_off[pr + 1] / rpq, partD, nullptr, red, &pq, &none);
+    const bool ok = pq > 0.0 && isfinite(pq);   // else breakdown: the problem stops as it is
+    if (lead) {
+      ps[B_PQ * nprob + pr] = pq;
+      ps[B_ACT * nprob + pr] = ok ? 1.0 : 0.0;
+      ps[B_RZ0 * nprob + pr] = rz0;
+    }
+    if (!ok) return;
+    al = rz0 / pq;
+  } else {
+    al = ps[B_ALPHA * nprob + pr];
+    if (lead) {
+      ps[B_ACT * nprob + pr] = 1.0;
+      ps[B_RZ0 * nprob + pr] = rz0;
+    }
+  }
+  const T alpha = (T)al;
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   double rr = 0.0, rz = 0.0;
   if (i < n) {
@@ -395,16 +461,42 @@ k_b_update(int64_t n, int nprob, PairIn P, const T* __restrict__ qsum,
   }
 }
 
-// p = z + beta p, z = D^-1 r (Jacobi) or the given z (the V-cycle's)
+// p = z + beta p, z = D^-1 r (Jacobi) or the given z (the V-cycle's).  fused:
+// beta and the stop test are formed here from the tile partials (the first
+// tile of a problem keeps the record), else they are in ps and the flags.
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
 k_b_pupdate(int64_t n, int nprob, const int32_t* __restrict__ tprob,
-            const int32_t* __restrict__ done, const double* __restrict__ ps,
+            int32_t* __restrict__ flags, const int64_t* __restrict__ row_off, int fused,
+            const double* __restrict__ partA, const double* __restrict__ partB,
+            double* __restrict__ ps,
             const T* __restrict__ r, const T* __restrict__ dinv, const T* __restrict__ z,
             T* __restrict__ p) {
+  __shared__ double red[2 * (kBlock / kWave)];
   const int pr = tprob[blockIdx.x];
-  if (done[pr]) return;
-  const T beta = (T)ps[B_BETA * nprob + pr];
+  double be;
+  if (fused) {
+    const int64_t t0 = row_off[pr] / kTileRows;
+    const bool lead = threadIdx.x == 0 && t0 == blockIdx.x;
+    if (ps[B_ACT * nprob + pr] == 0.0) {   // stopped before, or a breakdown
+      if (lead) flags[F_INNER * nprob + pr] = 1;
+      return;
+    }
+    double rr, rz;
+    b_sums(t0, row_off[pr + 1] / kTileRows, partA, partB, red, &rr, &rz);
+    be = rz / ps[B_RZ0 * nprob + pr];
+    if (lead) {
+      ps[B_RR * nprob + pr] = rr;
+      ps[B_BETA * nprob + pr] = be;
+      ps[B_RZ * nprob + pr] = rz;
+      flags[F_ITS * nprob + pr] += 1;
+      if (!(rr > ps[B_THR * nprob + pr]) || !isfinite(rr)) flags[F_INNER * nprob + pr] = 1;
+    }
+  } else {
+    if (flags[F_INNER * nprob + pr]) return;
+    be = ps[B_BETA * nprob + pr];
+  }
+  const T beta = (T)be;
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (i < n) p[i] = (z ? z[i] : dinv[i] * r[i]) + beta * p[i];
 }
@@ -600,20 +692,25 @@ int b_iteration(rt_ctx* ctx, hipStream_t st, rt_batch* B, T* x, T* r, bool amg =
   const bool pair = pair_serves(L, shape);
   const int rpb = pair ? kTileRows : spmv_rows_per_block(L, shape);
   if (pair)
-    RT_CHECK((launch_pair<T, PP_DOT>(st, L, S::diag(L), S::p(B), S::q(B), B->partA.p, nullptr,
+    RT_CHECK((launch_pair<T, PP_DOT>(st, L, S::diag(L), S::p(B), S::q(B), B->partD.p, nullptr,
                                      shape, B->tprob.p, done)));
   else
     RT_CHECK((launch_spmv_level<T, SP_DOT>(st, L, S::val(L), S::diag(L), S::p(B), nullptr, nullptr,
-                                           S::q(B), nullptr, B->partA.p, nullptr, shape,
+                                           S::q(B), nullptr, B->partD.p, nullptr, shape,
                                            B->tprob.p, done)));
-  hipLaunchKernelGGL(k_b_seg, dim3(B->nprob), dim3(kBlock), 0, st, (int)BOP_ALPHA, B->nprob,
-                     B->d_row_off.p, rpb, B->partA.p, (const double*)nullptr, B->ps.p,
-                     B->flags.p, 0.0, 0, 0.0);
-  RT_LAUNCH_CHECK();
+  const bool fa = B->max_tiles * (kTileRows / rpb) <= kFusedSeg;
+  const bool fb = B->max_tiles <= kFusedSeg;
+  if (!fa) {
+    hipLaunchKernelGGL(k_b_seg, dim3(B->nprob), dim3(kBlock), 0, st, (int)BOP_ALPHA, B->nprob,
+                       B->d_row_off.p, rpb, B->partD.p, (const double*)nullptr, B->ps.p,
+                       B->flags.p, 0.0, 0, 0.0);
+    RT_LAUNCH_CHECK();
+  }
   const unsigned nt = (unsigned)B->ntiles;
 #define RT_B_UPDATE(PAIR_)                                                                        \
   hipLaunchKernelGGL((k_b_update<T, PAIR_>), dim3(nt), dim3(kBlock), 0, st, B->n, B->nprob,        \
-                     L.pair.in(), PairSel<T>::sum(L.pair), B->tprob.p, done, B->ps.p, x, r,        \
+                     L.pair.in(), PairSel<T>::sum(L.pair), B->tprob.p, done, B->d_row_off.p,       \
+                     fa ? rpb : 0, B->partD.p, B->ps.p, x, r,                                      \
                      S::p(B), S::q(B), amg ? nullptr : S::dinv(L), B->partA.p, B->partB.p)
   if (pair) RT_B_UPDATE(true);
   else RT_B_UPDATE(false);
@@ -626,12 +723,15 @@ int b_iteration(rt_ctx* ctx, hipStream_t st, rt_batch* B, T* x, T* r, bool amg =
                        S::z(B), (T*)nullptr, B->partB.p);
     RT_LAUNCH_CHECK();
   }
-  hipLaunchKernelGGL(k_b_seg, dim3(B->nprob), dim3(kBlock), 0, st, (int)BOP_BETA, B->nprob,
-                     B->d_row_off.p, kTileRows, B->partA.p, B->partB.p, B->ps.p, B->flags.p, 0.0,
-                     0, 0.0);
-  RT_LAUNCH_CHECK();
+  if (!fb) {
+    hipLaunchKernelGGL(k_b_seg, dim3(B->nprob), dim3(kBlock), 0, st, (int)BOP_BETA, B->nprob,
+                       B->d_row_off.p, kTileRows, B->partA.p, B->partB.p, B->ps.p, B->flags.p, 0.0,
+                       0, 0.0);
+    RT_LAUNCH_CHECK();
+  }
   hipLaunchKernelGGL((k_b_pupdate<T>), dim3(nt), dim3(kBlock), 0, st, B->n, B->nprob, B->tprob.p,
-                     done, B->ps.p, r, S::dinv(L), amg ? S::z(B) : (const T*)nullptr, S::p(B));
+                     B->flags.p, B->d_row_off.p, fb ? 1 : 0, B->partA.p, B->partB.p, B->ps.p, r,
+                     S::dinv(L), amg ? S::z(B) : (const T*)nullptr, S::p(B));
   RT_LAUNCH_CHECK();
   return RT_OK;
 }
@@ -1081,6 +1181,7 @@ int rt_batch_create(rt_ctx* ctx, int nprob, rt_matrix* const* mats, rt_batch** o
   RT_B(B->d_row_off.reserve(nprob + 1));
   RT_B(B->partA.reserve(max_partials(n)));
   RT_B(B->partB.reserve(max_partials(n)));
+  RT_B(B->partD.reserve(max_partials(n)));
   RT_B(B->ps.reserve((size_t)B_COUNT * nprob));
   RT_B(B->flags.reserve((size_t)F_COUNT * nprob));
   RT_B(B->mres.reserve(std::max<int64_t>((int64_t)M_WIDTH * B->ntiles, (int64_t)M_WIDTH * nprob)));
@@ -1092,6 +1193,7 @@ int rt_batch_create(rt_ctx* ctx, int nprob, rt_matrix* const* mats, rt_batch** o
   for (int p = 0; p < nprob; ++p) {
     for (int64_t t = B->row_off[p] / kTileRows; t < B->row_off[p + 1] / kTileRows; ++t)
       tp[t] = p;
+    B->max_tiles = std::max(B->max_tiles, (B->row_off[p + 1] - B->row_off[p]) / kTileRows);
     hdt[p] = mats[p]->dt;
     hc[p] = mats[p]->c;
     ha[p] = mats[p]->a;

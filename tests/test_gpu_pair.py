@@ -187,3 +187,47 @@ def test_batch_of_pair_form_matrices(ctx, mixed_forms):
                 o += ref.size
                 assert np.max(np.abs(got - ref)) / np.max(np.abs(ref)) <= bar, (q, prec, shape)
     rt.rt_batch_free(B)
+
+
+@pytest.mark.parametrize("n,shape", [(65, -1), (66, 4), (33, 4), (20, -1)])
+@pytest.mark.parametrize("precond", [0, 1])
+def test_batch_reductions(ctx, n, shape, precond):
+    """Problems with more partials than the batch's update kernels sum
+    themselves (1024 tiles; a plain shape has 16 rows per partial), beside a
+    small one that stops first and a zero right-hand side (stops at once).  Every
+    problem against its own solve: x to the sum of both solves' bars."""
+    import torch
+    from paper_2001_11606_amd import rt
+    say(f"[batch sums] n={n} shape={shape} precond={precond}")
+    levels = 8 if precond else 1
+    probs = [synth.config3(n=n), synth.config4(n=9), synth.config3(n=12)]
+    built = [gpu_system(ctx, p, amg=rt.amg_opts(max_levels=levels, build_fp32=1)) for p in probs]
+    mats = [A for _, _, A in built]
+    rng = np.random.default_rng(11)
+    bs = [torch.tensor(rng.standard_normal(p.n_interior), device=ctx.device) for p in probs]
+    bs[2].zero_()
+    B = rt.rt_batch_create(ctx.handle, mats)
+    b = torch.cat(bs)
+    for prec, tol, bar in ((0, 1e-13, 1e-11), (1, 1e-11, 1e-9)):
+        opts = rt.solve_opts(prec, precond, tol, 4000, 1e-4, 60)
+        refs = []
+        for A, bp in zip(mats, bs):
+            x = torch.zeros_like(bp)
+            assert ctx.solve(A, bp, x, opts)[0] == rt.RT_OK
+            refs.append(x)
+        for prod in (0, 1, 2):
+            rt.rt_batch_set_spmv_shape(B, prod, shape)
+        runs = []
+        for graph in (0, 3, 0):
+            x = torch.zeros_like(b)
+            s, stats = rt.rt_batch_solve(ctx.handle, B, len(probs), b.data_ptr(), x.data_ptr(),
+                                         opts, graph)
+            assert s == rt.RT_OK
+            for got, ref in zip(x.split([r.numel() for r in refs]), refs):
+                scale = max(float(ref.abs().max()), 1e-300)
+                assert float((got - ref).abs().max()) <= 2 * bar * scale
+            runs.append(x)
+        assert torch.equal(runs[0], runs[2])   # the same bits
+        assert stats[2].iterations == 0 and stats[0].iterations > 0
+    rt.rt_batch_free(B)
+    ctx.free(*[h for _, nb, A in built for h in (A, nb)])
