@@ -376,13 +376,17 @@ k_b_init_jacobi(int64_t n, const int32_t* __restrict__ tprob, const int32_t* __r
 __device__ __forceinline__ void b_sums(int64_t q0, int64_t q1, const double* __restrict__ pa,
                                        const double* __restrict__ pb, double* red, double* a,
                                        double* b) {
-  double va = 0.0, vb = 0.0;
-  for (int64_t q = q0 + threadIdx.x; q < q1; q += kBlock) {
-    va += pa[q];
-    if (pb) vb += pb[q];
+  double a4[4] = {0.0, 0.0, 0.0, 0.0}, b4[4] = {0.0, 0.0, 0.0, 0.0};
+  for (int64_t q = q0 + threadIdx.x; q < q1; q += 4 * kBlock) {
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      const int64_t k = q + u * kBlock;
+      a4[u] += k < q1 ? pa[k] : 0.0;
+      if (pb) b4[u] += k < q1 ? pb[k] : 0.0;
+    }
   }
-  va = group_sum<kWave>(va);
-  vb = group_sum<kWave>(vb);
+  const double va = group_sum<kWave>((a4[0] + a4[1]) + (a4[2] + a4[3]));
+  const double vb = pb ? group_sum<kWave>((b4[0] + b4[1]) + (b4[2] + b4[3])) : 0.0;
   constexpr int W = kBlock / kWave;
   if ((threadIdx.x & (kWave - 1)) == 0) {
     red[threadIdx.x / kWave] = va;
@@ -399,9 +403,10 @@ __device__ __forceinline__ void b_sums(int64_t q0, int64_t q1, const double* __r
 }
 
 // Most partials of one problem that the blocks of the update kernels sum
-// themselves; a one-block launch per reduction (k_b_seg) takes 4.3 us, twice an
-// iteration, and the sum of up to this many (8 KB, from L2) under 1 us.
-constexpr int64_t kFusedSeg = 1024;
+// themselves (16 KB, from L2).  A launch per reduction (k_b_seg, 4.3 us, twice an
+// iteration) instead: 4 problems of up to 13.8k rows 2.95 | 3.14 ms a pass, 24 of
+// up to 456k rows (1783 tiles) 25.2 | 26.6 ms.
+constexpr int64_t kFusedSeg = 2048;
 
 // rpq: rows per partial of q.p in partD, 0: alpha is in ps (k_b_seg).
 // PAIR: q holds each tile's own part of A p, completed here (pair_in)

@@ -189,11 +189,11 @@ def test_batch_of_pair_form_matrices(ctx, mixed_forms):
     rt.rt_batch_free(B)
 
 
-@pytest.mark.parametrize("n,shape", [(65, -1), (66, 4), (33, 4), (20, -1)])
+@pytest.mark.parametrize("n,shape", [(82, -1), (82, 4), (33, 4), (20, -1)])
 @pytest.mark.parametrize("precond", [0, 1])
 def test_batch_reductions(ctx, n, shape, precond):
     """Problems with more partials than the batch's update kernels sum
-    themselves (1024 tiles; a plain shape has 16 rows per partial), beside a
+    themselves (2048 tiles; a plain shape has 16 rows per partial), beside a
     small one that stops first and a zero right-hand side (stops at once).  Every
     problem against its own solve: x to the sum of both solves' bars."""
     import torch
