@@ -225,16 +225,21 @@ k_start(int npr, const double* __restrict__ pr, const double* __restrict__ pc, i
 }
 
 // Streaming vector kernels: kVec elements per thread (coalesced per element
-// slot), one partial per block, no grid-stride loop.
+// slot), one up to kVecOne rows, where four leave most of the chip idle; one
+// partial per block, no grid-stride loop.  Beyond, the partials that every
+// block combines cost more than the idle units: steps with one | four elements
+// of 27k rows 550 | 600 us, 512k 6.8 | 6.3 ms, 1M 12.7 | 10.3 ms; at 262k
+// 1.32 | 1.35 ms (FP64, 255 neighbours) and 4.20 | 4.15 ms (FP32, 38).
 constexpr int kVec = 4;
+constexpr int64_t kVecOne = (int64_t)1 << 17;
+__host__ __device__ inline int vec_per_thread(int64_t n) { return n <= kVecOne ? 1 : kVec; }
 inline int vec_blocks(int64_t n) {
-  const int64_t per_block = (int64_t)kBlock * kVec;
+  const int64_t per_block = (int64_t)kBlock * vec_per_thread(n);
   return (int)std::max<int64_t>(1, (n + per_block - 1) / per_block);
 }
 #define RT_VEC_LOOP(i)                                                                  \
-  for (int _u = 0; _u < kVec; ++_u)                                                     \
-    for (int64_t i = (int64_t)blockIdx.x * kBlock * kVec + (int64_t)_u * kBlock + threadIdx.x; \
-         i < n; i = n)
+  for (int _u = 0, _e = vec_per_thread(n); _u < _e; ++_u)                               \
+    for (int64_t i = ((int64_t)blockIdx.x * _e + _u) * kBlock + threadIdx.x; i < n; i = n)
 
 // second reduction level: nb2 blocks each sum a contiguous chunk of pa (and pb)
 __global__ void __launch_bounds__(kBlock)
@@ -324,8 +329,13 @@ k_dot(int64_t n, const T* __restrict__ a, const T* __restrict__ b, double* __res
 // w = dinv (CW_X: |r_i| w_i / |x_i| of the updated x) or fixed weights (CW_W)
 // PAIR: q holds each tile's own part of A p, completed here (pair_in)
 // npq > 0: alpha is formed here from the product's npq partials (block 0
-// keeps the record), else it is s[S_ALPHA]
-template <typename T, bool JAC, int CW, bool PAIR>
+// keeps the record), else it is s[S_ALPHA].
+// With one element per thread all that does not wait for alpha is requested
+// before the partials are combined (16.4k FP64 rows 9.7 -> 5.5 us).  With four
+// the waves in flight hide the waits, and holding four rows' loads costs
+// registers and with them waves (FP32, 16.8M rows: 109 us on average as it is,
+// 138 us with all loads first).
+template <typename T, bool JAC, int CW, bool PAIR, int E>
 __global__ void __launch_bounds__(kBlock)
 k_update(int64_t n, PairIn P, const T* __restrict__ qsum, int npq, const double* __restrict__ pq,
          int slot, double* __restrict__ s, T* __restrict__ x, T* __restrict__ r,
@@ -334,6 +344,23 @@ k_update(int64_t n, PairIn P, const T* __restrict__ qsum, int npq, const double*
          double* __restrict__ partC, int32_t* __restrict__ stop) {
   __shared__ double red[kBlock / kWave];
   if (*stop) return;
+  struct Row {
+    T x, p, q, r, dinv, w;
+  };
+  auto load = [&](int64_t i) {
+    Row v;
+    v.x = x[i];
+    v.p = p[i];
+    v.q = q[i];
+    v.r = r[i];
+    v.dinv = JAC ? dinv[i] : T(0);
+    v.w = CW != CW_NONE ? w[i] : T(0);
+    if (PAIR) v.q += pair_in<T>(P, i, qsum);
+    return v;
+  };
+  const int64_t i0 = (int64_t)blockIdx.x * kBlock * E + threadIdx.x;
+  Row first{};
+  if (E == 1 && i0 < n) first = load(i0);
   double al = 0.0;
   if (npq > 0) {
     const Combined v = combine(npq, pq, nullptr, nullptr, red);
@@ -343,21 +370,22 @@ k_update(int64_t n, PairIn P, const T* __restrict__ qsum, int npq, const double*
   }
   const T alpha = (T)al;
   double rr = 0.0, rz = 0.0, cw = 0.0;
-  RT_VEC_LOOP(i) {
-    const T xi = x[i] + alpha * p[i];
+  for (int e = 0; e < E; ++e) {
+    const int64_t i = i0 + e * kBlock;
+    if (i >= n) break;
+    const Row v = E == 1 ? first : load(i);
+    const T xi = v.x + alpha * v.p;
     x[i] = xi;
-    T qi = q[i];
-    if (PAIR) qi += pair_in<T>(P, i, qsum);
-    const T ri = r[i] - alpha * qi;
+    const T ri = v.r - alpha * v.q;
     r[i] = ri;
     rr += (double)ri * (double)ri;
-    if (JAC) rz += (double)ri * (double)(dinv[i] * ri);
+    if (JAC) rz += (double)ri * (double)(v.dinv * ri);
     if (CW == CW_X) {
       const double ax = fabs((double)xi);
-      const double t = fabs((double)ri) * (double)w[i];
+      const double t = fabs((double)ri) * (double)v.w;
       cw = fmax(cw, ax > 0.0 ? t / ax : (ri == T(0) ? 0.0 : INFINITY));
     } else if (CW == CW_W) {
-      cw = fmax(cw, fabs((double)ri) * (double)w[i]);
+      cw = fmax(cw, fabs((double)ri) * (double)v.w);
     }
   }
   rr = block_sum(rr, red);
@@ -373,7 +401,7 @@ k_update(int64_t n, PairIn P, const T* __restrict__ qsum, int npq, const double*
 // p = z + beta p, with z = dinv r (Jacobi) or the preconditioned vector
 // np > 0: beta is formed here from the np partials of r.r, r.z and, with pc,
 // the componentwise measure (block 0 keeps the record), else it is s[S_BETA]
-template <typename T, bool JAC>
+template <typename T, bool JAC, int E>
 __global__ void __launch_bounds__(kBlock)
 k_pupdate(int64_t n, int np, const double* __restrict__ pa, const double* __restrict__ pb,
           const double* __restrict__ pc, int slot, double* __restrict__ s,
@@ -381,6 +409,15 @@ k_pupdate(int64_t n, int np, const double* __restrict__ pa, const double* __rest
           T* __restrict__ p, int32_t* __restrict__ stop) {
   __shared__ double red[kBlock / kWave];
   if (*stop) return;
+  const int64_t i0 = (int64_t)blockIdx.x * kBlock * E + threadIdx.x;
+  T zv[E], dv[E], pv[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {   // in flight while the partials are combined
+    const int64_t i = i0 + e * kBlock < n ? i0 + e * kBlock : n - 1;
+    zv[e] = JAC ? r[i] : z[i];
+    dv[e] = JAC ? dinv[i] : T(1);
+    pv[e] = p[i];
+  }
   double be = 0.0;
   if (np > 0) {
     const Combined v = combine(np, pa, pb, pc, red);
@@ -389,9 +426,10 @@ k_pupdate(int64_t n, int np, const double* __restrict__ pa, const double* __rest
     be = s[S_BETA];
   }
   const T beta = (T)be;
-  RT_VEC_LOOP(i) {
-    const T zi = JAC ? dinv[i] * r[i] : z[i];
-    p[i] = zi + beta * p[i];
+#pragma unroll
+  for (int e = 0; e < E; ++e) {
+    if (i0 + e * kBlock >= n) break;
+    p[i0 + e * kBlock] = (JAC ? dv[e] * zv[e] : zv[e]) + beta * pv[e];
   }
 }
 
@@ -567,12 +605,16 @@ int pupdate(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, int np, const do
   using S = Sel<T>;
   const Level& L = A->levels[0];
   const int gv = vec_blocks(L.n);
-  if (amg)
-    hipLaunchKernelGGL((k_pupdate<T, false>), dim3(gv), dim3(kBlock), 0, ctx->stream, L.n, np,
-                       W.partA, W.partB, pc, slot, W.scal, r, nullptr, S::z(W), S::p(W), W.stop);
-  else
-    hipLaunchKernelGGL((k_pupdate<T, true>), dim3(gv), dim3(kBlock), 0, ctx->stream, L.n, np,
-                       W.partA, W.partB, pc, slot, W.scal, r, S::dinv(L), nullptr, S::p(W), W.stop);
+#define RT_PUPD(JAC_, E_)                                                                        \
+  hipLaunchKernelGGL((k_pupdate<T, JAC_, E_>), dim3(gv), dim3(kBlock), 0, ctx->stream, L.n, np,   \
+                     W.partA, W.partB, pc, slot, W.scal, r, JAC_ ? S::dinv(L) : nullptr,          \
+                     JAC_ ? nullptr : S::z(W), S::p(W), W.stop)
+  const bool one = vec_per_thread(L.n) == 1;
+  if (amg && one) RT_PUPD(false, 1);
+  else if (amg) RT_PUPD(false, kVec);
+  else if (one) RT_PUPD(true, 1);
+  else RT_PUPD(true, kVec);
+#undef RT_PUPD
   RT_LAUNCH_CHECK();
   return RT_OK;
 }
@@ -609,15 +651,18 @@ int pcg_iteration(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r
   if (!fa) RT_CHECK(finalize(ctx, W, FIN_ALPHA, nbk, W.partD, nullptr, nullptr, slot));
   const T* w = static_cast<const T*>(cw.w);
   double* pc = cw.mode == CW_NONE ? nullptr : W.partC;
-#define RT_UPD1(JAC_, CW_, PAIR_)                                                               \
-  hipLaunchKernelGGL((k_update<T, JAC_, CW_, PAIR_>), dim3(gv), dim3(kBlock), 0, st, n,          \
+#define RT_UPD1(JAC_, CW_, PAIR_, E_)                                                           \
+  hipLaunchKernelGGL((k_update<T, JAC_, CW_, PAIR_, E_>), dim3(gv), dim3(kBlock), 0, st, n,      \
                      L.pair.in(), PairSel<T>::sum(L.pair), fa ? nbk : 0, W.partD, slot, W.scal, x, \
                      r, p, q,                                                                    \
                      JAC_ ? S::dinv(L) : nullptr, w, W.partA, JAC_ ? W.partB : nullptr, pc, stop)
-#define RT_UPD(JAC_, CW_)                   \
-  do {                                      \
-    if (pair) RT_UPD1(JAC_, CW_, true);     \
-    else RT_UPD1(JAC_, CW_, false);         \
+  const bool one = vec_per_thread(n) == 1;
+#define RT_UPD(JAC_, CW_)                            \
+  do {                                               \
+    if (pair && one) RT_UPD1(JAC_, CW_, true, 1);    \
+    else if (pair) RT_UPD1(JAC_, CW_, true, kVec);   \
+    else if (one) RT_UPD1(JAC_, CW_, false, 1);      \
+    else RT_UPD1(JAC_, CW_, false, kVec);            \
   } while (0)
   if (amg) {
     if (cw.mode == CW_X) RT_UPD(false, CW_X);
