@@ -265,6 +265,21 @@ __global__ void k_agg_members(int64_t n, const int32_t* __restrict__ pmap,
   if (I >= 0) amem[atomicAdd(&cur[I], 1)] = (int32_t)i;
 }
 
+// the members of every aggregate in ascending order (tmp: in any order): each
+// counts the smaller ones of its list
+__global__ void k_agg_rank(int64_t nmem, const int64_t* __restrict__ crange,
+                           const int32_t* __restrict__ pmap, const int32_t* __restrict__ tmp,
+                           int32_t* __restrict__ amem) {
+  const int64_t d = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (d >= nmem) return;
+  const int32_t i = tmp[d];
+  const int64_t a = crange[pmap[i]], b = crange[pmap[i] + 1];
+  int64_t rank = 0;
+#pragma unroll 4
+  for (int64_t j = a; j < b; ++j) rank += tmp[j] < i;
+  amem[a + rank] = i;
+}
+
 __global__ void k_i64_to_i32(int64_t n, const int64_t* __restrict__ a, int32_t* __restrict__ b) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i < n) b[i] = (int32_t)a[i];
@@ -1120,10 +1135,14 @@ int aggregate(rt_ctx* ctx, Level& L, int shift, double theta, DevBuf<uint64_t>& 
   RT_CHECK(L.amem.reserve(std::max<int64_t>(nmem, 1)));
   hipLaunchKernelGGL(k_i64_to_i32, dim3(grid_for(nc)), dim3(kBlock), 0, st, nc, L.crange.p,
                      cnt.p);   // cnt = next free slot per aggregate
+  DevBuf<int32_t> tmp;
+  RT_CHECK(tmp.reserve(std::max<int64_t>(nmem, 1)));
   hipLaunchKernelGGL(k_agg_members, dim3(grid_for(n)), dim3(kBlock), 0, st, n, L.pmap.p, cnt.p,
-                     L.amem.p);
+                     tmp.p);
+  if (nmem > 0)
+    hipLaunchKernelGGL(k_agg_rank, dim3(grid_for(nmem)), dim3(kBlock), 0, st, nmem, L.crange.p,
+                       L.pmap.p, tmp.p, L.amem.p);
   RT_LAUNCH_CHECK();
-  RT_CHECK((row_sort<int32_t, int32_t>(ctx, L.crange.p, L.amem.p, nullptr, nc)));
   return RT_OK;
 }
 

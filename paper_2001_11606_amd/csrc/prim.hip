@@ -147,12 +147,31 @@ __global__ void k_bucket_scatter(int64_t n, const uint64_t* __restrict__ kin,
   vout[d] = vin[i];
 }
 
+// The values of a bucket (vin, in any order) in ascending order: every item
+// counts the smaller ones of its bucket, whose slots end at cend[key].  One
+// thread sorting a bucket in place by insertion, which this replaces, is one
+// chain of loads and stores through memory: 1.19 ms for buckets of up to 150
+// items, whatever n (262k or 2.1M); 462 us at 389k Wendland particles, 9 us so.
+__global__ void k_bucket_rank(int64_t n, const uint64_t* __restrict__ keys,
+                              const int32_t* __restrict__ vin, const int32_t* __restrict__ cnt,
+                              const int32_t* __restrict__ cend, int32_t* __restrict__ vout) {
+  const int64_t d = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (d >= n) return;
+  const uint64_t k = keys[d];
+  const int32_t b = cend[k], a = b - cnt[k], v = vin[d];
+  int32_t rank = 0;
+#pragma unroll 4
+  for (int32_t j = a; j < b; ++j) {
+    const int32_t o = vin[j];
+    rank += o < v || (o == v && j < (int32_t)d);
+  }
+  vout[a + rank] = v;
+}
+
 __global__ void k_fill_i32(int64_t n, int32_t* __restrict__ p, int32_t v) {
   const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
 }
-
-__global__ void k_set_last(int64_t* p, int64_t v) { *p = v; }
 
 // per-block maximum of non-negative values (grid-stride)
 template <typename T>
@@ -194,11 +213,10 @@ int bucket_sort_pairs(rt_ctx* ctx, const uint64_t* kin, uint64_t* kout, const in
   if (key_bits > kBucketSortMaxBits || n <= 0 || n >= ((int64_t)1 << 31)) return RT_OK;
   hipStream_t st = ctx->stream;
   const int64_t nb = (int64_t)1 << key_bits;
-  DevBuf<int32_t> cnt, cur;
-  DevBuf<int64_t> off;
+  DevBuf<int32_t> cnt, cur, vtmp;
   RT_CHECK(cnt.reserve(nb));
   RT_CHECK(cur.reserve(nb));
-  RT_CHECK(off.reserve(nb + 1));
+  RT_CHECK(vtmp.reserve(n));
   hipLaunchKernelGGL(k_fill_i32, dim3(grid_for(nb)), dim3(kBlock), 0, st, nb, cnt.p, 0);
   RT_LAUNCH_CHECK();
   hipLaunchKernelGGL(k_bucket_count, dim3(grid_for(n)), dim3(kBlock), 0, st, n, kin, cnt.p);
@@ -207,14 +225,13 @@ int bucket_sort_pairs(rt_ctx* ctx, const uint64_t* kin, uint64_t* kout, const in
   RT_CHECK(max_nonneg<int32_t>(ctx, cnt.p, nb, &maxb));
   if (maxb > kBucketSortMaxBucket) return RT_OK;   // long buckets: the split sort does better
   RT_CHECK((scan<int32_t, int32_t>(ctx, cnt.p, cur.p, nb, false)));
-  RT_CHECK((scan<int32_t, int64_t>(ctx, cnt.p, off.p, nb, false)));
   hipLaunchKernelGGL(k_bucket_scatter, dim3(grid_for(n)), dim3(kBlock), 0, st, n, kin, vin, cur.p,
-                     kout, vout);
-  RT_LAUNCH_CHECK();
-  hipLaunchKernelGGL(k_set_last, dim3(1), dim3(1), 0, st, off.p + nb, n);
+                     kout, vtmp.p);
   RT_LAUNCH_CHECK();
   // the scatter order within a bucket is arbitrary: restore the input order
-  RT_CHECK((row_sort<int32_t, int32_t>(ctx, off.p, vout, nullptr, nb)));
+  hipLaunchKernelGGL(k_bucket_rank, dim3(grid_for(n)), dim3(kBlock), 0, st, n, kout, vtmp.p, cnt.p,
+                     cur.p, vout);
+  RT_LAUNCH_CHECK();
   RT_CHECK_HIP(hipStreamSynchronize(st));   // the temporaries are freed on return
   *done = true;
   return RT_OK;
