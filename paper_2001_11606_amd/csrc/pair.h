@@ -146,7 +146,7 @@ k_pair_spmv(int64_t n, int per, int64_t ntiles, PairArgs A, const T* __restrict_
             const int32_t* __restrict__ skip) {
   RT_DYNAMIC_LDS(dyn_lds);
   __shared__ double red[kBlock / kWave];
-  const int t = xcd_block(per);
+  const int t = xcd_block(per, tprob != nullptr);
   const int tid = threadIdx.x;
   if (t >= ntiles) {   // grids are padded to a multiple of the XCD count
     if (MODE == PP_DOT && tid == 0 && part) part[t] = 0.0;
@@ -246,7 +246,7 @@ int launch_pair(hipStream_t st, const Level& L, const T* diag, const T* x, T* y,
                 int* nparts, int shape = -1, const int32_t* tprob = nullptr,
                 const int32_t* skip = nullptr) {
   const PairForm& P = L.pair;
-  const int grid = spmv_blocks_rows(L.n, kTileRows);
+  const int grid = spmv_blocks_rows(L.n, kTileRows, tprob != nullptr);
   const int per = grid / kXcd;
   if (nparts) *nparts = grid;
   if (L.n == 0) return RT_OK;
