@@ -128,9 +128,11 @@ k_limiter(int64_t nin, int kernel, int limiter, double lk, double c,
       const double dy = periodic_disp(yi - pj[e].y, box, 1);
       const double dz = DIM == 3 ? periodic_disp(zi - pj[e].z, box, 2) : 0.0;
       const double r = sqrt(dx * dx + dy * dy + dz * dz);
-      // grad_i W_ij = 1/2 [W'(r,h_i) + W'(r,h_j)] x_ij / r
+      // grad_i W_ij = 1/2 [W'(r,h_i) + W'(r,h_j)] x_ij / r; equal smoothing lengths
+      // give equal derivatives
+      const double wi = sph_dwdr<DIM>(r, hi, kernel);
       const double w = vj[e] * (ej[e] - Ei) * 0.5 *
-                       (sph_dwdr<DIM>(r, hi, kernel) + sph_dwdr<DIM>(r, pj[e].h, kernel)) / r;
+                       (wi + (pj[e].h == hi ? wi : sph_dwdr<DIM>(r, pj[e].h, kernel))) / r;
       gx += w * dx;
       gy += w * dy;
       gz += w * dz;
