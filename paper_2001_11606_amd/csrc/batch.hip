@@ -427,6 +427,17 @@ k_b_update(int64_t n, int nprob, PairIn P, const T* __restrict__ qsum,
     return;
   }
   const double rz0 = ps[B_RZ * nprob + pr];
+  // the row's data, in flight while the partials are summed
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  T xi = 0, pi = 0, qi = 0, ri = 0, di = 0;
+  if (i < n) {
+    xi = x[i];
+    pi = p[i];
+    qi = q[i];
+    ri = r[i];
+    if (dinv) di = dinv[i];
+    if (PAIR) qi += pair_in<T>(P, i, qsum);
+  }
   double al;
   if (rpq > 0) {
     double pq, none;
@@ -447,16 +458,13 @@ k_b_update(int64_t n, int nprob, PairIn P, const T* __restrict__ qsum,
     }
   }
   const T alpha = (T)al;
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   double rr = 0.0, rz = 0.0;
   if (i < n) {
-    x[i] += alpha * p[i];
-    T qi = q[i];
-    if (PAIR) qi += pair_in<T>(P, i, qsum);
-    const T ri = r[i] - alpha * qi;
+    x[i] = xi + alpha * pi;
+    ri -= alpha * qi;
     r[i] = ri;
     rr = (double)ri * (double)ri;
-    if (dinv) rz = (double)ri * (double)(dinv[i] * ri);
+    if (dinv) rz = (double)ri * (double)(di * ri);
   }
   rr = block_sum(rr, red);
   rz = block_sum(rz, red);
@@ -479,14 +487,23 @@ k_b_pupdate(int64_t n, int nprob, const int32_t* __restrict__ tprob,
             T* __restrict__ p) {
   __shared__ double red[2 * (kBlock / kWave)];
   const int pr = tprob[blockIdx.x];
+  // stopped before, or a breakdown (fused: the flag is set here, by the first tile)
+  if (fused ? ps[B_ACT * nprob + pr] == 0.0 : flags[F_INNER * nprob + pr] != 0) {
+    if (fused && threadIdx.x == 0 && row_off[pr] / kTileRows == blockIdx.x)
+      flags[F_INNER * nprob + pr] = 1;
+    return;
+  }
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  T zi = 0, di = 1, pi = 0;   // in flight while the partials are summed
+  if (i < n) {
+    zi = z ? z[i] : r[i];
+    if (!z) di = dinv[i];
+    pi = p[i];
+  }
   double be;
   if (fused) {
     const int64_t t0 = row_off[pr] / kTileRows;
     const bool lead = threadIdx.x == 0 && t0 == blockIdx.x;
-    if (ps[B_ACT * nprob + pr] == 0.0) {   // stopped before, or a breakdown
-      if (lead) flags[F_INNER * nprob + pr] = 1;
-      return;
-    }
     double rr, rz;
     b_sums(t0, row_off[pr + 1] / kTileRows, partA, partB, red, &rr, &rz);
     be = rz / ps[B_RZ0 * nprob + pr];
@@ -498,12 +515,10 @@ k_b_pupdate(int64_t n, int nprob, const int32_t* __restrict__ tprob,
       if (!(rr > ps[B_THR * nprob + pr]) || !isfinite(rr)) flags[F_INNER * nprob + pr] = 1;
     }
   } else {
-    if (flags[F_INNER * nprob + pr]) return;
     be = ps[B_BETA * nprob + pr];
   }
   const T beta = (T)be;
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i < n) p[i] = (z ? z[i] : dinv[i] * r[i]) + beta * p[i];
+  if (i < n) p[i] = (z ? zi : di * zi) + beta * pi;
 }
 
 // tile partials of r.z for the problems not done; with p (else NULL) also p = z
