@@ -123,7 +123,22 @@ def resid_bytes(nnz_off: int, n: int, tile_cols: int, with_w32: bool) -> float:
     return 8.0 * nnz_off + idx + 8.0 * (n + 1) + per_row * n
 
 
-COUNTERS = os.path.join(ROOT, "profiles", "k_spmv_tiled_marshak3d_16.8M_counters.md")
+def pair_bytes(vbytes: int, nnz_off: int, n: int) -> float:
+    """Algorithmic bytes of one product of the pair form (a matrix without a
+    hierarchy): every pair once, its value, 16-bit local column and a quarter
+    of its group's row byte; the diagonal and x read once and y written once.
+    (What tiles leave each other, and x read by several tiles, comes on top.)"""
+    return (vbytes + 2.25) * nnz_off / 2 + 3.0 * vbytes * n
+
+
+def pair_resid_bytes(nnz_off: int, n: int, with_w32: bool) -> float:
+    """Algorithmic bytes of the refinement loop's FP64 residual in pair form:
+    the product and the pass that completes it (r, b, x and the diagonal read;
+    r written in FP64 and FP32, and the weights of the componentwise test)."""
+    return pair_bytes(8, nnz_off, n) + (8.0 * 5 + 4.0 + (4.0 if with_w32 else 0.0)) * n
+
+
+COUNTERS = os.path.join(ROOT, "profiles", "k_pair_spmv_marshak3d_16.8M_counters.md")
 
 
 def profiled_traffic(workload: str, n: int, kernel: str):
@@ -138,12 +153,12 @@ def profiled_traffic(workload: str, n: int, kernel: str):
     sha, traffic = None, {}
     for line in open(COUNTERS):
         line = line.strip()
-        if line.startswith("spmv_source_sha256: "):
+        if line.startswith("pair_source_sha256: "):
             sha = line.split(": ", 1)[1]
         elif line.startswith("traffic ") and ": " in line:
             name, _, v = line[len("traffic "):].rpartition(": ")
             traffic[name] = float(v)
-    src = os.path.join(ROOT, "paper_2001_11606_amd", "csrc", "spmv.h")
+    src = os.path.join(ROOT, "paper_2001_11606_amd", "csrc", "pair.h")
     if sha != hashlib.sha256(open(src, "rb").read()).hexdigest():
         return None
     return traffic.get(kernel)
@@ -401,7 +416,9 @@ def run_ensemble(args):
     sh = tuned.chosen[0][1]
     shapes = rt.rt_spmv_shapes()
     us32 = tuned.us[0][1][sh]
-    bytes32 = spmv_bytes(4, nnz, rows, tcols if shapes[sh][2] else 0)
+    # (the members are assembled without hierarchies: a batch in pair form)
+    bytes32 = (pair_bytes(4, nnz, rows) if tcols
+               else spmv_bytes(4, nnz, rows, tcols if shapes[sh][2] else 0))
     achieved = bytes32 / (us32 * 1e-6) / 1e9
     out = {
         "metric": METRIC, "value": value, "unit": "particle-updates/s", "n_gpus": 1,
@@ -843,14 +860,25 @@ def run_single(args):
     tiled32 = bool(tile_cols) and (sh is None or sh[s32][2])
     tiled64 = bool(tile_cols) and (sh is None or sh[s64][2])
     tiledr = bool(tile_cols) and (sh is None or sh[sres][2])
-    k32 = (("k_spmv_tiled<float, %d, %d, SP_DOT>" % tuple(sh[s32][:2])) if tiled32 and sh
+    # a matrix without a hierarchy serves its tiled shapes in pair form
+    paired = info.levels == 1 and args.precond == 0
+
+    def pair_name(t, shape, mode):
+        return "k_pair_spmv<%s%s, %s>" % (t, ", %d" % sh[shape][1] if sh else "", mode)
+
+    k32 = (pair_name("float", s32, "PP_DOT") if tiled32 and paired
+           else ("k_spmv_tiled<float, %d, %d, SP_DOT>" % tuple(sh[s32][:2])) if tiled32 and sh
            else "k_spmv_tiled<float> (default shape)" if tiled32 else "k_spmv<float> (plain CSR)")
-    k64r = (("k_spmv_tiled<double, %d, %d, SP_RESID>" % tuple(sh[sres][:2])) if tiledr and sh
+    k64r = (pair_name("double", sres, "PP_PLAIN") + " and k_pair_resid" if tiledr and paired
+            else ("k_spmv_tiled<double, %d, %d, SP_RESID>" % tuple(sh[sres][:2])) if tiledr and sh
             else "k_spmv_tiled<double> SP_RESID" if tiledr else "k_spmv<double> SP_RESID")
-    roof32 = _kernel_roof(k32, spmv_bytes(4, nnz_off, n_rows, tile_cols if tiled32 else 0),
+    roof32 = _kernel_roof(k32, pair_bytes(4, nnz_off, n_rows) if tiled32 and paired
+                          else spmv_bytes(4, nnz_off, n_rows, tile_cols if tiled32 else 0),
                           sum(r.spmv32_calls for r in reps), sum(r.spmv32_seconds for r in reps))
-    roof_res = _kernel_roof(k64r, resid_bytes(nnz_off, n_rows, tile_cols if tiledr else 0,
-                                              args.cw_tol > 0),
+    roof_res = _kernel_roof(k64r, pair_resid_bytes(nnz_off, n_rows, args.cw_tol > 0)
+                            if tiledr and paired
+                            else resid_bytes(nnz_off, n_rows, tile_cols if tiledr else 0,
+                                             args.cw_tol > 0),
                             sum(r.resid_calls for r in reps), sum(r.resid_seconds for r in reps))
     kernels = [k for k in (roof_res, roof32) if k]
     for k in kernels:
@@ -880,9 +908,11 @@ def run_single(args):
                "max_rel_err_E_mixed": _max_rel(E, ER), "max_rel_err_e_mixed": _max_rel(e, eR),
                "max_rel_err_E_fp64": _max_rel(E64, ER), "max_rel_err_e_fp64": _max_rel(e64, eR),
                "reference": "the same step in FP64 to 1e-14, normwise and componentwise"}
-        k64 = (("k_spmv_tiled<double, %d, %d, SP_DOT>" % tuple(sh[s64][:2])) if tiled64 and sh
-               else "FP64 SP_DOT product")
-        r64 = _kernel_roof(k64, spmv_bytes(8, nnz_off, n_rows, tile_cols if tiled64 else 0),
+        k64 = (pair_name("double", s64, "PP_DOT") if tiled64 and paired
+               else ("k_spmv_tiled<double, %d, %d, SP_DOT>" % tuple(sh[s64][:2]))
+               if tiled64 and sh else "FP64 SP_DOT product")
+        r64 = _kernel_roof(k64, pair_bytes(8, nnz_off, n_rows) if tiled64 and paired
+                           else spmv_bytes(8, nnz_off, n_rows, tile_cols if tiled64 else 0),
                            rep64.spmv64_calls, rep64.spmv64_seconds)
         if r64:
             cmp["fp64_cg_product"] = r64
