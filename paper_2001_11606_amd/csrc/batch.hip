@@ -9,12 +9,14 @@
 // Each launch then covers the whole ensemble: one product, one vector update,
 // one material pass for all problems.  The Krylov scalars are per problem
 // (alpha_p, beta_p, r_p.z_p, ||r_p||), kept on the device; the block partials
-// of a problem are combined by one block per problem in a fixed order.  A
+// of a problem are combined in a fixed order by the blocks of the kernel that
+// needs them (by one block per problem where they are many).  A
 // problem that meets its own tolerance is flagged, and the blocks of flagged
 // problems return at once, so the others keep iterating undisturbed.  Since
 // a flagged problem is left as it is, extra iterations are no-ops: the PCG
 // iterations can be replayed as HIP graphs of K iterations with a single
-// host read of the flags per graph.  Preconditioner: Jacobi.
+// host read of the flags per graph.  Preconditioner: Jacobi, or the V-cycle of
+// the problems' concatenated hierarchies.
 #include <algorithm>
 #include <chrono>
 #include <cmath>

@@ -4,8 +4,10 @@
 // order.  Interior particles occupy sorted positions [0, n_interior) and
 // ghosts [n_interior, n_total); perm[s] maps a sorted position back to the
 // caller's index.  The V-scaled diffusion matrix (rows and columns = sorted
-// interior particles) is stored as a diagonal plus an off-diagonal CSR with
-// int64 row pointers, int32 columns (ascending) and FP64 values, with FP32
+// interior particles) is stored as a diagonal plus its off-diagonal entries.
+// Without a hierarchy that is the pair form (PairForm, pair.h): every pair
+// once, in tiles of kTileRows rows.  With one, or where a plain shape or an
+// export asks for it, it is an off-diagonal CSR with int64 row pointers, int32 columns (ascending) and FP64 values, with FP32
 // copies for the mixed-precision solver.  For the sparse products each level
 // may also hold a tiled form of the same CSR: rows in tiles of kTileRows, the
 // ascending distinct columns of each tile (tile_cols, offsets tile_off) and,

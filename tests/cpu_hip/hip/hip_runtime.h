@@ -293,6 +293,8 @@ inline void wave_lds_add(bool active, T* p, T v) {
   bar.arrive_and_wait();
 }
 #define RT_WAVE_LDS_ADD(active, p, v) wave_lds_add((active), (p), (v))
+inline int min(int a, int b) { return a < b ? a : b; }
+inline int max(int a, int b) { return a > b ? a : b; }
 inline int __popcll(unsigned long long x) { return __builtin_popcountll(x); }
 
 template <typename... KArgs, typename... Args>
