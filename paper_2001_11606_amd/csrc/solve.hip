@@ -330,11 +330,10 @@ k_dot(int64_t n, const T* __restrict__ a, const T* __restrict__ b, double* __res
 // PAIR: q holds each tile's own part of A p, completed here (pair_in)
 // npq > 0: alpha is formed here from the product's npq partials (block 0
 // keeps the record), else it is s[S_ALPHA].
-// With one element per thread all that does not wait for alpha is requested
-// before the partials are combined (16.4k FP64 rows 9.7 -> 5.5 us).  With four
-// the waves in flight hide the waits, and holding four rows' loads costs
-// registers and with them waves (FP32, 16.8M rows: 109 us on average as it is,
-// 138 us with all loads first).
+// The first element's loads, which do not wait for alpha, are in flight while
+// the partials are combined (16.4k FP64 rows, one element per thread: 9.7 ->
+// 5.5 us; steps of 1M rows, four: 10.12 -> 10.04 ms).  Those of all four would
+// cost registers and with them waves (FP32, 16.8M rows: 109 -> 138 us).
 template <typename T, bool JAC, int CW, bool PAIR, int E>
 __global__ void __launch_bounds__(kBlock)
 k_update(int64_t n, PairIn P, const T* __restrict__ qsum, int npq, const double* __restrict__ pq,
@@ -360,7 +359,7 @@ k_update(int64_t n, PairIn P, const T* __restrict__ qsum, int npq, const double*
   };
   const int64_t i0 = (int64_t)blockIdx.x * kBlock * E + threadIdx.x;
   Row first{};
-  if (E == 1 && i0 < n) first = load(i0);
+  if (i0 < n) first = load(i0);
   double al = 0.0;
   if (npq > 0) {
     const Combined v = combine(npq, pq, nullptr, nullptr, red);
@@ -373,7 +372,7 @@ k_update(int64_t n, PairIn P, const T* __restrict__ qsum, int npq, const double*
   for (int e = 0; e < E; ++e) {
     const int64_t i = i0 + e * kBlock;
     if (i >= n) break;
-    const Row v = E == 1 ? first : load(i);
+    const Row v = e == 0 ? first : load(i);
     const T xi = v.x + alpha * v.p;
     x[i] = xi;
     const T ri = v.r - alpha * v.q;
