@@ -719,10 +719,11 @@ __global__ void k_dense_fill(int64_t n, const int64_t* __restrict__ rp,
 // needed), n <= kDenseMax, from src into dst: with P the inverse of the
 // 32 x 32 pivot block K, block (K, K) becomes P, (K, J) P A_KJ, (I, K) -A_IK P
 // and (I, J) A_IJ - A_IK P A_KJ.  One workgroup per 32 x 32 block; each inverts
-// the pivot block itself (32 steps in LDS), so that a step is one launch of
-// about 30 us, bound by those steps' divisions and barriers.  A coarsest level
-// of 170 rows takes 6 of them (0.18 ms), where one workgroup eliminating
-// column after column in global memory took 1.9 ms.  Rows and columns past n
+// the pivot block itself (32 steps, entries in registers, the next pivot's row
+// and column through LDS), so that a step is one launch of about 27 us (30 us
+// with the block in LDS and two barriers a step), bound by those steps' chain of
+// divisions.  A coarsest level of 170 rows takes 6 of them (0.16 ms), where one
+// workgroup eliminating column after column in global memory took 1.9 ms.  Rows and columns past n
 // read as the identity.
 constexpr int kGjBlock = 32;
 
@@ -734,28 +735,37 @@ __global__ void __launch_bounds__(kBlock)
 k_gj_step(int n, int kb, const double* __restrict__ src, double* __restrict__ dst) {
   constexpr int B = kGjBlock, PER = B * B / kBlock;   // entries per thread
   __shared__ double P[B][B + 1], L[B][B + 1], R[B][B + 1], Q[B][B + 1];
+  __shared__ double prow[2][B], pcol[2][B];   // pivot row and column, by step parity
   const int tid = threadIdx.x, j = tid % B, i0 = tid / B;   // entries (i0 + 8 e, j)
   const int I = blockIdx.y, J = blockIdx.x, K = kb * B;
+  double v[PER];   // the thread's entries of the pivot block
   for (int e = 0; e < PER; ++e) {
     const int i = i0 + e * (kBlock / B);
-    P[i][j] = gj_read(src, n, K + i, K + j);
+    v[e] = gj_read(src, n, K + i, K + j);
+    if (i == 0) prow[0][j] = v[e];
+    if (j == 0) pcol[0][i] = v[e];
     L[i][j] = gj_read(src, n, I * B + i, K + j);
     R[i][j] = gj_read(src, n, K + i, J * B + j);
   }
   __syncthreads();
   for (int k = 0; k < B; ++k) {
-    const double piv = 1.0 / P[k][k];
-    double v[PER];
+    const int b = k & 1;
+    const double piv = 1.0 / prow[b][k], rk = prow[b][j];
+#pragma unroll
     for (int e = 0; e < PER; ++e) {
       const int i = i0 + e * (kBlock / B);
-      if (i == k) v[e] = j == k ? piv : P[k][j] * piv;
-      else if (j == k) v[e] = -P[i][k] * piv;
-      else v[e] = P[i][j] - P[i][k] * (P[k][j] * piv);
+      const double ck = pcol[b][i];
+      if (i == k) v[e] = j == k ? piv : rk * piv;
+      else if (j == k) v[e] = -ck * piv;
+      else v[e] = v[e] - ck * (rk * piv);
+      if (i == k + 1) prow[b ^ 1][j] = v[e];
+      if (j == k + 1) pcol[b ^ 1][i] = v[e];
     }
     __syncthreads();
-    for (int e = 0; e < PER; ++e) P[i0 + e * (kBlock / B)][j] = v[e];
-    __syncthreads();
   }
+#pragma unroll
+  for (int e = 0; e < PER; ++e) P[i0 + e * (kBlock / B)][j] = v[e];
+  __syncthreads();
   // Q = P A_KJ (J != K), else P
   for (int e = 0; e < PER; ++e) {
     const int i = i0 + e * (kBlock / B);
