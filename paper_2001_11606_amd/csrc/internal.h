@@ -411,7 +411,7 @@ struct rt_matrix {
   rt::DevBuf<double> partF;          // second level of the partial reductions
   rt::DevBuf<float> w32;             // weights 1/(a_ii |x_i|) of the FP32 inner solve
   rt::DevBuf<double> scal;           // device scalars (see solve.hip)
-  rt::DevBuf<int32_t> stop;          // PCG stop flag: set on the device when the loop ends
+  rt::DevBuf<int32_t> stop;          // PCG stop flag, two words: set on the device when the loop ends
   // Residual carried between outer iterations: after a Newton step, r64 holds
   // bs - A xs for the step's right-hand side bs and solution xs (resid_ok);
   // bs_prev keeps that right-hand side while the next step forms its own, and

@@ -28,7 +28,10 @@
 // The stopping test runs on the device too: the residual's first reduction
 // (k_start) sets the thresholds and a stop flag, the kernel that forms ||r||^2
 // sets the flag once the threshold is met (or on breakdown), and every kernel
-// of the iteration does nothing once it is set.  The host queues the start and
+// of the iteration does nothing once it is set.  The flag is kept in two words
+// (STOP_X, STOP_P), so that no launch reads the word it writes: the waves of a
+// block read it one by one, and those that went on while the others left would
+// combine sums with shares missing.  The host queues the start and
 // several iterations between reads of the state -- as many as the observed
 // convergence rate says are still needed, scaled down so that it rarely
 // queues past the end -- so neither a start nor an iteration costs a host
@@ -50,6 +53,11 @@ namespace {
 // between (a kernel whose blocks read one writes the other)
 enum { S_RZ = 0, S_RZ_ALT, S_PQ, S_ALPHA, S_BETA, S_RR, S_RR0, S_CW0, S_BB, S_BAD, S_ITS, S_STOP,
        S_CW, S_RZ_PREV, S_RZ_LAST, S_THR, S_CWTHR, S_DONE, S_MIS, S_COUNT };
+// The two words of the stop flag.  The product and the x, r update read STOP_X;
+// the preconditioner and the p update read STOP_P.  The x, r update sets STOP_P
+// (breakdown, or STOP_X is set), the p update STOP_X (the loop ends, or STOP_P is
+// set); the one-block kernels between launches set both.
+enum { STOP_X = 0, STOP_P = 1, STOP_WORDS };
 // componentwise measure of the update kernel: none, |r_i| w_i / |x_i| with
 // w = 1/diag (the iterate's own measure), or |r_i| w_i with fixed weights
 enum { CW_NONE = 0, CW_X = 1, CW_W = 2 };
@@ -95,9 +103,9 @@ __device__ __forceinline__ Combined combine(int np, const double* __restrict__ p
 
 // alpha = r.z / p.Ap for the iteration that reads r.z from s[S_RZ + slot];
 // returns false (and the record, by the calling block's thread 0 if keep, sets
-// the stop flag) on breakdown: p.Ap not positive
+// *word) on breakdown: p.Ap not positive
 __device__ __forceinline__ bool take_alpha(double pq, int slot, double* __restrict__ s,
-                                           int32_t* __restrict__ stop, bool keep, double* alpha) {
+                                           int32_t* __restrict__ word, bool keep, double* alpha) {
   const bool ok = pq > 0.0 && isfinite(pq);
   *alpha = ok ? s[S_RZ + slot] / pq : 0.0;
   if (keep && threadIdx.x == 0) {
@@ -106,16 +114,17 @@ __device__ __forceinline__ bool take_alpha(double pq, int slot, double* __restri
     if (!ok) {
       s[S_BAD] = 1.0;
       s[S_STOP] = 1.0;
-      *stop = 1;
+      *word = 1;
     }
   }
   return ok;
 }
 
 // beta of the iteration from rr = ||r||^2, rz = r.z (new) and the componentwise
-// measure cw (tested if has_cw); returns false when the loop ends here
+// measure cw (tested if has_cw); returns false (and sets *word) when the loop
+// ends here
 __device__ __forceinline__ bool take_beta(double rr, double rz, double cw, bool has_cw, int slot,
-                                          double* __restrict__ s, int32_t* __restrict__ stop,
+                                          double* __restrict__ s, int32_t* __restrict__ word,
                                           bool keep, double* beta) {
   const double last = s[S_RZ + slot];
   const bool ends = !(rr > s[S_THR]) && (!has_cw || !(cw > s[S_CWTHR]));
@@ -130,28 +139,32 @@ __device__ __forceinline__ bool take_beta(double rr, double rz, double cw, bool 
     if (has_cw) s[S_CW] = cw;
     if (ends) {
       s[S_STOP] = 1.0;
-      *stop = 1;
+      *word = 1;
     }
   }
   return !ends;
 }
 
 // One block: combine the partials and update the scalars; nothing happens
-// once *stop is set, except for the norms (FIN_RR, FIN_BB).
+// once the stop flag is set, except for the norms (FIN_RR, FIN_BB).  Every wave
+// has read the flag before thread 0, behind the barriers of combine, sets it.
 __global__ void __launch_bounds__(kBlock)
 k_finalize(int op, int np, const double* __restrict__ pa, const double* __restrict__ pb,
            const double* __restrict__ pc, double* __restrict__ s, int32_t* __restrict__ stop,
            int slot) {
   __shared__ double red[kBlock / kWave];
-  if (op != FIN_RR && op != FIN_BB && *stop) return;
+  if (op != FIN_RR && op != FIN_BB && stop[op == FIN_BETA ? STOP_P : STOP_X]) return;
   const Combined v = combine(np, pa, pb, pc, red);
   double unused;
   switch (op) {
     case FIN_ALPHA:
-      (void)take_alpha(v.a, slot, s, stop, true, &unused);
+      if (!take_alpha(v.a, slot, s, stop + STOP_X, true, &unused) && threadIdx.x == 0)
+        stop[STOP_P] = 1;
       break;
     case FIN_BETA:
-      (void)take_beta(v.a, v.b, v.c, pc != nullptr, slot, s, stop, true, &unused);
+      if (!take_beta(v.a, v.b, v.c, pc != nullptr, slot, s, stop + STOP_X, true, &unused) &&
+          threadIdx.x == 0)
+        stop[STOP_P] = 1;
       break;
     default:
       if (threadIdx.x != 0) return;
@@ -221,7 +234,7 @@ k_start(int npr, const double* __restrict__ pr, const double* __restrict__ pc, i
   s[S_BAD] = 0.0;
   s[S_ITS] = 0.0;
   s[S_STOP] = halt ? 1.0 : 0.0;
-  *stop = halt ? 1 : 0;
+  stop[STOP_X] = stop[STOP_P] = halt ? 1 : 0;
 }
 
 // Streaming vector kernels: kVec elements per thread (coalesced per element
@@ -342,7 +355,11 @@ k_update(int64_t n, PairIn P, const T* __restrict__ qsum, int npq, const double*
          const T* __restrict__ w, double* __restrict__ partA, double* __restrict__ partB,
          double* __restrict__ partC, int32_t* __restrict__ stop) {
   __shared__ double red[kBlock / kWave];
-  if (*stop) return;
+  const bool keep = blockIdx.x == 0;
+  if (stop[STOP_X]) {   // read by this launch, never written by it
+    if (keep && threadIdx.x == 0) stop[STOP_P] = 1;
+    return;
+  }
   struct Row {
     T x, p, q, r, dinv, w;
   };
@@ -363,7 +380,7 @@ k_update(int64_t n, PairIn P, const T* __restrict__ qsum, int npq, const double*
   double al = 0.0;
   if (npq > 0) {
     const Combined v = combine(npq, pq, nullptr, nullptr, red);
-    if (!take_alpha(v.a, slot, s, stop, blockIdx.x == 0, &al)) return;
+    if (!take_alpha(v.a, slot, s, stop + STOP_P, keep, &al)) return;
   } else {
     al = s[S_ALPHA];
   }
@@ -407,7 +424,11 @@ k_pupdate(int64_t n, int np, const double* __restrict__ pa, const double* __rest
           const T* __restrict__ r, const T* __restrict__ dinv, const T* __restrict__ z,
           T* __restrict__ p, int32_t* __restrict__ stop) {
   __shared__ double red[kBlock / kWave];
-  if (*stop) return;
+  const bool keep = blockIdx.x == 0;
+  if (stop[STOP_P]) {   // read by this launch, never written by it
+    if (keep && threadIdx.x == 0) stop[STOP_X] = 1;
+    return;
+  }
   const int64_t i0 = (int64_t)blockIdx.x * kBlock * E + threadIdx.x;
   T zv[E], dv[E], pv[E];
 #pragma unroll
@@ -420,7 +441,7 @@ k_pupdate(int64_t n, int np, const double* __restrict__ pa, const double* __rest
   double be = 0.0;
   if (np > 0) {
     const Combined v = combine(np, pa, pb, pc, red);
-    if (!take_beta(v.a, v.b, v.c, pc != nullptr, slot, s, stop, blockIdx.x == 0, &be)) return;
+    if (!take_beta(v.a, v.b, v.c, pc != nullptr, slot, s, stop + STOP_X, keep, &be)) return;
   } else {
     be = s[S_BETA];
   }
@@ -516,7 +537,7 @@ struct Work {
         *w32 = nullptr;
   double *partA = nullptr, *partB = nullptr, *partC = nullptr, *partD = nullptr, *partF = nullptr,
          *scal = nullptr;
-  int32_t* stop = nullptr;
+  int32_t* stop = nullptr;   // STOP_WORDS words
 };
 
 template <typename T> struct Sel;
@@ -570,7 +591,8 @@ int finalize(rt_ctx* ctx, const Work& W, int op, int np, const double* pa, const
              const double* pc = nullptr, int slot = 0) {
   const bool in_loop = op == FIN_ALPHA || op == FIN_BETA;
   Partials p{np, pa, pb, pc};
-  RT_CHECK(fold(ctx, W, &p, W.partF, in_loop ? W.stop : nullptr));
+  RT_CHECK(fold(ctx, W, &p, W.partF,
+                in_loop ? W.stop + (op == FIN_BETA ? STOP_P : STOP_X) : nullptr));
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(kBlock), 0, ctx->stream, op, p.np, p.a, p.b, p.c,
                      W.scal, W.stop, slot);
   RT_LAUNCH_CHECK();
@@ -631,6 +653,7 @@ int pcg_iteration(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r
   T* q = S::q(W);
   T* z = S::z(W);
   int32_t* stop = W.stop;
+  const int32_t* stop_p = W.stop + STOP_P;
   const int gv = vec_blocks(n);
   int nbk = 0;
   Prof pf(ctx, S::kind);
@@ -638,11 +661,11 @@ int pcg_iteration(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r
   const bool pair = pair_serves(L, level_shape<T>(L));
   if (pair)
     RT_CHECK((launch_pair<T, PP_DOT>(st, L, S::diag(L), p, q, W.partD, &nbk, level_shape<T>(L),
-                                     nullptr, stop)));
+                                     nullptr, stop + STOP_X)));
   else
     RT_CHECK((launch_spmv_level<T, SP_DOT>(st, L, S::val(L), S::diag(L), p, nullptr, nullptr, q,
                                            nullptr, W.partD, &nbk, level_shape<T>(L), nullptr,
-                                           stop)));
+                                           stop + STOP_X)));
   RT_CHECK(pf.end());
   // the product's partials go to partD, so that the update's blocks can read
   // them while others already write theirs
@@ -668,8 +691,8 @@ int pcg_iteration(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r
     else if (cw.mode == CW_W) RT_UPD(false, CW_W);
     else RT_UPD(false, CW_NONE);
     RT_LAUNCH_CHECK();
-    RT_CHECK(vcycle<T>(ctx, A, r, z, stop));
-    hipLaunchKernelGGL(k_dot<T>, dim3(gv), dim3(kBlock), 0, st, n, r, z, W.partB, stop);
+    RT_CHECK(vcycle<T>(ctx, A, r, z, stop_p));
+    hipLaunchKernelGGL(k_dot<T>, dim3(gv), dim3(kBlock), 0, st, n, r, z, W.partB, stop_p);
   } else {
     if (cw.mode == CW_X) RT_UPD(true, CW_X);
     else if (cw.mode == CW_W) RT_UPD(true, CW_W);
@@ -793,7 +816,7 @@ int ensure_work(rt_matrix* A, bool mixed) {
   RT_CHECK(A->partD.reserve(max_partials(n)));
   RT_CHECK(A->partF.reserve(6 * kMaxPartials));
   RT_CHECK(A->scal.reserve(std::max<int>(S_COUNT, kScalars)));
-  RT_CHECK(A->stop.reserve(1));
+  RT_CHECK(A->stop.reserve(STOP_WORDS));
   if (mixed)
     for (auto* b : {&A->r32, &A->p32, &A->q32, &A->z32, &A->d32, &A->w32}) RT_CHECK(b->reserve(n));
   return RT_OK;
@@ -1118,7 +1141,7 @@ Work carve_work(Carve& c, int64_t n, bool mixed, double** bs, double** xs) {
   W.partB = c.take<double>(vec_blocks(n));
   W.partF = c.take<double>(6 * kMaxPartials);
   W.scal = c.take<double>(S_COUNT);
-  W.stop = c.take<int32_t>(1);
+  W.stop = c.take<int32_t>(STOP_WORDS);
   return W;
 }
 

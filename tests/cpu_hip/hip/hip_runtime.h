@@ -101,6 +101,42 @@ inline BlockState& g_block_ref() {
 }
 #define g_block g_block_ref()
 
+// Blocks that start while block 0 of their launch ends.  With g_late set, the
+// blocks of a launch after block 0 start on the watched words' values from
+// before the launch; the values that block 0 left appear, and the waves after
+// the first start, once every thread of the first wave waits at a barrier or
+// has ended.  between (may be empty) runs after block 0, with g_late unset: the
+// launches in it leave their own values in LDS.
+struct LateWrite {
+  int32_t* words = nullptr;
+  int n = 0;
+  std::function<void()> between;
+};
+inline LateWrite* g_late = nullptr;
+struct Hold {
+  std::atomic<int> waiting{0};
+  std::atomic<bool> open{true};
+  std::vector<int32_t> after;
+  LateWrite* late = nullptr;
+  void arrive() {
+    if (waiting.fetch_add(1) + 1 < 64) return;
+    std::copy(after.begin(), after.end(), late->words);
+    open.store(true);
+    open.notify_all();
+  }
+};
+inline Hold& g_hold_ref() {
+  static Hold* h = new Hold;
+  return *h;
+}
+#define g_hold g_hold_ref()
+inline thread_local bool t_holds = false;   // of the first wave, not yet at a barrier
+inline void late_arrive() {
+  if (!t_holds) return;
+  t_holds = false;
+  g_hold.arrive();
+}
+
 inline int log2i(int w) {
   int l = 0;
   while ((1 << l) < w) ++l;
@@ -157,9 +193,25 @@ void launch(dim3 grid, dim3 block, F&& f, size_t shmem = 0) {
     fprintf(stderr, "cpuhip: invalid block size %d\n", nt);
     abort();
   }
+  LateWrite* const late = nt > 64 && grid.x > 1 ? g_late : nullptr;
+  std::vector<int32_t> before;
+  if (late) before.assign(late->words, late->words + late->n);
   for (unsigned bz = 0; bz < grid.z; ++bz)
     for (unsigned by = 0; by < grid.y; ++by)
       for (unsigned bx = 0; bx < grid.x; ++bx) {
+        if (late && bx == 1) {
+          g_hold.after.assign(late->words, late->words + late->n);
+          g_late = nullptr;
+          if (late->between) late->between();
+          g_late = late;
+        }
+        const bool hold = late && bx > 0;
+        if (hold) {
+          std::copy(before.begin(), before.end(), late->words);
+          g_hold.late = late;
+          g_hold.waiting.store(0);
+          g_hold.open.store(false);
+        }
         g_block.reset(nt);
         std::unique_ptr<unsigned char[]> dyn(shmem ? new unsigned char[shmem] : nullptr);
         if (shmem) memset(dyn.get(), 0xBE, shmem);
@@ -169,7 +221,10 @@ void launch(dim3 grid, dim3 block, F&& f, size_t shmem = 0) {
           tctx.bid = dim3(bx, by, bz);
           tctx.bdim = block;
           tctx.gdim = grid;
+          t_holds = hold && t < 64;
+          if (hold && t >= 64) g_hold.open.wait(false);
           f();
+          late_arrive();
           // leave every barrier so that the remaining threads can proceed
           g_block.block_bar->arrive_and_drop();
           for (int w = 0; w < 7; ++w) g_block.group_bar[w][t >> w]->arrive_and_drop();
@@ -185,7 +240,10 @@ void launch(dim3 grid, dim3 block, F&& f, size_t shmem = 0) {
 #define blockDim (cpuhip::tctx.bdim)
 #define gridDim (cpuhip::tctx.gdim)
 
-inline void __syncthreads() { cpuhip::g_block.block_bar->arrive_and_wait(); }
+inline void __syncthreads() {
+  cpuhip::late_arrive();
+  cpuhip::g_block.block_bar->arrive_and_wait();
+}
 inline int atomicCAS(int* p, int cmp, int v) {
   std::atomic_ref<int>(*p).compare_exchange_strong(cmp, v);
   return cmp;
