@@ -7,10 +7,11 @@
 // pairs (i, j) of its rows i with j > i, and numbers the columns it meets
 // locally: its own rows 0..255, then the columns of later tiles (its external
 // columns, ascending, xcol[xoff[t] ...)).  Pairs are stored row by row in
-// groups of four, the last group of a row filled up with zero values on the
-// row's last column: one row byte, four 16-bit local columns and four values
-// per group.  The 256 threads of a tile's block take equal runs of consecutive
-// groups, and the groups are stored in the order of that walk (step k of
+// groups of four, the last group of a row filled up with zero values on
+// one column past the tile's own, where x reads as zero and the sums are
+// dropped (an infinite x elsewhere must not meet a zero value): one row byte,
+// four 16-bit local columns and four values per group.  The 256 threads of a
+// tile's block take equal runs of consecutive groups, and the groups are stored in the order of that walk (step k of
 // thread T at 256 k + T): loads are contiguous over a wave, there are no row
 // pointers and no ragged ends, a thread keeps its row's sum in a register, and
 // the lanes of a wave hold different rows, so that their LDS adds seldom meet
@@ -89,7 +90,7 @@ constexpr int kPairSets = kBlock / kWave;   // accumulator sets of a product
 // LDS bytes of a product over tiles of at most ncol columns
 template <typename T>
 inline size_t pair_lds(int ncol) {
-  return (sizeof(double) * kPairSets + sizeof(T)) * (size_t)ncol;
+  return (sizeof(double) * kPairSets + sizeof(T)) * (size_t)(ncol + 1);
 }
 
 // U groups of a thread: steps k .. k + U - 1 of its run.  The loads are not
@@ -164,8 +165,9 @@ k_pair_spmv(int64_t n, int per, int64_t ntiles, PairArgs A, const T* __restrict_
   const T* vt = val + 4 * g0;
   const rt_u16x4* ct = reinterpret_cast<const rt_u16x4*>(A.col + 4 * g0);
   const uint8_t* rows = A.row + g0;
-  double* acc = reinterpret_cast<double*>(dyn_lds);   // kPairSets sets of ncol
-  T* xs = reinterpret_cast<T*>(acc + kPairSets * ncol);
+  const int nset = ncol + 1;   // and the filling's column (8 or 32 of them: 0.6% of a 16.8M step)
+  double* acc = reinterpret_cast<double*>(dyn_lds);   // kPairSets sets of nset
+  T* xs = reinterpret_cast<T*>(acc + kPairSets * nset);
   PairBatch<T, U> b0, b1;
   b0.load(vt, ct, rows, 0, ng);   // in flight while the columns are staged
   T di = 0;
@@ -173,10 +175,11 @@ k_pair_spmv(int64_t n, int per, int64_t ntiles, PairArgs A, const T* __restrict_
     if (live) di = diag[i];
     xs[tid] = live ? x[i] : T(0);
     for (int k = tid; k < next; k += kBlock) xs[kTileRows + k] = x[A.xcol[x0 + k]];
+    if (tid == 0) xs[ncol] = T(0);
   }
-  for (int k = tid; k < kPairSets * ncol; k += kBlock) acc[k] = 0.0;
+  for (int k = tid; k < kPairSets * nset; k += kBlock) acc[k] = 0.0;
   __syncthreads();
-  double* mine = acc + (tid / kWave) * ncol;
+  double* mine = acc + (tid / kWave) * nset;
   T s = 0, xr = 1;
   int cur = -1;
   for (int k = 0; k * kBlock < ng; k += 2 * U) {
@@ -191,7 +194,7 @@ k_pair_spmv(int64_t n, int per, int64_t ntiles, PairArgs A, const T* __restrict_
   {
     double sum = 0.0;
 #pragma unroll
-    for (int w = 0; w < kPairSets; ++w) sum += acc[w * ncol + tid];
+    for (int w = 0; w < kPairSets; ++w) sum += acc[w * nset + tid];
     if (MODE != PP_ONES) sum = (double)di * (double)xs[tid] + sum;
     if (live) {
       y[i] = (T)sum;
@@ -201,7 +204,7 @@ k_pair_spmv(int64_t n, int per, int64_t ntiles, PairArgs A, const T* __restrict_
   for (int k = kTileRows + tid; k < ncol; k += kBlock) {
     double sum = 0.0;
 #pragma unroll
-    for (int w = 0; w < kPairSets; ++w) sum += acc[w * ncol + k];
+    for (int w = 0; w < kPairSets; ++w) sum += acc[w * nset + k];
     xsum[x0 + k - kTileRows] = (T)sum;
     if (MODE == PP_DOT) dot += (double)xs[k] * sum;
   }

@@ -248,7 +248,7 @@ k_pair_build(int64_t nin, const int64_t* __restrict__ ptr, const int32_t* __rest
       const int len = RT_UNIFORM(slen[r]);
       const int32_t me = lo + r;
       const int o = sgo[r];
-      int done = 0, last = 0;
+      int done = 0;
       int32_t cc = c[u];
       for (int k = 0; k < len; k += kWave) {
         if (k > 0) cc = k + lane < len ? in[srp[r] + k + lane] : -1;
@@ -265,7 +265,6 @@ k_pair_build(int64_t nin, const int64_t* __restrict__ ptr, const int32_t* __rest
           const int e = done + __popcll(m & ((1ull << lane) - 1));
           oc[4 * place(o + (e >> 2)) + (e & 3)] = (uint16_t)l;
         }
-        if (m) last = __shfl(l, 63 - __builtin_clzll(m));
         done += __popcll(m);
       }
       const int ng = (done + 3) / 4;
@@ -273,7 +272,7 @@ k_pair_build(int64_t nin, const int64_t* __restrict__ ptr, const int32_t* __rest
         const int at = place(o + q);
         orow[at] = (uint8_t)r;
         if (q == ng - 1)   // the row's last group is filled up
-          for (int e = done - 4 * q; e < 4; ++e) oc[4 * at + e] = (uint16_t)last;
+          for (int e = done - 4 * q; e < 4; ++e) oc[4 * at + e] = (uint16_t)(kTileRows + ext);
       }
     }
   }
@@ -477,7 +476,7 @@ k_pair_values(int64_t n, int kernel, PairArgs A, const double* __restrict__ sp4,
     double v[4];
 #pragma unroll
     for (int q = 0; q < 4; ++q) {
-      if (q > 0 && c[q] == c[q - 1]) {   // the filling of a row's last group
+      if (c[q] >= ncol) {   // the filling of a row's last group
         v[q] = 0.0;
         continue;
       }
