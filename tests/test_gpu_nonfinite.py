@@ -55,3 +55,12 @@ def _check(ctx, prob, amg, shapes=(-1,)):
 def test_pair_form_infinite_entry(ctx, name):
     from paper_2001_11606_amd import rt
     _check(ctx, CASES[name](), rt.amg_opts(max_levels=1))
+
+
+@pytest.mark.parametrize("name", list(CASES))
+def test_csr_rows_infinite_entry(ctx, name):
+    """A matrix with a hierarchy (its small fine level takes a plain shape by
+    default), then every kind of requested shape."""
+    from paper_2001_11606_amd import rt
+    _check(ctx, CASES[name](), rt.amg_opts(max_levels=8, coarse_size=16),
+           shapes=(-1, 0, 1, 2, 3, 4, 5, 6, 8, 13, 16))
