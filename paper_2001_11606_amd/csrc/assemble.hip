@@ -315,7 +315,7 @@ int assemble_csr(rt_ctx* ctx, rt_matrix* A, bool with_diag) {
     RT_CHECK(L.col.reserve(nnz));
   }
   RT_CHECK(L.val64.reserve(L.nnz + kSpmvPad));
-  const bool fp32 = A->has_fp32;
+  const bool fp32 = with_diag ? A->amg.build_fp32 != 0 : A->has_fp32;
   if (with_diag)
     for (auto* b : {&L.diag64, &L.dinv64, &L.sinv64}) RT_CHECK(b->reserve(nin));
   if (fp32) {
@@ -323,6 +323,7 @@ int assemble_csr(rt_ctx* ctx, rt_matrix* A, bool with_diag) {
     if (with_diag)
       for (auto* b : {&L.diag32, &L.dinv32, &L.sinv32}) RT_CHECK(b->reserve(nin));
   }
+  A->has_fp32 = fp32;   // the buffers exist
   if (nin > 0) {
     AsmArgs aa{nb->ptr.p, L.rp.p, nb->idx.p, nb->sp4.p, A->VD.p, A->sa.p,
                A->f.p, A->Eall.p, new_rows ? L.col.p : nullptr, L.val64.p,
@@ -402,8 +403,6 @@ int assemble(rt_ctx* ctx, const rt_neighbors* nb, const rt_step_inputs* in, rt_m
   if (A->levels.empty()) A->levels.resize(1);
   Level& L = A->levels[0];
   L.n = nin;
-  const bool fp32 = A->amg.build_fp32 != 0;
-  A->has_fp32 = fp32;
   // A matrix without a hierarchy is kept in pair form: half the bytes per
   // product and each pair evaluated once.  The set-up of a hierarchy reads
   // CSR rows, and so does a matrix asked to be untiled or whose tiles do not
@@ -414,13 +413,14 @@ int assemble(rt_ctx* ctx, const rt_neighbors* nb, const rt_step_inputs* in, rt_m
     L.csr_rows = false;
     L.pair.on = false;
     if (pairs) RT_CHECK(build_pairs(ctx, nb, L));
-  } else if (L.pair.on && !pairs) {   // re-assembled with other options
+  }
+  L.csr_vals = false;
+  if (L.pair.on && pairs) return assemble_pairs(ctx, A);
+  RT_CHECK(assemble_csr(ctx, A, true));
+  if (L.pair.on) {   // re-assembled with other options; only now are there CSR rows
     L.pair.on = false;
     tiles = true;
   }
-  L.csr_vals = false;
-  if (L.pair.on) return assemble_pairs(ctx, A);
-  RT_CHECK(assemble_csr(ctx, A, true));
   if (tiles) RT_CHECK(build_tiles(ctx, L));
   return RT_OK;
 }

@@ -649,6 +649,7 @@ int assemble_pairs(rt_ctx* ctx, rt_matrix* A) {
     RT_CHECK(P.sum32.reserve(P.ext_total));
     for (auto* b : {&L.diag32, &L.dinv32, &L.sinv32}) RT_CHECK(b->reserve(n));
   }
+  A->has_fp32 = fp32;   // the buffers exist
   L.csr_vals = false;
   const size_t lds = sizeof(PairRec) * (size_t)(kTileRows + P.max_ext);
   DiagArgs da{nb->ptr.p, nb->n_int_nbrs.p, nb->idx.p, nb->sp4.p, A->VD.p, A->sa.p, A->f.p,

@@ -368,7 +368,10 @@ inline void hipLaunchKernelGGL(void (*k)(KArgs...), dim3 grid, dim3 block, size_
 }
 
 // ---- runtime API -------------------------------------------------------------
+// larger requests fail (allocation failures of a test)
+inline size_t cpuhip_malloc_max = SIZE_MAX;
 inline hipError_t hipMalloc(void** p, size_t bytes) {
+  if (bytes > cpuhip_malloc_max) return hipErrorOutOfMemory;
   *p = malloc(bytes ? bytes : 1);
   return *p ? hipSuccess : hipErrorOutOfMemory;
 }

@@ -7,6 +7,7 @@
 //    p.Ap < 0), FP64 and mixed, plain and with late blocks: the same solution, bit
 //    for bit; printed, so that builds with other reductions can be compared.
 #include "../../paper_2001_11606_amd/csrc/solve.hip"
+#include "lattice.h"
 
 namespace {
 using namespace rt;
@@ -77,47 +78,10 @@ void late_kernels() {
   }
 }
 
-// an n x n lattice on the unit square; sign -1: negative masses, so negative volumes
-struct System {
-  std::vector<double> pos, h, one, m, e, b, zero;
-  rt_neighbors* nb = nullptr;
-  rt_matrix* A = nullptr;
-  System(rt_ctx* ctx, int n, double sign, double dt) {
-    const int N = n * n;
-    pos.resize(2 * N);
-    for (int i = 0; i < N; ++i) {
-      pos[i] = (i % n + 0.5 + 0.2 * ((i * 7) % 5 - 2) / 5.0) / n;
-      pos[N + i] = (i / n + 0.5 + 0.2 * ((i * 3) % 7 - 3) / 7.0) / n;
-    }
-    h.assign(N, 1.3 / n);
-    one.assign(N, 1.0);
-    zero.assign(N, 0.0);
-    m.assign(N, sign / N);
-    e.resize(N);
-    b.resize(N);
-    for (int i = 0; i < N; ++i) {
-      e[i] = 1.0 + 0.1 * (i % 11);
-      b[i] = (1.0 + (i * 13) % 17) / N;
-    }
-    rt_step_inputs in{dt, 1.0, 1.0, 0.0, RT_LIMITER_NONE, 2.0, m.data(), one.data(), one.data(),
-                      one.data(), zero.data(), e.data(), one.data(), zero.data(), zero.data()};
-    rt_amg_opts o{1, 256, 0.25, 1, 1, RT_SMOOTHER_L1_JACOBI, 2, 1, RT_PROLONG_PIECEWISE};
-    if (rt_build_neighbors(ctx, 2, N, N, pos.data(), h.data(), RT_KERNEL_CUBIC_SPLINE, &nb) < 0 ||
-        rt_assemble(ctx, nb, &in, &o, &A) < 0) {
-      printf("FAILED set-up: %s\n", rt_last_error());
-      exit(1);
-    }
-  }
-  ~System() {
-    rt_matrix_free(A);
-    rt_neighbors_free(nb);
-  }
-};
-
 void solves(rt_ctx* ctx) {
   for (double sign : {1.0, -1.0}) {
-    System S(ctx, 18, sign, 1e-3);
-    const int N = (int)S.b.size();
+    Lattice S(ctx, 18, Lattice::opts(1, 1, 1), sign);
+    const int N = S.N;
     for (int mixed = 0; mixed < 2; ++mixed) {
       std::vector<double> got[2];
       rt_solve_stats st[2];
