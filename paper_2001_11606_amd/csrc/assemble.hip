@@ -418,7 +418,7 @@ int assemble(rt_ctx* ctx, const rt_neighbors* nb, const rt_step_inputs* in, rt_m
   if (L.pair.on && pairs) return assemble_pairs(ctx, A);
   RT_CHECK(assemble_csr(ctx, A, true));
   if (L.pair.on) {   // re-assembled with other options; only now are there CSR rows
-    L.pair.on = false;
+    L.pair = PairForm();
     tiles = true;
   }
   if (tiles) RT_CHECK(build_tiles(ctx, L));

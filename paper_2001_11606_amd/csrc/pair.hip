@@ -610,7 +610,10 @@ int build_pairs(rt_ctx* ctx, const rt_neighbors* nb, Level& L) {
   RT_CHECK(ctx->sync_read(totals.p, sizeof(PairTotals)));
   PairTotals tot;
   std::memcpy(&tot, ctx->host, sizeof(tot));
-  if (tot.bad || tot.ext >= INT32_MAX) return RT_OK;
+  if (tot.bad || tot.ext >= INT32_MAX) {
+    P = PairForm();   // the columns and offsets go back to the cache
+    return RT_OK;
+  }
   L.n = n;
   L.nnz = tot.nnz;
   L.max_row = tot.max_row;

@@ -32,6 +32,17 @@ void failed_reassembly(rt_ctx* ctx) {
   cpuhip_malloc_max = SIZE_MAX;
   expect(S.solve(ctx, RT_PREC_FP64, &x) == RT_OK, "FP64 solve after it");
 }
+
+// a matrix re-assembled with a hierarchy gives the pair form's memory back
+void left_pair_form(rt_ctx* ctx) {
+  Lattice S(ctx, 18, Lattice::opts(1, 1, 1));
+  const rt::PairForm& P = S.A->levels[0].pair;
+  expect(P.on && P.col.p && P.val64.p && P.val32.p, "assembled in pair form");
+  expect(S.assemble(ctx, Lattice::opts(8, 1, 1)) == RT_OK && !P.on, "re-assembled with a hierarchy");
+  expect(!P.col.p && !P.row.p && !P.xcol.p && !P.in_pos.p && !P.val64.p && !P.val32.p && !P.sum64.p,
+         "no buffers of the pair form");
+  expect(S.solve(ctx, RT_PREC_MIXED, &x) == RT_OK, "mixed solve after it");
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -39,6 +50,7 @@ int main(int argc, char** argv) {
   if (argc < 2 || rt_create(&ctx, 0, nullptr) < 0) return 1;
   const std::string what = argv[1];
   if (what == "failed_reassembly") failed_reassembly(ctx);
+  else if (what == "left_pair_form") left_pair_form(ctx);
   else return 1;
   rt_destroy(ctx);
   printf(failures ? "%d failures\n" : "all ok\n", failures);

@@ -1,0 +1,42 @@
+"""Device memory of matrices whose tiles do not fit the pair form: CSR rows and
+the 16-bit columns of the tiled form, nothing of the pair form."""
+import pytest
+
+from gpu_common import gpu_system, say
+from test_gpu_pair import _crowded
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def ctx():
+    from paper_2001_11606_amd import rt
+    with rt.Context(0) as c:
+        yield c
+
+
+def _held(ctx, amg):
+    """Bytes held by a matrix of the crowded problem, and its entries."""
+    import torch
+    from paper_2001_11606_amd import rt
+    dp, nb, A = gpu_system(ctx, _crowded(3600), amg=rt.amg_opts(max_levels=1, build_fp32=0))
+    ctx.free(A)
+    rt.rt_release_cached(ctx.handle)
+    free = torch.cuda.mem_get_info()[0]
+    A = ctx.assemble(nb, dp.arrays, dp.dt, dp.c, dp.a, dp.opacity_exponent, dp.limiter,
+                     dp.limiter_k, amg=amg)
+    torch.cuda.synchronize()
+    rt.rt_release_cached(ctx.handle)
+    held = free - torch.cuda.mem_get_info()[0]
+    nnz = ctx.matrix_info(A).nnz
+    ctx.free(A, nb)
+    return held, nnz
+
+
+def test_untiled_matrix_holds_no_pair_form(ctx):
+    from paper_2001_11606_amd import rt
+    plain, nnz = _held(ctx, rt.amg_opts(max_levels=1, build_fp32=0, tiled_spmv=0))
+    tried, _ = _held(ctx, rt.amg_opts(max_levels=1, build_fp32=0, tiled_spmv=1))
+    say(f"[memory] nnz={nnz} plain {plain} tried {tried}")
+    assert nnz > 4_000_000   # the pair form's columns take 2 bytes an entry as well
+    assert tried - plain <= 2 * nnz + (6 << 20)   # the tiled form's columns, and rounding

@@ -23,7 +23,7 @@ def unit():
     return exe
 
 
-CHECKS = ["failed_reassembly"]
+CHECKS = ["failed_reassembly", "left_pair_form"]
 
 
 @pytest.mark.parametrize("check", CHECKS)
