@@ -36,9 +36,10 @@ void failed_reassembly(rt_ctx* ctx) {
 // a matrix re-assembled with a hierarchy gives the pair form's memory back
 void left_pair_form(rt_ctx* ctx) {
   Lattice S(ctx, 18, Lattice::opts(1, 1, 1));
-  const rt::PairForm& P = S.A->levels[0].pair;
-  expect(P.on && P.col.p && P.val64.p && P.val32.p, "assembled in pair form");
-  expect(S.assemble(ctx, Lattice::opts(8, 1, 1)) == RT_OK && !P.on, "re-assembled with a hierarchy");
+  auto pair = [&]() -> const rt::PairForm& { return S.A->levels[0].pair; };   // levels may move
+  expect(pair().on && pair().col.p && pair().val64.p && pair().val32.p, "assembled in pair form");
+  expect(S.assemble(ctx, Lattice::opts(8, 1, 1)) == RT_OK && !pair().on, "re-assembled with a hierarchy");
+  const rt::PairForm& P = pair();
   expect(!P.col.p && !P.row.p && !P.xcol.p && !P.in_pos.p && !P.val64.p && !P.val32.p && !P.sum64.p,
          "no buffers of the pair form");
   expect(S.solve(ctx, RT_PREC_MIXED, &x) == RT_OK, "mixed solve after it");
