@@ -65,18 +65,19 @@ __device__ __forceinline__ bool pair_insert(int32_t c, int* keys, unsigned long 
   return false;
 }
 
-// Exclusive prefix sum of one int per thread over the block; *total: the sum.
-__device__ __forceinline__ int block_prefix(int v, int* wsum, int* total) {
+// Exclusive prefix sum of one value per thread over the block; *total: the sum.
+template <typename T>
+__device__ __forceinline__ T block_prefix(T v, T* wsum, T* total) {
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  int incl = v;
+  T incl = v;
   for (int o = 1; o < kWave; o <<= 1) {
-    const int u = __shfl_up(incl, o);
+    const T u = __shfl_up(incl, o);
     if (lane >= o) incl += u;
   }
   __syncthreads();
   if (lane == kWave - 1) wsum[w] = incl;
   __syncthreads();
-  int base = 0, all = 0;
+  T base = 0, all = 0;
   for (int q = 0; q < (int)(blockDim.x / kWave); ++q) {
     if (q < w) base += wsum[q];
     all += wsum[q];
@@ -284,11 +285,11 @@ constexpr int kScanThreads = 1024;
 __global__ void __launch_bounds__(kScanThreads)
 k_pair_scan(int64_t nt, const PairStat* __restrict__ stat, int64_t* __restrict__ xoff,
             PairTotals* __restrict__ out) {
-  __shared__ int wsum[kScanThreads / kWave];
+  __shared__ int64_t wsum[kScanThreads / kWave];   // a sum past 32 bits ends the pair form
   __shared__ double red[kScanThreads / kWave];
   const int64_t per = (nt + kScanThreads - 1) / kScanThreads;
   const int64_t a = threadIdx.x * per, b = a + per < nt ? a + per : nt;
-  int ext = 0;
+  int64_t ext = 0;
   double distinct = 0, nnz = 0, max_ext = 0, max_row = 0, bad = 0;   // whole numbers below 2^53
   for (int64_t k = a; k < b; ++k) {
     const PairStat s = stat[k];
@@ -299,7 +300,7 @@ k_pair_scan(int64_t nt, const PairStat* __restrict__ stat, int64_t* __restrict__
     max_row = fmax(max_row, (double)s.max_row);
     bad = fmax(bad, (double)s.bad);
   }
-  int total = 0;
+  int64_t total = 0;
   int64_t o = block_prefix(ext, wsum, &total);
   for (int64_t k = a; k < b; ++k) {
     xoff[k] = o;
