@@ -419,7 +419,7 @@ int assemble(rt_ctx* ctx, const rt_neighbors* nb, const rt_step_inputs* in, rt_m
   RT_CHECK(assemble_csr(ctx, A, true));
   if (L.pair.on) {   // re-assembled with other options; only now are there CSR rows
     L.pair = PairForm();
-    tiles = true;
+    tiles = A->amg.tiled_spmv != 0;
   }
   if (tiles) RT_CHECK(build_tiles(ctx, L));
   return RT_OK;

@@ -44,6 +44,27 @@ void left_pair_form(rt_ctx* ctx) {
          "no buffers of the pair form");
   expect(S.solve(ctx, RT_PREC_MIXED, &x) == RT_OK, "mixed solve after it");
 }
+
+// a matrix in pair form re-assembled untiled is untiled
+void left_untiled(rt_ctx* ctx) {
+  std::vector<double> want;
+  for (int tiled : {1, 0}) {
+    Lattice S(ctx, 18, Lattice::opts(1, 1, 1));
+    rt_matrix_info info{};
+    expect(S.solve(ctx, RT_PREC_FP64, tiled ? &want : &x) == RT_OK, "solve in pair form");
+    expect(S.assemble(ctx, Lattice::opts(tiled ? 8 : 1, 1, tiled)) == RT_OK &&
+               rt_matrix_get_info(S.A, &info) == RT_OK &&
+               (info.level_tile_cols[0] > 0) == (tiled != 0),
+           tiled ? "tiled with a hierarchy" : "untiled on request");
+    expect(S.solve(ctx, RT_PREC_FP64, &x) == RT_OK, "solve after it");
+    double d = 0.0, w = 0.0;
+    for (int i = 0; i < S.N; ++i) {
+      d = std::fmax(d, std::fabs(x[i] - want[i]));
+      w = std::fmax(w, std::fabs(want[i]));
+    }
+    expect(d <= 1e-11 * w, "the same solution");   // both solves stop at 1e-12 ||b||
+  }
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -52,6 +73,7 @@ int main(int argc, char** argv) {
   const std::string what = argv[1];
   if (what == "failed_reassembly") failed_reassembly(ctx);
   else if (what == "left_pair_form") left_pair_form(ctx);
+  else if (what == "left_untiled") left_untiled(ctx);
   else return 1;
   rt_destroy(ctx);
   printf(failures ? "%d failures\n" : "all ok\n", failures);

@@ -41,7 +41,7 @@ def unit(library):
     return _build("handles")
 
 
-CHECKS = ["failed_reassembly", "left_pair_form"]
+CHECKS = ["failed_reassembly", "left_pair_form", "left_untiled"]
 
 
 @pytest.mark.parametrize("check", CHECKS)
