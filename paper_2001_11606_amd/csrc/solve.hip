@@ -215,7 +215,8 @@ k_start(int npr, const double* __restrict__ pr, const double* __restrict__ pc, i
   else bb = s[S_BB];
   const double rr = v.a, cw = v.c, thr2 = t.tol2 * bb;
   const bool mis = mismatch && *mismatch != 0;
-  const bool done = rr <= thr2 && !(cw > t.cwthr);
+  // (a residual that is not a number ends refinements, not the FP64 loop)
+  const bool done = (t.inner_tol > 0.0 ? !(rr > thr2) : rr <= thr2) && !(cw > t.cwthr);
   s[S_RR] = s[S_RR0] = rr;
   s[S_CW] = s[S_CW0] = cw;
   s[S_MIS] = mis ? 1.0 : 0.0;

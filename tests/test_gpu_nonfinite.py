@@ -64,3 +64,20 @@ def test_csr_rows_infinite_entry(ctx, name):
     from paper_2001_11606_amd import rt
     _check(ctx, CASES[name](), rt.amg_opts(max_levels=8, coarse_size=16),
            shapes=(-1, 0, 1, 2, 3, 4, 5, 6, 8, 13, 16))
+
+
+@pytest.mark.parametrize("levels", [1, 8])
+def test_guess_that_is_not_a_number(ctx, levels):
+    """No iterations and no refinements on a residual that is not a number."""
+    import torch
+    from paper_2001_11606_amd import rt
+    prob = synth.config1(n=21)
+    dp, nb, A = gpu_system(ctx, prob, amg=rt.amg_opts(max_levels=levels, coarse_size=16))
+    b = torch.ones(prob.n_interior, dtype=torch.float64, device=ctx.device)
+    for prec in (0, 1):
+        x = torch.ones_like(b)
+        x[7] = float("nan")
+        _, st = ctx.solve(A, b, x, rt.solve_opts(prec, 0, 1e-10, 200))
+        assert st.iterations == 0 and st.refinements == 0 and np.isnan(st.rel_residual), prec
+        assert torch.isnan(x[7]) and int((x == 1.0).sum()) == prob.n_interior - 1
+    ctx.free(A, nb)
