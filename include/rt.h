@@ -271,7 +271,7 @@ void rt_matrix_free(rt_matrix* A);
  * A matrix assembled with max_levels 1 and tiled_spmv 1 keeps only the entries
  * right of the diagonal (each pair once); its tiled shapes run on that form, E
  * being the groups of four pairs a lane has in work, and its CSR rows are made
- * when a plain shape, rt_matrix_tune or an export first asks for them.
+ * when a plain shape or rt_matrix_tune first asks for them.
  * rt_spmv_shapes writes the (G, E, tiled) of up to max shapes (any pointer
  * may be NULL) and returns how many exist.  rt_matrix_tune times the Krylov-loop product on every
  * level of A with every shape, in FP64 and, when A holds FP32 copies, FP32,

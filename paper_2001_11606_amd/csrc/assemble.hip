@@ -288,32 +288,59 @@ int pick_group(double avg_row) {
   return 4;
 }
 
-// Row pointers, columns and values of the fine level as CSR rows; with_diag:
-// also the diagonal and ghost couplings (a level in pair form has them already).
-int assemble_csr(rt_ctx* ctx, rt_matrix* A, bool with_diag) {
+// Row pointers and room for the columns of the fine level's CSR rows; max_row
+// may be NULL.
+int csr_structure(rt_ctx* ctx, const rt_neighbors* nb, DevBuf<int64_t>* rp, DevBuf<int32_t>* col,
+                  int64_t* nnz, int64_t* max_row) {
   hipStream_t st = ctx->stream;
+  const int64_t nin = nb->n_interior;
+  RT_CHECK(rp->reserve(nin + 1));
+  DevBuf<int64_t> cnt;
+  RT_CHECK(cnt.reserve(nin + 1));
+  RT_CHECK_HIP(hipMemsetAsync(cnt.p + nin, 0, sizeof(int64_t), st));
+  if (nin > 0) {
+    hipLaunchKernelGGL(k_int_counts, dim3(grid_for(nin)), dim3(kBlock), 0, st, nin,
+                       nb->n_int_nbrs.p, cnt.p);
+    RT_LAUNCH_CHECK();
+  }
+  RT_CHECK((scan<int64_t, int64_t>(ctx, cnt.p, rp->p, nin + 1, false)));
+  RT_CHECK(ctx->sync_read(rp->p + nin, sizeof(int64_t)));
+  std::memcpy(nnz, ctx->host, sizeof(int64_t));
+  if (max_row) RT_CHECK(max_nonneg<int64_t>(ctx, cnt.p, nin, max_row));
+  return col->reserve(*nnz);
+}
+
+// Columns and values of the rows, and the rest of aa's outputs.
+int csr_fill(rt_ctx* ctx, const rt_matrix* A, const AsmArgs& aa) {
   const rt_neighbors* nb = A->nb;
   const int64_t n = nb->n_total, nin = nb->n_interior;
+  if (nin == 0) return RT_OK;
+  const int G = pick_group((double)nb->npairs / (double)n);
+  const int per = (grid_for(nin * (int64_t)G, kBlock) + kXcd - 1) / kXcd;
+  const int grid = per * kXcd;
+#define RT_ASM(D_, G_)                                                                         \
+  hipLaunchKernelGGL((k_assemble<D_, G_, 4>), dim3(grid), dim3(kBlock), 0, ctx->stream, nin, n, \
+                     nb->kernel, A->dt, A->c, aa, per)
+  if (nb->dim == 3) {
+    if (G == 64) RT_ASM(3, 64); else if (G == 16) RT_ASM(3, 16);
+    else if (G == 8) RT_ASM(3, 8); else RT_ASM(3, 4);
+  } else {
+    if (G == 64) RT_ASM(2, 64); else if (G == 16) RT_ASM(2, 16);
+    else if (G == 8) RT_ASM(2, 8); else RT_ASM(2, 4);
+  }
+#undef RT_ASM
+  RT_LAUNCH_CHECK();
+  return RT_OK;
+}
+
+// The fine level's CSR rows, kept in the level; with_diag: also the diagonal and
+// ghost couplings (a level in pair form has them already).
+int assemble_csr(rt_ctx* ctx, rt_matrix* A, bool with_diag) {
+  const rt_neighbors* nb = A->nb;
+  const int64_t nin = nb->n_interior;
   Level& L = A->levels[0];
   const bool new_rows = !L.csr_rows;
-  if (new_rows) {
-    RT_CHECK(L.rp.reserve(nin + 1));
-    DevBuf<int64_t> cnt;
-    RT_CHECK(cnt.reserve(nin + 1));
-    RT_CHECK_HIP(hipMemsetAsync(cnt.p + nin, 0, sizeof(int64_t), st));
-    if (nin > 0) {
-      hipLaunchKernelGGL(k_int_counts, dim3(grid_for(nin)), dim3(kBlock), 0, st, nin,
-                         nb->n_int_nbrs.p, cnt.p);
-      RT_LAUNCH_CHECK();
-    }
-    RT_CHECK((scan<int64_t, int64_t>(ctx, cnt.p, L.rp.p, nin + 1, false)));
-    RT_CHECK(ctx->sync_read(L.rp.p + nin, sizeof(int64_t)));
-    int64_t nnz = 0;
-    std::memcpy(&nnz, ctx->host, sizeof(int64_t));
-    L.nnz = nnz;
-    RT_CHECK(max_nonneg<int64_t>(ctx, cnt.p, nin, &L.max_row));
-    RT_CHECK(L.col.reserve(nnz));
-  }
+  if (new_rows) RT_CHECK(csr_structure(ctx, nb, &L.rp, &L.col, &L.nnz, &L.max_row));
   RT_CHECK(L.val64.reserve(L.nnz + kSpmvPad));
   const bool fp32 = with_diag ? A->amg.build_fp32 != 0 : A->has_fp32;
   if (with_diag)
@@ -324,29 +351,12 @@ int assemble_csr(rt_ctx* ctx, rt_matrix* A, bool with_diag) {
       for (auto* b : {&L.diag32, &L.dinv32, &L.sinv32}) RT_CHECK(b->reserve(nin));
   }
   A->has_fp32 = fp32;   // the buffers exist
-  if (nin > 0) {
-    AsmArgs aa{nb->ptr.p, L.rp.p, nb->idx.p, nb->sp4.p, A->VD.p, A->sa.p,
-               A->f.p, A->Eall.p, new_rows ? L.col.p : nullptr, L.val64.p,
-               with_diag ? L.diag64.p : nullptr, L.dinv64.p, L.sinv64.p, A->g.p,
-               fp32 ? L.val32.p : nullptr, fp32 ? L.diag32.p : nullptr,
-               fp32 ? L.dinv32.p : nullptr, fp32 ? L.sinv32.p : nullptr, nb->box};
-    const double avg = nin ? (double)nb->npairs / (double)n : 0.0;
-    const int G = pick_group(avg);
-    const int per = (grid_for(nin * (int64_t)G, kBlock) + kXcd - 1) / kXcd;
-    const int grid = per * kXcd;
-#define RT_ASM(D_, G_)                                                                           \
-  hipLaunchKernelGGL((k_assemble<D_, G_, 4>), dim3(grid), dim3(kBlock), 0, st, nin, n, nb->kernel, \
-                     A->dt, A->c, aa, per)
-    if (nb->dim == 3) {
-      if (G == 64) RT_ASM(3, 64); else if (G == 16) RT_ASM(3, 16);
-      else if (G == 8) RT_ASM(3, 8); else RT_ASM(3, 4);
-    } else {
-      if (G == 64) RT_ASM(2, 64); else if (G == 16) RT_ASM(2, 16);
-      else if (G == 8) RT_ASM(2, 8); else RT_ASM(2, 4);
-    }
-#undef RT_ASM
-    RT_LAUNCH_CHECK();
-  }
+  RT_CHECK(csr_fill(ctx, A, AsmArgs{nb->ptr.p, L.rp.p, nb->idx.p, nb->sp4.p, A->VD.p, A->sa.p,
+                                    A->f.p, A->Eall.p, new_rows ? L.col.p : nullptr, L.val64.p,
+                                    with_diag ? L.diag64.p : nullptr, L.dinv64.p, L.sinv64.p,
+                                    A->g.p, fp32 ? L.val32.p : nullptr,
+                                    fp32 ? L.diag32.p : nullptr, fp32 ? L.dinv32.p : nullptr,
+                                    fp32 ? L.sinv32.p : nullptr, nb->box}));
   L.csr_rows = L.csr_vals = true;
   return RT_OK;
 }
@@ -429,26 +439,46 @@ int ensure_csr(rt_ctx* ctx, rt_matrix* A) {
   return A->levels[0].csr_vals ? RT_OK : assemble_csr(ctx, A, false);
 }
 
+int csr_view(rt_ctx* ctx, const rt_matrix* A, bool fp32, CsrRows* tmp, CsrView* out) {
+  const Level& L = A->levels[0];
+  if (L.csr_vals) {
+    *out = CsrView{L.rp.p, L.col.p, L.val64.p, L.val32.p};
+    return RT_OK;
+  }
+  const rt_neighbors* nb = A->nb;
+  int64_t nnz = 0;
+  RT_CHECK(csr_structure(ctx, nb, &tmp->rp, &tmp->col, &nnz, nullptr));
+  RT_CHECK(tmp->val64.reserve(nnz));
+  if (fp32) RT_CHECK(tmp->val32.reserve(nnz));
+  RT_CHECK(csr_fill(ctx, A, AsmArgs{nb->ptr.p, tmp->rp.p, nb->idx.p, nb->sp4.p, A->VD.p, A->sa.p,
+                                    A->f.p, A->Eall.p, tmp->col.p, tmp->val64.p, nullptr, nullptr,
+                                    nullptr, nullptr, fp32 ? tmp->val32.p : nullptr, nullptr,
+                                    nullptr, nullptr, nb->box}));
+  *out = CsrView{tmp->rp.p, tmp->col.p, tmp->val64.p, tmp->val32.p};
+  return RT_OK;
+}
+
 int matrix_export(rt_ctx* ctx, const rt_matrix* A, int64_t* urp, int32_t* ucol, double* uval,
                   double* ug) {
   hipStream_t st = ctx->stream;
   const rt_neighbors* nb = A->nb;
   const Level& L = A->levels[0];
   const int64_t nin = A->n;
-  RT_CHECK(ensure_csr(ctx, const_cast<rt_matrix*>(A)));   // made on demand for a pair-form level
+  CsrRows tmp;
+  CsrView R;
+  RT_CHECK(csr_view(ctx, A, false, &tmp, &R));
   DevBuf<int64_t> cnt;
   RT_CHECK(cnt.reserve(nin + 1));
   RT_CHECK_HIP(hipMemsetAsync(cnt.p + nin, 0, sizeof(int64_t), st));
   if (nin > 0) {
     hipLaunchKernelGGL(k_export_counts, dim3(grid_for(nin)), dim3(kBlock), 0, st, nin,
-                       nb->iperm.p, L.rp.p, cnt.p);
+                       nb->iperm.p, R.rp, cnt.p);
     RT_LAUNCH_CHECK();
   }
   RT_CHECK((scan<int64_t, int64_t>(ctx, cnt.p, urp, nin + 1, false)));
   if (nin == 0) return RT_OK;
   hipLaunchKernelGGL(k_export_scatter, dim3(grid_for(nin)), dim3(kBlock), 0, st, nin,
-                     nb->perm.p, L.rp.p, L.col.p, L.val64.p, L.diag64.p, A->g.p, urp, ucol, uval,
-                     ug);
+                     nb->perm.p, R.rp, R.col, R.val64, L.diag64.p, A->g.p, urp, ucol, uval, ug);
   RT_LAUNCH_CHECK();
   RT_CHECK((row_sort<int32_t, double>(ctx, urp, ucol, uval, nin)));
   RT_CHECK_HIP(hipStreamSynchronize(st));

@@ -439,8 +439,23 @@ int assemble_pairs(rt_ctx* ctx, rt_matrix* A);
 int pair_resid(rt_ctx* ctx, const Level& L, const double* x, const double* b, double* r,
                float* r32, float* w32, double* part, double* pmax, int* nparts, int shape,
                const int32_t* tprob = nullptr, const int32_t* skip = nullptr);
-// the CSR form of a level in pair form, made on demand (assemble.hip)
+// the CSR form of a level in pair form, made on demand and kept (assemble.hip)
 int ensure_csr(rt_ctx* ctx, rt_matrix* A);
+// the fine level's CSR rows for a call that only reads the matrix: the level's
+// own where it has them, else made in tmp (fp32: with the FP32 values)
+struct CsrRows {
+  DevBuf<int64_t> rp;
+  DevBuf<int32_t> col;
+  DevBuf<double> val64;
+  DevBuf<float> val32;
+};
+struct CsrView {
+  const int64_t* rp = nullptr;
+  const int32_t* col = nullptr;
+  const double* val64 = nullptr;
+  const float* val32 = nullptr;
+};
+int csr_view(rt_ctx* ctx, const rt_matrix* A, bool fp32, CsrRows* tmp, CsrView* out);
 
 // neighbours
 int build_neighbors(rt_ctx* ctx, int dim, int64_t n_total, int64_t n_interior,

@@ -65,6 +65,34 @@ void left_untiled(rt_ctx* ctx) {
     expect(d <= 1e-11 * w, "the same solution");   // both solves stop at 1e-12 ||b||
   }
 }
+
+// an export only reads the matrix
+void export_reads(rt_ctx* ctx) {
+  Lattice S(ctx, 18, Lattice::opts(1, 1, 1));
+  const rt_matrix* A = S.A;
+  rt_matrix_info info{};
+  rt_matrix_get_info(A, &info);
+  std::vector<int64_t> rp[2];
+  std::vector<int32_t> col[2];
+  std::vector<double> val[2], g[2];
+  for (int k = 0; k < 2; ++k) {   // made for the call, then with the level's own rows
+    rp[k].resize(S.N + 1);
+    col[k].resize(info.nnz);
+    val[k].resize(info.nnz);
+    g[k].resize(S.N);
+    if (k == 1) {
+      rt_matrix_set_spmv_shape(S.A, 0, RT_PREC_FP64, 0);
+      expect(S.solve(ctx, RT_PREC_FP64, &x) == RT_OK && A->levels[0].csr_vals, "a plain shape");
+    }
+    expect(rt_matrix_export(ctx, A, rp[k].data(), col[k].data(), val[k].data(), g[k].data()) == RT_OK,
+           "export");
+    if (k == 0)
+      expect(!A->levels[0].csr_rows && !A->levels[0].csr_vals && !A->levels[0].rp.p &&
+                 !A->levels[0].col.p && !A->levels[0].val64.p,
+             "the matrix is as it was");
+  }
+  expect(rp[0] == rp[1] && col[0] == col[1] && val[0] == val[1] && g[0] == g[1], "the same entries");
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -74,6 +102,7 @@ int main(int argc, char** argv) {
   if (what == "failed_reassembly") failed_reassembly(ctx);
   else if (what == "left_pair_form") left_pair_form(ctx);
   else if (what == "left_untiled") left_untiled(ctx);
+  else if (what == "export_reads") export_reads(ctx);
   else return 1;
   rt_destroy(ctx);
   printf(failures ? "%d failures\n" : "all ok\n", failures);
