@@ -1317,7 +1317,7 @@ int level_vectors(Level& L, bool fp32, int cycle) {
     if (cycle >= 2)
       for (auto* b : {&L.wr32, &L.wx32}) RT_CHECK(b->reserve(L.n));
     if (cycle == 3) RT_CHECK(L.kw32.reserve(L.n));
-    RT_CHECK(L.val32.reserve(L.nnz + kSpmvPad));
+    if (!L.pair.on) RT_CHECK(L.val32.reserve(L.nnz + kSpmvPad));   // that of CSR rows
     RT_CHECK(L.diag32.reserve(L.n));
   }
   return RT_OK;

@@ -38,6 +38,8 @@ void left_pair_form(rt_ctx* ctx) {
   Lattice S(ctx, 18, Lattice::opts(1, 1, 1));
   auto pair = [&]() -> const rt::PairForm& { return S.A->levels[0].pair; };   // levels may move
   expect(pair().on && pair().col.p && pair().val64.p && pair().val32.p, "assembled in pair form");
+  const rt::Level& F = S.A->levels[0];
+  expect(!F.rp.p && !F.col.p && !F.val64.p && !F.val32.p, "no buffers of CSR rows");
   expect(S.assemble(ctx, Lattice::opts(8, 1, 1)) == RT_OK && !pair().on, "re-assembled with a hierarchy");
   const rt::PairForm& P = pair();
   expect(!P.col.p && !P.row.p && !P.xcol.p && !P.in_pos.p && !P.val64.p && !P.val32.p && !P.sum64.p,
