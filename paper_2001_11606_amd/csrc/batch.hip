@@ -1140,7 +1140,7 @@ int rt_batch_create(rt_ctx* ctx, int nprob, rt_matrix* const* mats, rt_batch** o
     return RT_E_ARG;
   }
   // matrices in pair form make a batch in pair form; else every matrix's CSR
-  // rows are copied (made on demand where a matrix has the pair form)
+  // rows are copied (made for the copy where a matrix has the pair form)
   bool pair = true;
   std::vector<int64_t> group_off(nprob + 1, 0), ext_off(nprob + 1, 0);
   for (int p = 0; p < nprob; ++p) {
@@ -1237,8 +1237,10 @@ int rt_batch_create(rt_ctx* ctx, int nprob, rt_matrix* const* mats, rt_batch** o
   for (int p = 0; p < nprob; ++p) {
     rt_matrix* A = mats[p];
     const Level& S = A->levels[0];
-    if (!pair) RT_B(ensure_csr(ctx, A));
-    CopyArgs ca{pair ? nullptr : S.rp.p, S.diag64.p, S.dinv64.p, A->V.p, A->sa.p, A->f.p, A->rho.p, A->cv.p,
+    CsrRows made;   // released in stream order
+    CsrView rows;
+    if (!pair) RT_B(csr_view(ctx, A, fp32, &made, &rows));
+    CopyArgs ca{rows.rp, S.diag64.p, S.dinv64.p, A->V.p, A->sa.p, A->f.p, A->rho.p, A->cv.p,
                 A->m.p, A->e_prev.p, A->E_prev.p, A->Qe.p, A->QE.p, A->g.p,
                 fp32 ? S.diag32.p : nullptr, fp32 ? S.dinv32.p : nullptr, A->nb->perm.p,
                 A->n, B->row_off[p + 1] - B->row_off[p], B->row_off[p], nnz_off[p],
@@ -1264,11 +1266,11 @@ int rt_batch_create(rt_ctx* ctx, int nprob, rt_matrix* const* mats, rt_batch** o
       L.tile_cols_total += S.tile_cols_total;
     } else if (S.nnz > 0) {
       hipLaunchKernelGGL(k_b_copy_cols, dim3(grid_for(S.nnz)), dim3(kBlock), 0, st, S.nnz,
-                         S.col.p, nnz_off[p], B->row_off[p], L.col.p);
+                         rows.col, nnz_off[p], B->row_off[p], L.col.p);
       if (hipGetLastError() != hipSuccess ||
-          hipMemcpyAsync(L.val64.p + nnz_off[p], S.val64.p, sizeof(double) * S.nnz,
+          hipMemcpyAsync(L.val64.p + nnz_off[p], rows.val64, sizeof(double) * S.nnz,
                          hipMemcpyDeviceToDevice, st) != hipSuccess ||
-          (fp32 && hipMemcpyAsync(L.val32.p + nnz_off[p], S.val32.p, sizeof(float) * S.nnz,
+          (fp32 && hipMemcpyAsync(L.val32.p + nnz_off[p], rows.val32, sizeof(float) * S.nnz,
                                   hipMemcpyDeviceToDevice, st) != hipSuccess)) {
         set_error("rt_batch_create: copy of problem %d failed", p);
         return fail(RT_E_DEVICE);

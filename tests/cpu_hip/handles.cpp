@@ -95,6 +95,36 @@ void export_reads(rt_ctx* ctx) {
   }
   expect(rp[0] == rp[1] && col[0] == col[1] && val[0] == val[1] && g[0] == g[1], "the same entries");
 }
+
+// a batch only reads its matrices
+void batch_reads(rt_ctx* ctx) {
+  Lattice P(ctx, 9, Lattice::opts(1, 1, 1)), H(ctx, 7, Lattice::opts(8, 1, 1));
+  rt_matrix* mats[] = {P.A, H.A};
+  rt_batch* B = nullptr;
+  expect(rt_batch_create(ctx, 2, mats, &B) == RT_OK, "a batch of both forms");
+  const rt::Level& L = P.A->levels[0];
+  expect(L.pair.on && !L.csr_rows && !L.csr_vals && !L.rp.p && !L.col.p && !L.val64.p && !L.val32.p,
+         "the matrix in pair form is as it was");
+  std::vector<double> b(P.b), got(P.N + H.N, 0.25), want;
+  b.insert(b.end(), H.b.begin(), H.b.end());
+  for (int prec : {RT_PREC_FP64, RT_PREC_MIXED}) {
+    rt_solve_opts o{prec, 0, 1e-12, 200, 1e-3, 20, 0.0};
+    got.assign(got.size(), 0.25);
+    expect(rt_batch_solve(ctx, B, b.data(), got.data(), &o, 0, nullptr) == RT_OK, "batched solve");
+    want.clear();
+    for (Lattice* S : {&P, &H}) {
+      expect(S->solve(ctx, prec, &x) == RT_OK, "its own solve");
+      want.insert(want.end(), x.begin(), x.end());
+    }
+    double d = 0.0, w = 0.0;
+    for (size_t i = 0; i < got.size(); ++i) {
+      d = std::fmax(d, std::fabs(got[i] - want[i]));
+      w = std::fmax(w, std::fabs(want[i]));
+    }
+    expect(d <= 1e-11 * w, "the same solution");   // both stop at 1e-12 ||b||
+  }
+  rt_batch_free(B);
+}
 }  // namespace
 
 int main(int argc, char** argv) {
@@ -105,6 +135,7 @@ int main(int argc, char** argv) {
   else if (what == "left_pair_form") left_pair_form(ctx);
   else if (what == "left_untiled") left_untiled(ctx);
   else if (what == "export_reads") export_reads(ctx);
+  else if (what == "batch_reads") batch_reads(ctx);
   else return 1;
   rt_destroy(ctx);
   printf(failures ? "%d failures\n" : "all ok\n", failures);

@@ -41,7 +41,7 @@ def unit(library):
     return _build("handles")
 
 
-CHECKS = ["failed_reassembly", "left_pair_form", "left_untiled", "export_reads"]
+CHECKS = ["failed_reassembly", "left_pair_form", "left_untiled", "export_reads", "batch_reads"]
 
 
 @pytest.mark.parametrize("check", CHECKS)
