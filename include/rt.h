@@ -271,7 +271,9 @@ void rt_matrix_free(rt_matrix* A);
  * A matrix assembled with max_levels 1 and tiled_spmv 1 keeps only the entries
  * right of the diagonal (each pair once); its tiled shapes run on that form, E
  * being the groups of four pairs a lane has in work, and its CSR rows are made
- * when a plain shape or rt_matrix_tune first asks for them.
+ * when a plain shape or rt_matrix_tune first asks for them: by the solve that
+ * runs the shape, or by a re-assembly after the shape was set.  A batch of such
+ * matrices does the same.
  * rt_spmv_shapes writes the (G, E, tiled) of up to max shapes (any pointer
  * may be NULL) and returns how many exist.  rt_matrix_tune times the Krylov-loop product on every
  * level of A with every shape, in FP64 and, when A holds FP32 copies, FP32,
@@ -397,7 +399,10 @@ int rt_matrix_set_cycle_depth(rt_matrix* A, int depth);
  * and a message giving the bytes needed.  The matrix (and its
  * AMG hierarchy) must come from rt_assemble, whose buffers the V-cycle uses;
  * the residual rt_newton_step carries between outer iterations is left as
- * it was.  No per-product timings are recorded (stats->spmv_* are 0).
+ * it was.  No per-product timings are recorded (stats->spmv_* are 0).  It makes
+ * no CSR rows: a plain shape set on a matrix without them (see rt_spmv_shapes)
+ * takes effect once another call has made them; until then the matrix's own
+ * form is multiplied.
  * Every call on one GPU uses the same array and leaves its contents behind:
  * calls that overlap on one GPU (other streams, other contexts or threads)
  * race, and so do calls on one matrix overlapping with rt_solve or

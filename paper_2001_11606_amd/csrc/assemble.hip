@@ -19,6 +19,7 @@
 
 #include "internal.h"
 #include "kernels_sph.h"
+#include "pair.h"
 #include "prim.h"
 #include "reduce.h"
 #include "spmv.h"
@@ -425,7 +426,12 @@ int assemble(rt_ctx* ctx, const rt_neighbors* nb, const rt_step_inputs* in, rt_m
     if (pairs) RT_CHECK(build_pairs(ctx, nb, L));
   }
   L.csr_vals = false;
-  if (L.pair.on && pairs) return assemble_pairs(ctx, A);
+  if (L.pair.on && pairs) {
+    RT_CHECK(assemble_pairs(ctx, A));
+    // the rows of a requested plain shape, which rt_solve_noalloc cannot make
+    const bool rows = wants_rows(L, L.shape64) || (A->has_fp32 && wants_rows(L, L.shape32));
+    return rows ? ensure_csr(ctx, A) : RT_OK;
+  }
   RT_CHECK(assemble_csr(ctx, A, true));
   if (L.pair.on) {   // re-assembled with other options; only now are there CSR rows
     L.pair = PairForm();
@@ -436,7 +442,9 @@ int assemble(rt_ctx* ctx, const rt_neighbors* nb, const rt_step_inputs* in, rt_m
 }
 
 int ensure_csr(rt_ctx* ctx, rt_matrix* A) {
-  return A->levels[0].csr_vals ? RT_OK : assemble_csr(ctx, A, false);
+  Level& L = A->levels[0];
+  if (L.csr_vals) return RT_OK;
+  return A->nb ? assemble_csr(ctx, A, false) : pair_rows(ctx, L, A->has_fp32);
 }
 
 int csr_view(rt_ctx* ctx, const rt_matrix* A, bool fp32, CsrRows* tmp, CsrView* out) {

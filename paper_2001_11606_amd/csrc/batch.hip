@@ -834,6 +834,8 @@ int b_solve(rt_ctx* ctx, rt_batch* B, const rt_solve_opts* o, int graph_k, rt_so
   // the V-cycle when asked for and the batch's depth is above 1 (else Jacobi)
   const bool amg = o->precond == 1 && cycle_depth(B->H.get()) > 1;
   const Level& L = B->L;
+  // a plain shape's rows, before any capture
+  if (wants_rows(L, mixed ? L.shape32 : L.shape64)) RT_CHECK(ensure_csr(ctx, B->H.get()));
   hipLaunchKernelGGL(k_b_fill_i32, dim3(grid_for((int64_t)F_COUNT * np)), dim3(kBlock), 0, st,
                      (int64_t)F_COUNT * np, B->flags.p, 0);
   RT_LAUNCH_CHECK();

@@ -439,7 +439,10 @@ int assemble_pairs(rt_ctx* ctx, rt_matrix* A);
 int pair_resid(rt_ctx* ctx, const Level& L, const double* x, const double* b, double* r,
                float* r32, float* w32, double* part, double* pmax, int* nparts, int shape,
                const int32_t* tprob = nullptr, const int32_t* skip = nullptr);
-// the CSR form of a level in pair form, made on demand and kept (assemble.hip)
+// the CSR rows of a level in pair form from its pairs (pair.hip)
+int pair_rows(rt_ctx* ctx, Level& L, bool fp32);
+// those rows, made on demand and kept: from the neighbour lists, or for a batch,
+// which has none, from the pairs (assemble.hip)
 int ensure_csr(rt_ctx* ctx, rt_matrix* A);
 // the fine level's CSR rows for a call that only reads the matrix: the level's
 // own where it has them, else made in tmp (fp32: with the FP32 values)

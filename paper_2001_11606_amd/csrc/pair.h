@@ -230,6 +230,10 @@ template <> struct PairSel<float> {
 inline bool plain_shape(int shape) {
   return shape >= 0 && shape < kNumSpmvShapes && !kSpmvShapes[shape].tiled;
 }
+// whether a solve that multiplies with this shape needs the CSR rows made
+inline bool wants_rows(const Level& L, int shape) {
+  return L.pair.on && (plain_shape(shape) || plain_shape(resid_shape(L)));
+}
 inline bool pair_serves(const Level& L, int shape) {
   return L.pair.on && (!plain_shape(shape) || !L.csr_vals);
 }

@@ -20,6 +20,7 @@
 // it from both ends with records gathered from global memory.  The diagonal
 // needs the sums of both ends: a product of the pair form with the vector of
 // ones.
+#include <algorithm>
 #include <cstring>
 
 #include "internal.h"
@@ -577,7 +578,75 @@ k_pair_resid(int64_t n, PairIn P, const double* __restrict__ xsum, const double*
   }
 }
 
+// ---- CSR rows from the pair form ------------------------------------------------
+// For levels without neighbour lists (a batch) whose caller asks for a plain
+// shape.  One block per tile; FILL: the entries of both rows of a pair at their
+// rows' next free places (the rows are sorted afterwards), else their numbers.
+// Made once per batch at most, so the rows' counters are global atomics.
+template <bool FILL>
+__global__ void __launch_bounds__(kBlock)
+k_pair_rows(PairArgs A, const double* __restrict__ val, const int64_t* __restrict__ rp,
+            int32_t* __restrict__ cnt, int32_t* __restrict__ col, double* __restrict__ out) {
+  const int64_t t = blockIdx.x, r0 = t * kTileRows, x0 = A.xoff[t];
+  const int ncol = kTileRows + (int)(A.xoff[t + 1] - x0);
+  const int64_t g0 = A.goff[t];
+  const int ng = A.gcnt[t];
+  const double* v = val + 4 * g0;   // two planes: entries 0-1 of every group, entries 2-3
+  for (int g = threadIdx.x; g < ng; g += kBlock) {
+    const int64_t i = r0 + A.row[g0 + g];
+    for (int q = 0; q < 4; ++q) {
+      const int c = A.col[4 * (g0 + g) + q];
+      if (c >= ncol) continue;   // the filling of a row's last group
+      const int64_t j = c < kTileRows ? r0 + c : A.xcol[x0 + c - kTileRows];
+      const int a = atomicAdd(&cnt[i], 1), b = atomicAdd(&cnt[j], 1);
+      if (FILL) {
+        const double w = v[2 * (q < 2 ? g : ng + g) + (q & 1)];
+        col[rp[i] + a] = (int32_t)j;
+        out[rp[i] + a] = w;
+        col[rp[j] + b] = (int32_t)i;
+        out[rp[j] + b] = w;
+      }
+    }
+  }
+}
+
+__global__ void k_pair_to_f32(int64_t n, const double* __restrict__ a, float* __restrict__ b) {
+  const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+  if (i < n) b[i] = (float)a[i];
+}
+
 }  // namespace
+
+int pair_rows(rt_ctx* ctx, Level& L, bool fp32) {
+  hipStream_t st = ctx->stream;
+  const int64_t n = L.n;
+  DevBuf<int32_t> cnt;
+  RT_CHECK(cnt.reserve(n + 1));
+  RT_CHECK(L.rp.reserve(n + 1));
+  RT_CHECK(L.col.reserve(std::max<int64_t>(L.nnz, 1)));
+  RT_CHECK(L.val64.reserve(L.nnz + kSpmvPad));
+  if (fp32) RT_CHECK(L.val32.reserve(L.nnz + kSpmvPad));
+  const dim3 tiles((unsigned)L.pair.ntiles);
+  for (int fill = 0; fill < 2; ++fill) {
+    hipLaunchKernelGGL(k_zero_i32, dim3(grid_for(n + 1)), dim3(kBlock), 0, st, n + 1, cnt.p);
+    if (fill)
+      hipLaunchKernelGGL(k_pair_rows<true>, tiles, dim3(kBlock), 0, st, L.pair.args(),
+                         L.pair.val64.p, L.rp.p, cnt.p, L.col.p, L.val64.p);
+    else
+      hipLaunchKernelGGL(k_pair_rows<false>, tiles, dim3(kBlock), 0, st, L.pair.args(),
+                         L.pair.val64.p, nullptr, cnt.p, nullptr, nullptr);
+    RT_LAUNCH_CHECK();
+    if (!fill) RT_CHECK((scan<int32_t, int64_t>(ctx, cnt.p, L.rp.p, n + 1, false)));
+  }
+  RT_CHECK((row_sort<int32_t, double>(ctx, L.rp.p, L.col.p, L.val64.p, n)));
+  if (fp32) {
+    hipLaunchKernelGGL(k_pair_to_f32, dim3(grid_for(L.nnz)), dim3(kBlock), 0, st, L.nnz, L.val64.p,
+                       L.val32.p);
+    RT_LAUNCH_CHECK();
+  }
+  L.csr_rows = L.csr_vals = true;
+  return RT_OK;
+}
 
 int build_pairs(rt_ctx* ctx, const rt_neighbors* nb, Level& L) {
   hipStream_t st = ctx->stream;

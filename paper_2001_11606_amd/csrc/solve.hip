@@ -826,9 +826,7 @@ int ensure_work(rt_matrix* A, bool mixed) {
 // The CSR rows of a level in pair form, when a plain shape asks for them.
 int ensure_shapes(rt_ctx* ctx, rt_matrix* A, bool mixed) {
   const Level& L = A->levels[0];
-  if (!L.pair.on || !(plain_shape(resid_shape(L)) || plain_shape(mixed ? L.shape32 : L.shape64)))
-    return RT_OK;
-  return ensure_csr(ctx, A);
+  return wants_rows(L, mixed ? L.shape32 : L.shape64) ? ensure_csr(ctx, A) : RT_OK;
 }
 
 // The matrix's own work buffers (after ensure_work)

@@ -101,9 +101,7 @@ int rt_matrix_tune(rt_ctx* ctx, rt_matrix* A, int reps, rt_tune_report* rep) {
     Level& L = A->levels[l];
     r->chosen[l][0] = r->chosen[l][1] = r->chosen[l][2] = -1;
     if (L.n == 0) continue;
-    // the plain shapes' rows (a batch in pair form has none: the pair form serves
-    // every shape)
-    if (L.pair.on && A->nb) RT_CHECK(ensure_csr(ctx, A));
+    if (L.pair.on) RT_CHECK(ensure_csr(ctx, A));   // the plain shapes' rows
     for (int p = 0; p < 3; ++p) {
       if (p == 1 && !A->has_fp32) continue;
       if (p == 2 && (l > 0 || !A->has_fp32)) continue;   // refinement residuals: fine level

@@ -1,6 +1,7 @@
-"""Handles of matrices in pair form (cpu_hip/handles.cpp, one check per test)
-and the offsets of its external columns (cpu_hip/pair_scan.cpp) under the host
-emulation of the kernels with AddressSanitizer."""
+"""Handles of matrices in pair form (cpu_hip/handles.cpp, one check per test),
+the offsets of its external columns (cpu_hip/pair_scan.cpp) and plain shapes on
+batches of them (cpu_hip/batch_shape.cpp) under the host emulation of the
+kernels with AddressSanitizer."""
 import os
 import shutil
 import subprocess
@@ -51,3 +52,7 @@ def test_handles(unit, check):
 
 def test_external_columns_past_32_bits(library):
     _run(_build("pair_scan", without=["pair.hip"]))
+
+
+def test_plain_shape_of_a_batch(library):
+    _run(_build("batch_shape", without=["batch.hip"]))
