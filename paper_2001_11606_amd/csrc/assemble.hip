@@ -447,6 +447,14 @@ int ensure_csr(rt_ctx* ctx, rt_matrix* A) {
   return A->nb ? assemble_csr(ctx, A, false) : pair_rows(ctx, L, A->has_fp32);
 }
 
+void drop_csr(Level& L) {
+  L.rp.release();
+  L.col.release();
+  L.val64.release();
+  L.val32.release();
+  L.csr_rows = L.csr_vals = false;
+}
+
 int csr_view(rt_ctx* ctx, const rt_matrix* A, bool fp32, CsrRows* tmp, CsrView* out) {
   const Level& L = A->levels[0];
   if (L.csr_vals) {

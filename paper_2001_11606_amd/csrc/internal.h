@@ -444,6 +444,7 @@ int pair_rows(rt_ctx* ctx, Level& L, bool fp32);
 // those rows, made on demand and kept: from the neighbour lists, or for a batch,
 // which has none, from the pairs (assemble.hip)
 int ensure_csr(rt_ctx* ctx, rt_matrix* A);
+void drop_csr(Level& L);   // gives them back
 // the fine level's CSR rows for a call that only reads the matrix: the level's
 // own where it has them, else made in tmp (fp32: with the FP32 values)
 struct CsrRows {

@@ -101,7 +101,8 @@ int rt_matrix_tune(rt_ctx* ctx, rt_matrix* A, int reps, rt_tune_report* rep) {
     Level& L = A->levels[l];
     r->chosen[l][0] = r->chosen[l][1] = r->chosen[l][2] = -1;
     if (L.n == 0) continue;
-    if (L.pair.on) RT_CHECK(ensure_csr(ctx, A));   // the plain shapes' rows
+    const bool made = L.pair.on && !L.csr_vals;
+    if (made) RT_CHECK(ensure_csr(ctx, A));   // the plain shapes' rows
     for (int p = 0; p < 3; ++p) {
       if (p == 1 && !A->has_fp32) continue;
       if (p == 2 && (l > 0 || !A->has_fp32)) continue;   // refinement residuals: fine level
@@ -128,6 +129,7 @@ int rt_matrix_tune(rt_ctx* ctx, rt_matrix* A, int reps, rt_tune_report* rep) {
       r->chosen[l][p] = arg;
       (p == 0 ? L.shape64 : p == 1 ? L.shape32 : L.shape_res) = arg;
     }
+    if (made && !wants_rows(L, L.shape64) && !wants_rows(L, L.shape32)) drop_csr(L);
   }
   return RT_OK;
 }

@@ -40,3 +40,34 @@ def test_untiled_matrix_holds_no_pair_form(ctx):
     say(f"[memory] nnz={nnz} plain {plain} tried {tried}")
     assert nnz > 4_000_000   # the pair form's columns take 2 bytes an entry as well
     assert tried - plain <= 2 * nnz + (6 << 20)   # the tiled form's columns, and rounding
+
+
+@pytest.mark.parametrize("batch", [False, True])
+def test_tuning_keeps_rows_only_for_a_plain_choice(ctx, batch):
+    """rt_matrix_tune and rt_batch_tune make CSR rows to time the plain shapes
+    (16 bytes an entry with FP32); 64^3 particles choose the pair form, and the
+    rows are given back."""
+    import torch
+    import synth
+    from paper_2001_11606_amd import rt
+    dp, nb, A = gpu_system(ctx, synth.config3(n=64), amg=rt.amg_opts(max_levels=1))
+    B = rt.rt_batch_create(ctx.handle, [A]) if batch else None
+    nnz = ctx.matrix_info(A).nnz
+    torch.cuda.synchronize()
+    rt.rt_release_cached(ctx.handle)
+    free = torch.cuda.mem_get_info()[0]
+    if batch:
+        rep = rt.rt_batch_tune(ctx.handle, B, 3)
+        chosen = [rep.chosen[0][p] for p in range(3)]
+    else:
+        chosen = ctx.tune(A, 3)["chosen"][0]
+    torch.cuda.synchronize()
+    rt.rt_release_cached(ctx.handle)
+    held = free - torch.cuda.mem_get_info()[0]
+    say(f"[memory] chosen {chosen}, held after the tuner {held}")
+    shapes = rt.rt_spmv_shapes()
+    plain = [c for c in chosen if c >= 0 and not shapes[c][2]]
+    assert held >= 12 * nnz if plain else held <= 4 << 20
+    if B:
+        rt.rt_batch_free(B)
+    ctx.free(A, nb)
