@@ -861,6 +861,27 @@ __global__ void k_axpy1(int64_t n, const T* __restrict__ y, T* __restrict__ x,
   if (i < n) x[i] += y[i];
 }
 
+// out = x as the cycle's products gather it (CycleArgs), d (else NULL) = out: for
+// large plain levels, whose products would form it once per entry (form_x)
+template <typename T>
+__global__ void __launch_bounds__(kBlock)
+k_cycle_x(int64_t n, const T* x, const T* __restrict__ b, const T* __restrict__ s,
+          const CycleArgs<T> Q, T* out, T* __restrict__ d, const int32_t* __restrict__ tp,
+          const int32_t* __restrict__ stop) {
+  if (stop && stop[tp ? tp[blockIdx.x] : 0]) return;
+  const int64_t i = blockIdx.x * (int64_t)kTileRows + threadIdx.x;
+  if (i >= n) return;
+  T v;
+  if (Q.x == CX_SCALED) {
+    v = (Q.f * s[i]) * b[i];
+  } else {
+    const int32_t I = Q.pmap[i];
+    v = x[i] + (I >= 0 ? Q.xc[I] : T(0));
+  }
+  out[i] = v;
+  if (d) d[i] = v;
+}
+
 // bc[I] = sum of b - A x over the members of aggregate I, for a small level
 // (plain shapes): a block per aggregate, 16 lanes per member row, x as the
 // cycle's products gather it (CycleArgs).  One launch where the residual
@@ -1432,6 +1453,27 @@ static int cycle_product(hipStream_t st, Level& L, const T* x, const T* b, T* y,
                                         nullptr, Q);
 }
 
+// Large levels with a plain shape: x that the products would form in their
+// gathers, two or three reads per entry instead of one, goes into buf first (and
+// into d, where steps follow).  An untiled level of 423 | 812 entries a row,
+// 262k rows: a mixed solve 11.1 | 35.2 ms so, 14.6 | 44.6 ms with the gathers; on
+// levels up to kSmallNnz the launch costs more than the reads, and a tile reads
+// each column once.
+template <typename T>
+static int form_x(hipStream_t st, Level& L, const T** x, const T* b, T* buf, CycleArgs<T>* Q,
+                  bool d, const int32_t* tp, const int32_t* sk) {
+  using B = LevelBufs<T>;
+  const int shape = spmv_effective_shape(L, level_shape<T>(L));
+  if (Q->x == CX_PLAIN || kSpmvShapes[shape].tiled || L.nnz <= kSmallNnz) return RT_OK;
+  hipLaunchKernelGGL(k_cycle_x<T>, dim3((unsigned)((L.n + kTileRows - 1) / kTileRows)), dim3(kBlock),
+                     0, st, L.n, *x, b, B::sinv(L), *Q, buf, d ? B::d(L) : nullptr, tp, sk);
+  RT_LAUNCH_CHECK();
+  *x = buf;
+  Q->x = CX_PLAIN;
+  Q->xout = nullptr;   // buf is where it was asked for
+  return RT_OK;
+}
+
 // Smoothing steps first .. S.steps - 1 on level L, x (described by Q: CX_SCALED
 // stands for the step before the first one) to out; the steps between
 // alternate between tmp and out, neither of which may be x's own vector where
@@ -1517,7 +1559,9 @@ static int vcycle_level(rt_ctx* ctx, rt_matrix* A, size_t l, const T* b, T* out,
     CycleArgs<T> Q;
     Q.step = CS_STEP;
     Q.x = CX_SCALED;
-    RT_CHECK(cycle_product<T>(st, L, b, b, out, Q, tp, sk));
+    const T* x = b;
+    RT_CHECK(form_x<T>(st, L, &x, b, t, &Q, false, tp, sk));
+    RT_CHECK(cycle_product<T>(st, L, x, b, out, Q, tp, sk));
     Q.x = CX_PLAIN;
     RT_CHECK(cycle_product<T>(st, L, out, b, t, Q, tp, sk));
     return cycle_product<T>(st, L, t, b, out, Q, tp, sk);
@@ -1536,11 +1580,14 @@ static int vcycle_level(rt_ctx* ctx, rt_matrix* A, size_t l, const T* b, T* out,
   Q.f = (T)S.c2[0];
   const T* x = b;
   if (S.steps > 1) {
+    // (the first of these steps writes t where their number is odd)
+    RT_CHECK(form_x<T>(st, L, &x, b, S.steps % 2 == 0 ? out : t, &Q, true, tp, sk));
     RT_CHECK(cycle_smooth<T>(st, L, S, 1, x, b, out, t, Q, tp, sk));
     x = t;
     Q = CycleArgs<T>();
   } else {
     Q.xout = t;
+    RT_CHECK(form_x<T>(st, L, &x, b, t, &Q, false, tp, sk));
   }
   const int shape = spmv_effective_shape(L, level_shape<T>(L));
   if (!L.smoothed && !kSpmvShapes[shape].tiled && L.nnz <= kSmallNnz) {
@@ -1584,7 +1631,9 @@ static int vcycle_level(rt_ctx* ctx, rt_matrix* A, size_t l, const T* b, T* out,
     Q.xc = B::x(C);
     Q.pmap = L.pmap.p;
   }
-  return cycle_smooth<T>(st, L, S, 0, t, b, r, out, Q, tp, sk);
+  x = t;
+  RT_CHECK(form_x<T>(st, L, &x, b, t, &Q, false, tp, sk));
+  return cycle_smooth<T>(st, L, S, 0, x, b, r, out, Q, tp, sk);
 }
 
 template <typename T>
