@@ -33,7 +33,9 @@ enum SpmvMode {
                   // optionally pmax[block] = max_i |y_i| / (a_ii |x_i|) and
                   // w32 = 1 / (a_ii |x_i|) (see cw_term)
   SP_CYCLE = 3,   // a product of the multigrid cycle (CycleArgs)
+  SP_CYCLE_PLAIN = 4,   // the same where x is CX_PLAIN, without the gathers' cases
 };
+constexpr bool cycle_mode(int mode) { return mode == SP_CYCLE || mode == SP_CYCLE_PLAIN; }
 
 // A product of the multigrid cycle, with the vector passes around it done in
 // its gathers and its last step: x is x[c]; f s[c] b[c], the first smoothing
@@ -169,8 +171,8 @@ k_spmv(int64_t n, int per, const int64_t* __restrict__ rp, const int32_t* __rest
     const int64_t k0 = rp[i], k1 = rp[i + 1];
     const T di = diag[i];
     T bi = 0, si = 0, dv = 0;
-    if (MODE == SP_RESID || MODE == SP_CYCLE) bi = b[i];
-    if (MODE == SP_CYCLE) {
+    if (MODE == SP_RESID || cycle_mode(MODE)) bi = b[i];
+    if (cycle_mode(MODE)) {
       si = s[i];
       if (Q.c1 != T(0) && Q.x != CX_SCALED) dv = Q.d[i];
     }
@@ -198,7 +200,7 @@ k_spmv(int64_t n, int per, const int64_t* __restrict__ rp, const int32_t* __rest
     // Past the row's end the loop multiplies zeros with x of the last column, which
     // is not a number where that x is infinite: then the row's own entries alone.
     // (Selecting in the loop instead: 6 to 11% of a product of 885k rows.)
-    if (MODE != SP_CYCLE && sum != sum) {
+    if (!cycle_mode(MODE) && sum != sum) {
       sum = 0;
       for (int64_t k = k0 + lane; k < k1; k += G) sum += val[k] * x[col[k]];
     }
@@ -330,9 +332,9 @@ k_spmv_tiled(int64_t n, int per, const int64_t* __restrict__ rp, const uint16_t*
   __shared__ int srp[kTileRows + 1];      // row bounds relative to the tile's aligned base
   __shared__ int64_t sbase;
   __shared__ T sy[kTileRows];
-  constexpr bool kNeedB = MODE == SP_RESID || MODE == SP_CYCLE;
+  constexpr bool kNeedB = MODE == SP_RESID || cycle_mode(MODE);
   // the rows' own data, fetched while the columns are staged
-  __shared__ T sdx[(kNeedB ? 3 : 2) + (MODE == SP_CYCLE ? 2 : 0)][kTileRows];
+  __shared__ T sdx[(kNeedB ? 3 : 2) + (cycle_mode(MODE) ? 2 : 0)][kTileRows];
   __shared__ double red[kBlock / kWave];
   constexpr int NG = kBlock / G;   // row groups per block; UNR rows per group in flight
   static_assert(kTileRows % (NG * UNR) == 0, "tile rows must split evenly over the groups");
@@ -355,7 +357,7 @@ k_spmv_tiled(int64_t n, int per, const int64_t* __restrict__ rp, const uint16_t*
       gather_x<T, MODE, false>(own, x, b, s, Q, xo);
       sdx[1][tid] = xo[0];
       if (kNeedB) sdx[2][tid] = b[i];
-      if (MODE == SP_CYCLE) {
+      if (cycle_mode(MODE)) {
         sdx[kNeedB ? 3 : 2][tid] = s[i];
         if (Q.c1 != T(0) && Q.x != CX_SCALED) sdx[kNeedB ? 4 : 3][tid] = Q.d[i];
       }
@@ -440,7 +442,7 @@ k_spmv_tiled(int64_t n, int per, const int64_t* __restrict__ rp, const uint16_t*
     const T xi = sdx[1][tid];
     T bi = 0, si = 0;
     if (kNeedB) bi = sdx[2][tid];
-    if (MODE == SP_CYCLE) si = sdx[kNeedB ? 3 : 2][tid];
+    if (cycle_mode(MODE)) si = sdx[kNeedB ? 3 : 2][tid];
     const T ax = di * xi + sy[tid];
     if (MODE == SP_PLAIN) {
       out_store(y + i, ax);
@@ -455,7 +457,7 @@ k_spmv_tiled(int64_t n, int per, const int64_t* __restrict__ rp, const uint16_t*
       if (pmax) cwm = cw_term((double)r, (double)di, (double)xi);
       if (w32) out_store(w32 + i, cw_weight((double)di, (double)xi));
     } else {
-      const T dv = Q.c1 != T(0) && Q.x != CX_SCALED ? sdx[MODE == SP_CYCLE ? 4 : 0][tid] : T(0);
+      const T dv = Q.c1 != T(0) && Q.x != CX_SCALED ? sdx[cycle_mode(MODE) ? 4 : 0][tid] : T(0);
       cycle_out(Q, i, xi, ax, bi, si, dv, y);
     }
   }
