@@ -430,9 +430,10 @@ namespace rt {
 // level untiled when a tile has more than kTileMaxCols distinct columns
 int build_tiles(rt_ctx* ctx, Level& L);
 // pair form of a level from the interior neighbour lists (pair.hip): the
-// structure (*L.pair.on = false when a tile does not fit it), then per
-// assembly the values, diagonal and ghost couplings
-int build_pairs(rt_ctx* ctx, const rt_neighbors* nb, Level& L);
+// structure (L.pair.on = false when a tile does not fit it; *no_tiles is set
+// when a tile has too many columns for build_tiles as well), then per assembly
+// the values, diagonal and ghost couplings
+int build_pairs(rt_ctx* ctx, const rt_neighbors* nb, Level& L, bool* no_tiles);
 int assemble_pairs(rt_ctx* ctx, rt_matrix* A);
 // r = b - A x from the pair form (FP64), with the outputs of the CSR residual
 // product: r32 and w32 may be NULL, part and pmax receive *nparts values

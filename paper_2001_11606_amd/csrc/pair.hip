@@ -34,7 +34,7 @@ namespace {
 constexpr int kPairSlots = 512;   // hash table of 64-column blocks
 constexpr int kPairRows = 4;      // rows a wave reads at a time
 
-struct PairStat {   // per tile
+struct PairStat {   // per tile; bad: 1 it does not fit, 2 nor would a tile of CSR rows
   int32_t ext, distinct, max_row, bad;
   int64_t nnz;
 };
@@ -229,7 +229,10 @@ k_pair_build(int64_t nin, const int64_t* __restrict__ ptr, const int32_t* __rest
     nblk[t] = fits ? blocks : 0;
     goff[t] = g0;
     gcnt[t] = groups;
-    stat[t] = PairStat{ext, ext + low + owned, longest, fits ? 0 : 1, (int64_t)nnz};
+    // (a full table has missed columns, so that many at least)
+    const int distinct = ext + low + owned;
+    stat[t] = PairStat{ext, distinct, longest, fits ? 0 : distinct < kTileMaxCols ? 1 : 2,
+                       (int64_t)nnz};
   }
   __syncthreads();
   if (!fits) return;   // uniform over the block
@@ -648,7 +651,7 @@ int pair_rows(rt_ctx* ctx, Level& L, bool fp32) {
   return RT_OK;
 }
 
-int build_pairs(rt_ctx* ctx, const rt_neighbors* nb, Level& L) {
+int build_pairs(rt_ctx* ctx, const rt_neighbors* nb, Level& L, bool* no_tiles) {
   hipStream_t st = ctx->stream;
   PairForm& P = L.pair;
   P.on = false;
@@ -681,6 +684,7 @@ int build_pairs(rt_ctx* ctx, const rt_neighbors* nb, Level& L) {
   PairTotals tot;
   std::memcpy(&tot, ctx->host, sizeof(tot));
   if (tot.bad || tot.ext >= INT32_MAX) {
+    *no_tiles = tot.bad == 2;
     P = PairForm();   // the columns and offsets go back to the cache
     return RT_OK;
   }

@@ -71,3 +71,36 @@ def test_tuning_keeps_rows_only_for_a_plain_choice(ctx, batch):
     if B:
         rt.rt_batch_free(B)
     ctx.free(A, nb)
+
+
+def test_tiles_follow_the_columns(ctx):
+    """Across the row lengths at which tiles stop to fit, a matrix without a
+    hierarchy (pair form, else tiles, else neither) reports the tile columns of
+    the CSR build of one with a hierarchy."""
+    import numpy as np
+    import torch
+    import synth
+    from gpu_common import _wendland
+    from paper_2001_11606_amd import rt
+    seen = set()
+    for support in (3.0, 4.0, 4.6, 4.8, 5.0, 5.2, 5.4, 6.0):
+        prob = _wendland(3, 18)
+        prob.h = np.full_like(prob.h, support / 18)
+        dp, nb, A = gpu_system(ctx, prob, amg=rt.amg_opts(max_levels=1))
+        H = ctx.assemble(nb, dp.arrays, dp.dt, dp.c, dp.a, dp.opacity_exponent, dp.limiter,
+                         dp.limiter_k, amg=rt.amg_opts(max_levels=8))
+        a, h = ctx.matrix_info(A), ctx.matrix_info(H)
+        say(f"[tiles] support {support}: {a.nnz / a.n:.0f} entries a row, "
+            f"{a.level_tile_cols[0]} tile columns")
+        assert a.nnz == h.nnz and a.level_tile_cols[0] == h.level_tile_cols[0]
+        seen.add(a.level_tile_cols[0] > 0)
+        b = torch.ones(prob.n_interior, dtype=torch.float64, device=ctx.device)
+        xs = []
+        for M in (A, H):
+            x = torch.zeros_like(b)
+            s, _ = ctx.solve(M, b, x, rt.solve_opts(0, 0, 1e-12, 2000))
+            assert s == rt.RT_OK
+            xs.append(x)
+        assert float((xs[0] - xs[1]).abs().max()) <= 1e-10 * float(xs[1].abs().max())
+        ctx.free(A, H, nb)
+    assert seen == {False, True}
