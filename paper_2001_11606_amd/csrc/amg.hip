@@ -888,6 +888,14 @@ k_cycle_x(int64_t n, const T* x, const T* __restrict__ b, const T* __restrict__ 
 // product and its restriction took two.  Blocks past the aggregates write
 // Q.xout (where asked for), a row per thread: rows outside every aggregate
 // have an x too.
+//
+// Up to kDownMost aggregates, two rounds of resident blocks: a block holds 16
+// rows of 64 entries, and the many small aggregates of large 2-D levels (4
+// rows of 8 entries) leave it nearly empty.  Mixed V-cycle solves with a limit of
+// 1024 | 4096 | 16384 | none: 1M rows in 2-D 4.94 | 4.92 | 5.06 | 5.85 ms, 490k
+// 4.57 | 4.44 | 4.48 | 4.97 ms, 160k 2.29 | 2.25 | 2.30 | 2.29 ms; in 3-D the
+// same within 2%.
+constexpr int64_t kDownMost = 4096;
 constexpr int kDownG = 16, kDownE = 4;
 template <typename T>
 __global__ void __launch_bounds__(kBlock)
@@ -1596,7 +1604,7 @@ static int vcycle_level(rt_ctx* ctx, rt_matrix* A, size_t l, const T* b, T* out,
     RT_CHECK(form_x<T>(st, L, &x, b, t, &Q, false, tp, sk));
   }
   const int shape = spmv_effective_shape(L, level_shape<T>(L));
-  if (!L.smoothed && !kSpmvShapes[shape].tiled && L.nnz <= kSmallNnz) {
+  if (!L.smoothed && !kSpmvShapes[shape].tiled && L.nnz <= kSmallNnz && C.n <= kDownMost) {
     static_assert(kTileRows == kBlock, "a block of the row pass is a tile of the skip flags");
     const int64_t rowb = Q.xout ? (n + kTileRows - 1) / kTileRows : 0;
     hipLaunchKernelGGL(k_resid_restrict<T>, dim3((unsigned)(C.n + rowb)), dim3(kBlock), 0, st, n,
