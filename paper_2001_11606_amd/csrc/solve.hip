@@ -755,7 +755,13 @@ int pcg_core(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r, int
   const int gv = vec_blocks(n);
   *out = LoopState{};
   if (max_it <= 0) return read_state(ctx, W, out);
-  if (amg) RT_CHECK(vcycle<T>(ctx, A, r, z, W.stop));
+  if (amg) {
+    // A loop that ends where it starts (the last outer iteration of a step, the
+    // last refinement) would run dozens of launches of a V-cycle for nothing.
+    RT_CHECK(read_state(ctx, W, out));
+    if (ctx->host[S_STOP] != 0.0) return RT_OK;
+    RT_CHECK(vcycle<T>(ctx, A, r, z, W.stop));
+  }
   if (resume) {
     // the last loop on this system ended at a residual replacement: its
     // search direction p carries over, p = z + beta p with the new r.z
