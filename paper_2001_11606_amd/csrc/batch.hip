@@ -348,10 +348,6 @@ k_b_seg(int op, int nprob, const int64_t* __restrict__ row_off, int rpb,
       }
       break;
     case BOP_BETA:
-      if (PS(B_ACT) == 0.0) {   // breakdown in this iteration
-        inner[p] = 1;
-        break;
-      }
       PS(B_RR) = a;
       PS(B_BETA) = b / PS(B_RZ);
       PS(B_RZ) = b;
@@ -728,6 +724,8 @@ int b_iteration(rt_ctx* ctx, hipStream_t st, rt_batch* B, T* x, T* r, bool amg =
     RT_CHECK((launch_spmv_level<T, SP_DOT>(st, L, S::val(L), S::diag(L), S::p(B), nullptr, nullptr,
                                            S::q(B), nullptr, B->partD.p, nullptr, shape,
                                            B->tprob.p, done)));
+  // fa implies fb: a breakdown is flagged by BOP_ALPHA where !fa, else by the p
+  // update, which is then fused
   const bool fa = B->max_tiles * (kTileRows / rpb) <= kFusedSeg;
   const bool fb = B->max_tiles <= kFusedSeg;
   if (!fa) {
