@@ -107,23 +107,84 @@ void batch_reads(rt_ctx* ctx) {
          "the matrix in pair form is as it was");
   std::vector<double> b(P.b), got(P.N + H.N, 0.25), want;
   b.insert(b.end(), H.b.begin(), H.b.end());
-  for (int prec : {RT_PREC_FP64, RT_PREC_MIXED}) {
-    rt_solve_opts o{prec, 0, 1e-12, 200, 1e-3, 20, 0.0};
-    got.assign(got.size(), 0.25);
-    expect(rt_batch_solve(ctx, B, b.data(), got.data(), &o, 0, nullptr) == RT_OK, "batched solve");
-    want.clear();
-    for (Lattice* S : {&P, &H}) {
-      expect(S->solve(ctx, prec, &x) == RT_OK, "its own solve");
-      want.insert(want.end(), x.begin(), x.end());
-    }
-    double d = 0.0, w = 0.0;
-    for (size_t i = 0; i < got.size(); ++i) {
-      d = std::fmax(d, std::fabs(got[i] - want[i]));
-      w = std::fmax(w, std::fabs(want[i]));
-    }
-    expect(d <= 1e-11 * w, "the same solution");   // both stop at 1e-12 ||b||
+  rt_solve_opts o{RT_PREC_FP64, 0, 1e-12, 2, 1e-3, 20, 0.0};   // two steps
+  expect(rt_batch_solve(ctx, B, b.data(), got.data(), &o, 0, nullptr) == RT_NOT_CONVERGED,
+         "batched steps");
+  for (Lattice* S : {&P, &H}) {
+    x.assign(S->N, 0.25);
+    expect(rt_solve(ctx, S->A, S->b.data(), x.data(), &o, nullptr) == RT_NOT_CONVERGED, "its own steps");
+    want.insert(want.end(), x.begin(), x.end());
   }
+  double d = 0.0, w = 0.0;
+  for (size_t i = 0; i < got.size(); ++i) {
+    d = std::fmax(d, std::fabs(got[i] - want[i]));
+    w = std::fmax(w, std::fabs(want[i]));
+  }
+  expect(d <= 1e-12 * w, "the same vectors");
   rt_batch_free(B);
+}
+
+// the product over several tiles, the last one ragged, against the exported rows:
+// the residual of a guess, then three CG steps
+void tiles(rt_ctx* ctx) {
+  Lattice S(ctx, 24, Lattice::opts(1, 1, 1));
+  const rt::PairForm& P = S.A->levels[0].pair;
+  expect(P.on && P.ntiles == 3 && S.N % 256 != 0 && P.ext_total > 0, "three tiles");
+  rt_matrix_info info{};
+  rt_matrix_get_info(S.A, &info);
+  std::vector<int64_t> rp(S.N + 1);
+  std::vector<int32_t> col(info.nnz);
+  std::vector<double> val(info.nnz), g(S.N), diag(S.N), r(S.N), z(S.N), p(S.N), q(S.N), y(S.N);
+  expect(rt_matrix_export(ctx, S.A, rp.data(), col.data(), val.data(), g.data()) == RT_OK, "export");
+  auto mul = [&](const std::vector<double>& v, std::vector<double>* out) {
+    for (int i = 0; i < S.N; ++i) {
+      double s = 0.0;
+      for (int64_t k = rp[i]; k < rp[i + 1]; ++k) s += val[k] * v[col[k]];
+      (*out)[i] = s;
+    }
+  };
+  auto dot = [&](const std::vector<double>& a, const std::vector<double>& b) {
+    double s = 0.0;
+    for (int i = 0; i < S.N; ++i) s += a[i] * b[i];
+    return s;
+  };
+  for (int i = 0; i < S.N; ++i)
+    for (int64_t k = rp[i]; k < rp[i + 1]; ++k)
+      if (col[k] == i) diag[i] = val[k];
+  for (int its : {0, 3}) {
+    x.resize(S.N);
+    for (int i = 0; i < S.N; ++i) y[i] = x[i] = 0.5 + 0.01 * ((i * 29) % 41);
+    rt_solve_opts o{RT_PREC_FP64, 0, 1e-14, its, 1e-3, 20, 0.0};
+    rt_solve_stats st{};
+    expect(rt_solve(ctx, S.A, S.b.data(), x.data(), &o, &st) == RT_NOT_CONVERGED && st.iterations == its,
+           its ? "three steps" : "no step");
+    mul(y, &q);
+    for (int i = 0; i < S.N; ++i) {
+      r[i] = S.b[i] - q[i];
+      p[i] = z[i] = r[i] / diag[i];
+    }
+    double rz = dot(r, z);
+    for (int k = 0; k < its; ++k) {
+      mul(p, &q);
+      const double alpha = rz / dot(p, q);
+      for (int i = 0; i < S.N; ++i) {
+        y[i] += alpha * p[i];
+        r[i] -= alpha * q[i];
+        z[i] = r[i] / diag[i];
+      }
+      const double next = dot(r, z);
+      for (int i = 0; i < S.N; ++i) p[i] = z[i] + next / rz * p[i];
+      rz = next;
+    }
+    const double rel = std::sqrt(dot(r, r) / dot(S.b, S.b));
+    double d = 0.0, w = 0.0;
+    for (int i = 0; i < S.N; ++i) {
+      d = std::fmax(d, std::fabs(x[i] - y[i]));
+      w = std::fmax(w, std::fabs(y[i]));
+    }
+    // rounding of sums of some 30 terms, three times
+    expect(std::fabs(st.rel_residual - rel) <= 1e-11 * rel && d <= 1e-11 * w, "the host's values");
+  }
 }
 }  // namespace
 
@@ -136,6 +197,7 @@ int main(int argc, char** argv) {
   else if (what == "left_untiled") left_untiled(ctx);
   else if (what == "export_reads") export_reads(ctx);
   else if (what == "batch_reads") batch_reads(ctx);
+  else if (what == "tiles") tiles(ctx);
   else return 1;
   rt_destroy(ctx);
   printf(failures ? "%d failures\n" : "all ok\n", failures);

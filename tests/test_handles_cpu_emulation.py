@@ -42,7 +42,8 @@ def unit(library):
     return _build("handles")
 
 
-CHECKS = ["failed_reassembly", "left_pair_form", "left_untiled", "export_reads", "batch_reads"]
+CHECKS = ["failed_reassembly", "left_pair_form", "left_untiled", "export_reads", "batch_reads",
+          "tiles"]
 
 
 @pytest.mark.parametrize("check", CHECKS)
