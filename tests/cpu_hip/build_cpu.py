@@ -8,6 +8,7 @@ import os
 import sys
 import subprocess
 import concurrent.futures as cf
+import functools
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(os.path.dirname(HERE))
@@ -32,6 +33,7 @@ def _one(src):
     return obj
 
 
+@functools.lru_cache(maxsize=None)   # once for the test modules of one run
 def build():
     os.makedirs(OUT_DIR, exist_ok=True)
     with cf.ThreadPoolExecutor(6) as ex:
