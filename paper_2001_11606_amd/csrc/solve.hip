@@ -20,7 +20,7 @@
 //
 // Scalars (alpha, beta, r.z, ...) and thresholds stay on the device; block
 // partials of the dot products are combined in FP64 in a fixed order.  Up to
-// kFusedPartials of them, every block of the kernel that needs a scalar
+// a few thousand of them, every block of the kernel that needs a scalar
 // combines them itself (all get the same bits, block 0 keeps the record);
 // beyond that a one-block kernel does.  An iteration is then three launches
 // instead of five: below 1M rows the one-block kernels took 5.5 us each, as
@@ -566,10 +566,16 @@ template <> struct Sel<float> {
 #define RT_PARTIAL_FOLD_MIN (4 * kMaxPartials)
 #endif
 
-// partials a kernel's blocks combine themselves (32 KB read by every block)
+// Partials a kernel's blocks combine themselves: of a product (one array, 32 KB
+// read by every block) and of a vector pass (three arrays).  40 CG steps in FP64,
+// combined by every block | by a launch of their own: product partials, 3456
+// 3.75 | 3.82 ms, 4025 4.17 | 4.23, 5488 5.42 | 5.45, 8192 7.55 | 7.54; vector
+// partials, 1372 5.46 | 5.52 ms, 1688 6.47 | 6.39, 2048 7.54 | 7.46, 2680 9.86 |
+// 9.68, 4000 14.8 | 14.2 (FP32: 1688 4.98 | 5.02, 2680 7.41 | 7.34).
 #ifndef RT_FUSED_PARTIALS
 #define RT_FUSED_PARTIALS 4096
 #endif
+constexpr int kFusedVec = RT_FUSED_PARTIALS < 1536 ? RT_FUSED_PARTIALS : 1536;
 
 // np partials folded to at most kMaxPartials when they are many
 struct Partials {
@@ -670,7 +676,7 @@ int pcg_iteration(rt_ctx* ctx, rt_matrix* A, const Work& W, bool amg, T* x, T* r
   RT_CHECK(pf.end());
   // the product's partials go to partD, so that the update's blocks can read
   // them while others already write theirs
-  const bool fa = nbk <= RT_FUSED_PARTIALS, fb = gv <= RT_FUSED_PARTIALS;
+  const bool fa = nbk <= RT_FUSED_PARTIALS, fb = gv <= kFusedVec;
   if (!fa) RT_CHECK(finalize(ctx, W, FIN_ALPHA, nbk, W.partD, nullptr, nullptr, slot));
   const T* w = static_cast<const T*>(cw.w);
   double* pc = cw.mode == CW_NONE ? nullptr : W.partC;
