@@ -283,11 +283,12 @@ void rt_matrix_free(rt_matrix* A);
  * shape per level and product for all later products of A and writes the
  * timings (microseconds per product; 0 = not timed) and choices (-1 = none)
  * to *rep when rep is not NULL.  It synchronises the stream and allocates
- * temporary vectors.
+ * temporary vectors, and for a matrix in pair form its CSR rows, which stay only
+ * where a plain shape is the fastest.
  * rt_matrix_set_spmv_shape forces a shape (index into the table; -1 restores
  * the default, picked from the level's longest row: tiled shapes with two
- * rows in flight on tiled levels, else the smallest plain shape whose one
- * pass covers the row; the residual product's default is the FP64 product's
+ * rows in flight on tiled levels (a plain one of few lanes on those of up to
+ * 1.57M entries), else the smallest plain shape whose one pass covers the row; the residual product's default is the FP64 product's
  * shape).  Results of a product do not depend on the shape beyond the order
  * of floating-point additions within a row.                                  */
 #define RT_MAX_LEVELS 16

@@ -6,12 +6,13 @@
 // caller's index.  The V-scaled diffusion matrix (rows and columns = sorted
 // interior particles) is stored as a diagonal plus its off-diagonal entries.
 // Without a hierarchy that is the pair form (PairForm, pair.h): every pair
-// once, in tiles of kTileRows rows.  With one, or where a plain shape or an
-// export asks for it, it is an off-diagonal CSR with int64 row pointers, int32 columns (ascending) and FP64 values, with FP32
+// once, in tiles of kTileRows rows.  With one, or where a plain shape asks for
+// it, it is an off-diagonal CSR with int64 row pointers, int32 columns (of the
+// fine level in the order of the neighbour lists) and FP64 values, with FP32
 // copies for the mixed-precision solver.  For the sparse products each level
 // may also hold a tiled form of the same CSR: rows in tiles of kTileRows, the
-// ascending distinct columns of each tile (tile_cols, offsets tile_off) and,
-// per entry, the 16-bit position of its column in its tile's list (lcol).
+// distinct columns of each tile (tile_cols, offsets tile_off) and, per entry,
+// the 16-bit position of its column in its tile's list (lcol).
 // Value and lcol arrays carry kSpmvPad spare entries so that 16-byte chunk
 // loads may run past the last entry.
 #pragma once
@@ -270,7 +271,8 @@ struct rt_neighbors {
   rt::DevBuf<int32_t> iperm;    // user -> sorted
   rt::DevBuf<double> sp4;       // 4 x n_total: (x, y, z, h) per particle, sorted order
   rt::DevBuf<int64_t> ptr;      // n_total + 1, sorted order
-  rt::DevBuf<int32_t> idx;      // npairs, sorted indices, ascending per row
+  rt::DevBuf<int32_t> idx;      // npairs, sorted indices: interior ones first, in the order of the
+                                // cells searched, ascending within a cell
   rt::DevBuf<int32_t> n_int_nbrs;  // interior neighbours per interior row
 };
 
@@ -337,7 +339,7 @@ struct Level {
   // pair form (fine level of a matrix without a hierarchy): products run on
   // it, and the CSR above is made from the neighbour lists when something asks
   // for it (csr_rows: rp and col hold this structure, csr_vals: the values are
-  // those of the last assembly)
+  // those of the last assembly); a batch's is made from its pairs
   PairForm pair;
   bool csr_rows = false, csr_vals = false;
   DevBuf<uint64_t> code;        // Morton code of each node's cell block (candidate blocks)
