@@ -28,9 +28,9 @@ int main() {
     std::vector<double> b(P.b), first(P.N + Q.N), got(P.N + Q.N);
     b.insert(b.end(), Q.b.begin(), Q.b.end());
     auto solve = [&](int prec, std::vector<double>* x) {
-      rt_solve_opts o{prec, 0, 1e-12, 2, 1e-3, 1, 0.0};   // two steps, replayed
+      rt_solve_opts o{prec, 0, 1e-12, 1, 1e-3, 1, 0.0};   // one step, replayed
       x->assign(b.size(), 0.25);
-      return rt_batch_solve(ctx, B, b.data(), x->data(), &o, 2, nullptr);
+      return rt_batch_solve(ctx, B, b.data(), x->data(), &o, 1, nullptr);
     };
     auto near = [&](const std::vector<double>& x, const std::vector<double>& y, double bar) {
       double d = 0.0, w = 0.0;

@@ -38,10 +38,11 @@ struct Lattice {
     }
   }
   int assemble(rt_ctx* ctx, rt_amg_opts o) { return rt_assemble(ctx, nb, &in, &o, &A); }
-  int solve(rt_ctx* ctx, int precision, std::vector<double>* x, rt_solve_stats* st = nullptr) {
+  // its steps of CG from a constant guess (RT_NOT_CONVERGED)
+  int steps(rt_ctx* ctx, int precision, int its, std::vector<double>* x) {
     x->assign(N, 0.25);
-    rt_solve_opts o{precision, 0, 1e-12, 200, 1e-3, 20, 0.0};
-    return rt_solve(ctx, A, b.data(), x->data(), &o, st);
+    rt_solve_opts o{precision, 0, 1e-15, its, 1e-9, 1, 0.0};
+    return rt_solve(ctx, A, b.data(), x->data(), &o, nullptr);
   }
   Lattice(const Lattice&) = delete;
   ~Lattice() {

@@ -94,7 +94,7 @@ void solves(rt_ctx* ctx) {
           late.n = STOP_WORDS;
           cpuhip::g_late = &late;
         }
-        rt_solve_opts o{mixed ? RT_PREC_MIXED : RT_PREC_FP64, 0, 1e-12, 200, 1e-3, 20, 0.0};
+        rt_solve_opts o{mixed ? RT_PREC_MIXED : RT_PREC_FP64, 0, 1e-6, 200, 1e-3, 20, 0.0};
         status[k] = rt_solve(ctx, S.A, S.b.data(), got[k].data(), &o, &st[k]);
         cpuhip::g_late = nullptr;
       }

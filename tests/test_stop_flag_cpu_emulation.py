@@ -22,12 +22,14 @@ def test_stop_flag_is_uniform_over_a_block():
             for s in build_cpu.SOURCES if s != "solve.hip"]
     # one order of additions in both builds: no second level of the reductions
     flags = [f for f in build_cpu.FLAGS if not f.startswith("-DRT_PARTIAL_FOLD_MIN")]
+    exes = {f: os.path.join(build_cpu.OUT_DIR, f"stop_flag_{f}") for f in (4096, 0)}
+    builds = [subprocess.Popen(["g++"] + flags + [f"-DRT_FUSED_PARTIALS={f}",
+                                                  os.path.join(HERE, "cpu_hip", "stop_flag.cpp"),
+                                                  "-x", "none"] + objs + ["-o", exe])
+              for f, exe in exes.items()]
+    assert [p.wait() for p in builds] == [0, 0]
     lines = []
-    for fused in (4096, 0):
-        exe = os.path.join(build_cpu.OUT_DIR, f"stop_flag_{fused}")
-        subprocess.run(["g++"] + flags + [f"-DRT_FUSED_PARTIALS={fused}",
-                                          os.path.join(HERE, "cpu_hip", "stop_flag.cpp"),
-                                          "-x", "none"] + objs + ["-o", exe], check=True)
+    for exe in exes.values():
         r = subprocess.run([exe], capture_output=True, text=True, timeout=900,
                            env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
         assert r.returncode == 0 and "all ok" in r.stdout, r.stdout[-3000:] + r.stderr[-3000:]
